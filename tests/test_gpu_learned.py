@@ -74,6 +74,53 @@ def test_forward_backward_match_reference(B):
             o += size
 
 
+@pytest.mark.parametrize("B", [15, 16, 17, 31, 32, 33, 291, 292, 4101, 37301])
+def test_batch_sizes_at_tile_edges_match_reference(B):
+    """Row tiles (16 forward, 32 backward) with and without a remainder, one block's gradients
+    against several blocks' summed (from 292 rows on the scratch holds two), more tiles than blocks;
+    parameters and features at addresses that are only 4-byte aligned.  Bar as above: BF16 products
+    of values rounded at the same points, FP32 sums; outputs past the batch stay untouched."""
+    from paper_2204_04321_amd import _lib
+    rng = np.random.default_rng(B)
+    params = ol.init_params(rng)
+    for W, b in params:
+        b[:] = rng.normal(size=b.shape) * 0.1
+    flat = _flat(params)
+    params = _unflat(flat.astype(np.float64))
+    X = rng.normal(size=(B, 10)).astype(np.float32)
+    dY = (rng.normal(size=(B, 22)) / B).astype(np.float32)
+
+    def at_odd(a):
+        t = torch.full((a.size + 2,), 7.0, dtype=torch.float32, device="cuda")
+        t[1:-1].copy_(torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32).ravel()))
+        return t
+
+    def ptr(t):
+        return t.data_ptr() + 4
+    P, Xd, Yd, dYd = at_odd(flat), at_odd(X), at_odd(np.zeros((B, 22))), at_odd(dY)
+    acts, G = at_odd(np.zeros((3, B, 128))), at_odd(np.full(flat.size, np.nan))
+    dacts = at_odd(np.full((2, B, 128), np.nan))
+    L, s = _lib.lib(), torch.cuda.current_stream().cuda_stream
+    _lib.check(L.fo_mlp_forward(ptr(P), ptr(Xd), B, ptr(acts), ptr(Yd), s))
+    _lib.check(L.fo_mlp_backward(ptr(P), ptr(Xd), B, ptr(acts), ptr(dYd), ptr(dacts), ptr(G), s))
+    G1 = G.clone()
+    _lib.check(L.fo_mlp_backward(ptr(P), ptr(Xd), B, ptr(acts), ptr(dYd), ptr(dacts), ptr(G), s))
+    torch.cuda.synchronize()
+    assert torch.equal(G, G1)
+    for t in (P, Xd, Yd, dYd, acts, G, dacts):
+        assert t[0].item() == 7.0 and t[-1].item() == 7.0
+    Yo, ao = ol.mlp_forward(params, X.astype(np.float64))
+    Go = ol.mlp_backward(params, ao, dY.astype(np.float64))
+    Yg, Gg = Yd[1:-1].cpu().numpy().reshape(B, 22), G[1:-1].cpu().numpy()
+    assert np.linalg.norm(Yg - Yo) <= 1e-3 * np.linalg.norm(Yo)
+    o = 0
+    for (i, j), (gw, gb) in zip(zip(ol.LAYERS[:-1], ol.LAYERS[1:]), Go):
+        for ref in (gw.ravel(), gb):
+            a = Gg[o:o + ref.size]
+            assert np.linalg.norm(a - ref) <= 1e-3 * np.linalg.norm(ref) + 1e-12, (i, j, ref.size)
+            o += ref.size
+
+
 def test_adam_matches_reference():
     from paper_2204_04321_amd.api import MLP
     rng = np.random.default_rng(5)
