@@ -33,6 +33,8 @@
 // + r 2 nlev(kr) + 2 (kc - max(kr-1, 0)) + d.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "fo_internal.h"
 
 // Multiply-adds are fused only where one source expression holds both operations, so
@@ -48,72 +50,31 @@ constexpr int WAVE = 64;
 constexpr double G1 = 0.21132486540518711775;   // 1/2 - 1/(2 sqrt 3)
 constexpr double G2 = 0.78867513459481288225;   // 1/2 + 1/(2 sqrt 3)
 
-template <int NV>
-struct Elem;
-template <>
-struct Elem<3> {  // wedge: P1 triangle x linear in zeta
-  static constexpr int NPE = 6, NQ = 6, NQB = 3;
-};
-template <>
-struct Elem<4> {  // hexahedron: bilinear quad x linear in zeta
-  static constexpr int NPE = 8, NQ = 8, NQB = 4;
-};
-
-// Quadrature on the reference cell ([0,1]^2 or the unit triangle, zeta in [0,1]):
-// weights, zeta, 2D basis values and reference derivatives at each point.
+// Quadrature of a prism (the unit triangle times zeta in [0,1]: a degree-2 rule of three points
+// times two Gauss points) and of its lower face: weights, zeta, 2D basis values and reference
+// derivatives at each point.
+constexpr int NQ = 6, NQB = 3;
 struct QTable {
-  double w[8], zeta[8], lam[8][4], dlx[8][4], dly[8][4];
-  double bw[4], blam[4][4], bdlx[4][4], bdly[4][4];
+  double w[NQ], zeta[NQ], lam[NQ][3];
+  double bw[NQB], blam[NQB][3], bdlx[NQB][3], bdly[NQB][3];
 };
 
-__constant__ QTable kQ[2];   // [0] wedge, [1] hex
+__constant__ QTable kQ;
 
-constexpr void basis2d_tab(int nv, double xi, double eta, double *lam, double *dx, double *dy) {
-  if (nv == 3) {
-    lam[0] = 1.0 - xi - eta; lam[1] = xi; lam[2] = eta; lam[3] = 0.0;
-    dx[0] = -1.0; dx[1] = 1.0; dx[2] = 0.0; dx[3] = 0.0;
-    dy[0] = -1.0; dy[1] = 0.0; dy[2] = 1.0; dy[3] = 0.0;
-  } else {
-    const double mx = 1.0 - xi, my = 1.0 - eta;
-    lam[0] = mx * my; lam[1] = xi * my; lam[2] = xi * eta; lam[3] = mx * eta;
-    dx[0] = -my; dx[1] = my; dx[2] = eta; dx[3] = -eta;
-    dy[0] = -mx; dy[1] = -xi; dy[2] = xi; dy[3] = mx;
-  }
-}
-
-constexpr QTable make_table(int nv) {
+constexpr QTable make_table() {
   QTable t{};
-  const int nq = nv == 3 ? 6 : 8, nqb = nv == 3 ? 3 : 4;
-  for (int q = 0; q < nq; ++q) {
-    double xi = 0, eta = 0, zeta = 0, w = 0;
-    if (nv == 3) {
-      const int tq = q % 3;
-      xi = (tq == 1) ? 2.0 / 3.0 : 1.0 / 6.0;
-      eta = (tq == 2) ? 2.0 / 3.0 : 1.0 / 6.0;
-      zeta = (q < 3) ? G1 : G2;
-      w = 1.0 / 12.0;
-    } else {
-      xi = (q & 1) ? G2 : G1;
-      eta = (q & 2) ? G2 : G1;
-      zeta = (q & 4) ? G2 : G1;
-      w = 0.125;
-    }
-    t.w[q] = w;
-    t.zeta[q] = zeta;
-    basis2d_tab(nv, xi, eta, t.lam[q], t.dlx[q], t.dly[q]);
+  for (int q = 0; q < NQ; ++q) {
+    const int tq = q % 3;
+    const double xi = (tq == 1) ? 2.0 / 3.0 : 1.0 / 6.0, eta = (tq == 2) ? 2.0 / 3.0 : 1.0 / 6.0;
+    t.w[q] = 1.0 / 12.0;
+    t.zeta[q] = (q < 3) ? G1 : G2;
+    t.lam[q][0] = 1.0 - xi - eta; t.lam[q][1] = xi; t.lam[q][2] = eta;
   }
-  for (int r = 0; r < nqb; ++r) {
-    double xi = 0, eta = 0;
-    if (nv == 3) {
-      xi = (r == 1) ? 2.0 / 3.0 : 1.0 / 6.0;
-      eta = (r == 2) ? 2.0 / 3.0 : 1.0 / 6.0;
-      t.bw[r] = 1.0 / 6.0;
-    } else {
-      xi = (r & 1) ? G2 : G1;
-      eta = (r & 2) ? G2 : G1;
-      t.bw[r] = 0.25;
-    }
-    basis2d_tab(nv, xi, eta, t.blam[r], t.bdlx[r], t.bdly[r]);
+  for (int r = 0; r < NQB; ++r) {
+    t.bw[r] = 1.0 / 6.0;
+    for (int i = 0; i < 3; ++i) t.blam[r][i] = t.lam[r][i];
+    t.bdlx[r][0] = -1.0; t.bdlx[r][1] = 1.0;
+    t.bdly[r][0] = -1.0; t.bdly[r][2] = 1.0;
   }
   return t;
 }
@@ -300,16 +261,97 @@ __device__ __forceinline__ void tet_layer(const MeshView &m, int ra, int picard,
   }
 }
 
+// Metadata of a task's vertex columns, one column per lane (a task has at most 64)
+struct TaskColumns {
+  int deg, soff, col_lo, col_hi;
+};
+
+__device__ __forceinline__ TaskColumns load_columns(const MeshView &m, int vb, int nvt, int lane) {
+  TaskColumns t = {0, 0, 0, 0};
+  if (lane < nvt) {
+    t.deg = m.deg[vb + lane];
+    t.soff = m.slot_off[vb + lane];
+    const int64_t c = m.colptr[vb + lane];
+    t.col_lo = int(uint32_t(uint64_t(c)));
+    t.col_hi = int(uint32_t(uint64_t(c) >> 32));
+  }
+  return t;
+}
+
+template <bool JAC>
+__device__ __forceinline__ void clear_windows(const MeshView &m, double *Jw, double *Rw, int vb, int ve, int max_slot,
+                                              int max_tv, int lane) {
+  if constexpr (JAC) {
+    const int slot_size = m.slot_off[ve - 1] + 12 * m.deg[ve - 1];
+    for (int e = lane; e < slot_size; e += WAVE) { Jw[e] = 0.0; Jw[max_slot + e] = 0.0; }
+  }
+  for (int e = lane; e < 2 * (ve - vb); e += WAVE) { Rw[e] = 0.0; Rw[2 * max_tv + e] = 0.0; }
+}
+
+// Copies a finished level's window to its CSR rows and clears it for level + 2 (store = false:
+// clears it only).  Four vertex columns at a time: all LDS reads of a batch are issued before
+// the first global store, so one LDS latency is exposed per batch, not per chunk.  Each lane moves
+// two consecutive entries: one 16-byte LDS read and one 16-byte clearing write per column cover
+// up to 128 entries (degree <= 10 on three levels).
+template <bool JAC, class JT>
+__device__ __forceinline__ void copy_out(const TaskColumns &cols, int lev, int slot, bool store, int vb, int nvt,
+                                         int L, double *Jw, double *Rw, int max_slot, int max_tv, int lane,
+                                         double *__restrict__ R, JT *__restrict__ J) {
+  const int nl = nlev(lev, L);
+  const int lk = cumlev(lev);
+  double *wb = Jw + slot * max_slot;   // 16-byte aligned, as is every column's slot
+  for (int i0 = 0; i0 < nvt; i0 += 4) {
+    if constexpr (JAC) {
+      double2 val[4];
+      int nn[4], so[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int ii = i0 + i < nvt ? i0 + i : nvt - 1;
+        so[i] = __builtin_amdgcn_readlane(cols.soff, ii);
+        nn[i] = i0 + i < nvt ? 4 * nl * __builtin_amdgcn_readlane(cols.deg, ii) : 0;
+        const int e = 2 * lane;
+        val[i] = *reinterpret_cast<const double2 *>(wb + so[i] + (e < nn[i] ? e : 0));
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (i0 + i >= nvt) break;
+        const int ii = i0 + i;
+        const int D = __builtin_amdgcn_readlane(cols.deg, ii);
+        const int64_t col = int64_t(unsigned(__builtin_amdgcn_readlane(cols.col_lo, ii))) |
+                            (int64_t(__builtin_amdgcn_readlane(cols.col_hi, ii)) << 32);
+        JT *dst = J + col + int64_t(4) * D * lk;
+        double *src = wb + so[i];
+        const int e = 2 * lane;   // nn is a multiple of 4, so e < nn implies e + 1 < nn
+        if (e < nn[i]) {
+          if (store) store2_nt(dst + e, val[i].x, val[i].y);
+          *reinterpret_cast<double2 *>(src + e) = make_double2(0.0, 0.0);
+        }
+        for (int f = e + 2 * WAVE; f < nn[i]; f += 2 * WAVE) {
+          const double2 w = *reinterpret_cast<const double2 *>(src + f);
+          if (store) store2_nt(dst + f, w.x, w.y);
+          *reinterpret_cast<double2 *>(src + f) = make_double2(0.0, 0.0);
+        }
+      }
+    }
+    if (lane < 8 && i0 + (lane >> 1) < nvt) {
+      const int u = vb + i0 + (lane >> 1);
+      double *rs = Rw + slot * 2 * max_tv + 2 * (u - vb) + (lane & 1);
+      if (R && store) R[2 * (int64_t(u) * (L + 1) + lev) + (lane & 1)] = *rs;
+      *rs = 0.0;
+    }
+  }
+}
+
 // One wave = one task (a run of vertex columns); one lane = one (v, t) item.
 // N3 selects the n = 3 viscosity power; JAC adds the Jacobian; JT is its value type
 // (double, or float with FP32 derivative arithmetic over the FP64 primal).
-template <int NV, bool JAC, class JT, bool N3, bool TET = false>
+template <bool JAC, class JT, bool N3, bool TET>
 __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, const double *__restrict__ U,
                                            double *__restrict__ R, JT *__restrict__ J, int picard,
                                            int max_slot, int max_tv, unsigned char *smem) {
-  constexpr int NQ = Elem<NV>::NQ, NQB = Elem<NV>::NQB;
+  constexpr int NV = 3;
   using AT = JT;   // derivative arithmetic type
-  const QTable &Q = kQ[NV == 3 ? 0 : 1];
+  const QTable &Q = kQ;
   // The level windows accumulate in FP64 for either value type: FP32 LDS atomics on this
   // scatter pattern saturate the LDS data path (measured), FP64 ones do not.
   double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
@@ -327,7 +369,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
   // that vertex is always corner 0 (a cyclic rotation keeps the triangle's orientation, and
   // the triangle rules are invariant under it): its selections become constants and its
   // Jacobian entries can be carried from layer to layer in registers (below).
-  constexpr bool ROT = NV == 3 && !TET;
+  constexpr bool ROT = !TET;
   const int rot = ROT ? al : 0;
   const int al_own = ROT ? 0 : al;
   const int Dv = m.deg[v];
@@ -340,7 +382,6 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
   // reload costs a scratch round trip that serialises the layer's gather loads.
   const uint32_t imeta_base = uint32_t(soff) | (uint32_t(Dv) << 12) | (uint32_t(v - vb) << 20);
   const uint32_t imeta_cell = imeta_base | (uint32_t(al_own) << 26);
-  const int slot_size = m.slot_off[ve - 1] + 12 * m.deg[ve - 1];
   // 8 bits per corner: its rank in v's neighbour list
   uint32_t irank = act ? m.item_rank[item] : 0u;
   if constexpr (ROT) irank = ((irank >> (8 * rot)) | (irank << (8 * (3 - rot)))) & 0xFFFFFFu;
@@ -400,7 +441,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
   }
   // P1 triangles: the horizontal basis gradients and the map determinant are constant
   double lxc[NV], lyc[NV], detc = 0, sxc = 0, syc = 0;
-  if constexpr (NV == 3) {
+  {
     const double x_xi = xl[1] - xl[0], x_eta = xl[2] - xl[0];
     const double y_xi = yl[1] - yl[0], y_eta = yl[2] - yl[0];
     detc = x_xi * y_eta - x_eta * y_xi;
@@ -410,28 +451,12 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
 #pragma unroll
     for (int i = 0; i < NV; ++i) { sxc += su[i] * lxc[i]; syc += su[i] * lyc[i]; }
   }
-  double lx_al = 0.0, ly_al = 0.0;
-  if constexpr (NV == 3) {
-    lx_al = ROT ? lxc[0] : sel4(al, lxc[0], lxc[1], lxc[2], 0.0);
-    ly_al = ROT ? lyc[0] : sel4(al, lyc[0], lyc[1], lyc[2], 0.0);
-  }
+  const double lx_al = ROT ? lxc[0] : sel4(al, lxc[0], lxc[1], lxc[2], 0.0);
+  const double ly_al = ROT ? lyc[0] : sel4(al, lyc[0], lyc[1], lyc[2], 0.0);
 
-  // metadata of the task's vertex columns, one per lane (a task has at most 64 columns)
   const int nvt = ve - vb;
-  int my_deg = 0, my_soff = 0, my_col_lo = 0, my_col_hi = 0;
-  if (lane < nvt) {
-    my_deg = m.deg[vb + lane];
-    my_soff = m.slot_off[vb + lane];
-    const int64_t c = m.colptr[vb + lane];
-    my_col_lo = int(uint32_t(uint64_t(c)));
-    my_col_hi = int(uint32_t(uint64_t(c) >> 32));
-  }
-
-  // ---- zero both level windows -------------------------------------------------------------
-  if constexpr (JAC) {
-    for (int e = lane; e < slot_size; e += WAVE) { Jw[e] = 0.0; Jw[max_slot + e] = 0.0; }
-  }
-  for (int e = lane; e < 2 * (ve - vb); e += WAVE) { Rw[e] = 0.0; Rw[2 * max_tv + e] = 0.0; }
+  const TaskColumns cols = load_columns(m, vb, nvt, lane);
+  clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
   wave_sync();
 
   // ---- bed friction on the lower face of the bottom layer: rows of v's level-0 node, added
@@ -506,10 +531,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
 #pragma unroll
     for (int i = 0; i < NV; ++i) vidk[i] = lvid[i];
     // one statement, so that reloads of spilled operands are issued together
-    if constexpr (NV == 3)
-      asm volatile("" : "+v"(ipy), "+v"(imt), "+v"(vidk[0]), "+v"(vidk[1]), "+v"(vidk[2]));
-    else
-      asm volatile("" : "+v"(ipy), "+v"(imt), "+v"(vidk[0]), "+v"(vidk[1]), "+v"(vidk[2]), "+v"(vidk[NV - 1]));
+    asm volatile("" : "+v"(ipy), "+v"(imt), "+v"(vidk[0]), "+v"(vidk[1]), "+v"(vidk[2]));
     const int al = int(imt >> 26), soff = int(imt & 4095u), Dv = int((imt >> 12) & 255u);
     const int rloc = 2 * int((imt >> 20) & 63u);
     // gather levels k and k+1 (repeat loads hit the cache)
@@ -534,7 +556,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
     }
     // wedges: x/y slopes of z, u, v at fixed zeta are (level-k sum) + zeta (increment sum)
     double HS[12];
-    if constexpr (NV == 3 && !TET) {
+    if constexpr (!TET) {
 #pragma unroll
       for (int h = 0; h < 12; ++h) HS[h] = 0.0;
 #pragma unroll
@@ -566,7 +588,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
     AT FA[2][4][2], FH[2][4][2], FB[2][4][3];
     if constexpr (TET) {
       tet_layer<AT, JAC, N3>(m, al, picard, xr, yr, zlo, dz, ulo, du, vlo, dv, sv, Rb0, Rb1, Rt0, Rt1, Jx);
-    } else if constexpr (NV == 3) {
+    } else {
       // Wedges.  The residual-only kernel runs the same loop without the tangents, so
       // both kernels produce the same residual bits.  The tangents are accumulated in
       // factorised form.  Every tangent
@@ -654,140 +676,6 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
           }
         }
       }
-    } else {
-#pragma unroll 1
-      for (int q = 0; q < NQ; ++q) {
-        const double zeta = Q.zeta[q], l0 = 1.0 - zeta, l1 = zeta;
-        double lam[NV], lx[NV], ly[NV];
-        double det, sx, sy;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) lam[i] = Q.lam[q][i];
-        if constexpr (NV == 3) {
-#pragma unroll
-          for (int i = 0; i < NV; ++i) { lx[i] = lxc[i]; ly[i] = lyc[i]; }
-          det = detc; sx = sxc; sy = syc;
-        } else {
-          double x_xi = 0, x_eta = 0, y_xi = 0, y_eta = 0;
-#pragma unroll
-          for (int i = 0; i < NV; ++i) {
-            x_xi += xl[i] * Q.dlx[q][i]; x_eta += xl[i] * Q.dly[q][i];
-            y_xi += yl[i] * Q.dlx[q][i]; y_eta += yl[i] * Q.dly[q][i];
-          }
-          det = x_xi * y_eta - x_eta * y_xi;
-          const double iG = rcp64(det);
-          const double i00 = y_eta * iG, i01 = -x_eta * iG, i10 = -y_xi * iG, i11 = x_xi * iG;
-          sx = 0; sy = 0;
-#pragma unroll
-          for (int i = 0; i < NV; ++i) {
-            lx[i] = Q.dlx[q][i] * i00 + Q.dly[q][i] * i10;
-            ly[i] = Q.dlx[q][i] * i01 + Q.dly[q][i] * i11;
-            sx += su[i] * lx[i];
-            sy += su[i] * ly[i];
-          }
-        }
-        // vertical map: z_zeta and the slopes of z along x, y at fixed zeta
-        double zze = 0, zxs, zys, ucx, ucy, vcx, vcy, dum = 0, dvm = 0;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          zze = fma(lam[i], dz[i], zze);
-          dum = fma(lam[i], du[i], dum);
-          dvm = fma(lam[i], dv[i], dvm);
-        }
-        if constexpr (NV == 3) {
-          zxs = fma(zeta, HS[1], HS[0]); zys = fma(zeta, HS[3], HS[2]);
-          ucx = fma(zeta, HS[5], HS[4]); ucy = fma(zeta, HS[7], HS[6]);
-          vcx = fma(zeta, HS[9], HS[8]); vcy = fma(zeta, HS[11], HS[10]);
-        } else {
-          zxs = zys = ucx = ucy = vcx = vcy = 0;
-#pragma unroll
-          for (int i = 0; i < NV; ++i) {
-            const double zc = fma(zeta, dz[i], zlo[i]);
-            const double uc = fma(zeta, du[i], ulo[i]);
-            const double vc = fma(zeta, dv[i], vlo[i]);
-            zxs = fma(lx[i], zc, zxs); zys = fma(ly[i], zc, zys);
-            ucx = fma(lx[i], uc, ucx); ucy = fma(ly[i], uc, ucy);
-            vcx = fma(lx[i], vc, vcx); vcy = fma(ly[i], vc, vcy);
-          }
-        }
-        const double iz = rcp64(zze);
-        const double px = -zxs * iz, py = -zys * iz;        // d zeta / dx, d zeta / dy
-        const double W = Q.w[q] * det * zze;
-        // velocity gradient, strain rates, viscosity
-        const double ux = ucx + px * dum, uy = ucy + py * dum, uz = iz * dum;
-        const double vx = vcx + px * dvm, vy = vcy + py * dvm, vz = iz * dvm;
-        const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = 0.5 * uz, eyz = 0.5 * vz;
-        const double qq = exx * exx + eyy * eyy + exx * eyy + exy * exy + exz * exz + eyz * eyz;
-        const double qe = qq + m.eps0_sq;
-        double mu;
-        if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
-        else mu = m.visc_pref * powq(qe, m.visc_exp);
-        const double s2 = 2.0 * mu * W;
-        const double t2 = picard ? 0.0 : 2.0 * (m.visc_exp * mu * rcp64(qe)) * W;
-        const double e1x = 2.0 * exx + eyy, e1y = exy, e1z = exz;
-        const double e2x = exy, e2y = exx + 2.0 * eyy, e2z = eyz;
-        const double gvx = W * m.rho_g * sx, gvy = W * m.rho_g * sy;
-        // v's own nodes in this cell: corner al at the lower and upper level
-        const double lam_a = sel4(al, lam[0], lam[1], lam[2], lam[NV - 1]);
-        double lxa, lya;
-        if constexpr (NV == 3) { lxa = lx_al; lya = ly_al; }
-        else { lxa = sel4(al, lx[0], lx[1], lx[2], lx[NV - 1]); lya = sel4(al, ly[0], ly[1], ly[2], ly[NV - 1]); }
-        const double abx = l0 * lxa - lam_a * px, aby = l0 * lya - lam_a * py, abz = -lam_a * iz;
-        const double atx = l1 * lxa + lam_a * px, aty = l1 * lya + lam_a * py, atz = lam_a * iz;
-        const double gb0 = e1x * abx + e1y * aby + e1z * abz, gb1 = e2x * abx + e2y * aby + e2z * abz;
-        const double gt0 = e1x * atx + e1y * aty + e1z * atz, gt1 = e2x * atx + e2y * aty + e2z * atz;
-        const double nb = lam_a * l0, nt = lam_a * l1;     // v's basis functions at q
-        Rb0 = fma(s2, gb0, fma(gvx, nb, Rb0));
-        Rb1 = fma(s2, gb1, fma(gvy, nb, Rb1));
-        Rt0 = fma(s2, gt0, fma(gvx, nt, Rt0));
-        Rt1 = fma(s2, gt1, fma(gvy, nt, Rt1));
-        if constexpr (JAC) {
-          // row side: 2 mu W times the row node's gradient (with the constant factors of
-          // d(eps_c . grad N_a)/dU folded into 2x copies here and 1/2 copies on the column
-          // side; all scalings are exact), and 2 mu' W times its strain projection
-          AT RA[2][7];
-          {
-            const AT s2a = AT(s2), t2a = AT(t2);
-            const AT ax[2] = {AT(abx), AT(atx)}, ay[2] = {AT(aby), AT(aty)}, az[2] = {AT(abz), AT(atz)};
-            const AT g0[2] = {AT(gb0), AT(gt0)}, g1[2] = {AT(gb1), AT(gt1)};
-#pragma unroll
-            for (int a = 0; a < 2; ++a) {
-              const AT Ax = s2a * ax[a], Ay = s2a * ay[a];
-              RA[a][0] = Ax; RA[a][1] = Ay; RA[a][2] = s2a * az[a];
-              RA[a][3] = Ax + Ax; RA[a][4] = Ay + Ay;
-              RA[a][5] = t2a * g0[a]; RA[a][6] = t2a * g1[a];
-            }
-          }
-          // column side in the derivative type: d(grad N_b) and d(eps_e^2) along (b, u|v)
-          const AT pxa = AT(px), pya = AT(py), izh = AT(0.5 * iz);
-          const AT e1xa = AT(e1x), e1ya = AT(e1y), e1z2 = AT(2.0 * e1z);
-          const AT e2xa = AT(e2x), e2ya = AT(e2y), e2z2 = AT(2.0 * e2z);
-#pragma unroll
-          for (int j = 0; j < NV; ++j) {
-            const AT lxj = AT(lx[j]), lyj = AT(ly[j]), lmj = AT(lam[j]);
-#pragma unroll
-            for (int lev = 0; lev < 2; ++lev) {
-              const AT ll = AT(lev ? l1 : l0);
-              const AT dl = lev ? lmj : -lmj;
-              const AT bx = fma(ll, lxj, dl * pxa), by = fma(ll, lyj, dl * pya), bzh = dl * izh;
-              const AT bxh = AT(0.5) * bx, byh = AT(0.5) * by;
-              const AT gu = fma(e1xa, bx, fma(e1ya, by, e1z2 * bzh));   // d(eps_e^2)/dU_(b,u)
-              const AT gv = fma(e2xa, bx, fma(e2ya, by, e2z2 * bzh));   // d(eps_e^2)/dU_(b,v)
-#pragma unroll
-              for (int a = 0; a < 2; ++a) {
-                AT &uu = Jx[a][0][0][j][lev], &uv = Jx[a][0][1][j][lev];
-                AT &vu = Jx[a][1][0][j][lev], &vv = Jx[a][1][1][j][lev];
-                const AT Ax = RA[a][0], Ay = RA[a][1], Az = RA[a][2], Ax2 = RA[a][3], Ay2 = RA[a][4];
-                const AT T0 = RA[a][5], T1 = RA[a][6];
-                uu = fma(Ax2, bx, uu); uu = fma(Ay, byh, uu); uu = fma(Az, bzh, uu); uu = fma(T0, gu, uu);
-                uv = fma(Ax, by, uv); uv = fma(Ay, bxh, uv); uv = fma(T0, gv, uv);
-                vu = fma(Ay, bx, vu); vu = fma(Ax, byh, vu); vu = fma(T1, gu, vu);
-                vv = fma(Ax, bxh, vv); vv = fma(Ay2, by, vv); vv = fma(Az, bzh, vv); vv = fma(T1, gv, vv);
-              }
-            }
-          }
-        }
-      }
-  
     }
 
     // The window adds run at wave priority 1 and the copy-out at 2 (below): the other wave's
@@ -816,7 +704,7 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
 #pragma unroll
           for (int cd = 0; cd < 4; ++cd) {
             const int c = cd >> 1, d = cd & 1;
-            if constexpr (NV == 3 && !TET) {
+            if constexpr (!TET) {
               const AT Ux = FH[a][cd][0] - FA[a][cd][0], Uy = FH[a][cd][1] - FA[a][cd][1];
 #pragma unroll
               for (int j = 0; j < NV; ++j) {
@@ -850,83 +738,347 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
     wave_sync();
 
     // ---- level k is complete: copy it to its CSR rows and clear it for level k+2 ------------
-    // Copy out four vertex columns at a time: all LDS reads of a batch are issued before
-    // the first global store, so one LDS latency is exposed per batch, not per chunk.
-    auto flush = [&](int lev_k, int slot) {
-      const int nl = nlev(lev_k, L);
-      const int lk = cumlev(lev_k);
-      double *wb = Jw + slot * max_slot;   // 16-byte aligned, as is every column's slot
-      for (int i0 = 0; i0 < nvt; i0 += 4) {
-        if constexpr (JAC) {
-          // each lane moves two consecutive entries: one 16-byte LDS read and one 16-byte
-          // clearing write per column cover up to 128 entries (degree <= 10 at nl = 3)
-          double2 val[4];
-          int nn[4], so[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int ii = i0 + i < nvt ? i0 + i : nvt - 1;
-            so[i] = __builtin_amdgcn_readlane(my_soff, ii);
-            nn[i] = i0 + i < nvt ? 4 * nl * __builtin_amdgcn_readlane(my_deg, ii) : 0;
-            const int e = 2 * lane;
-            val[i] = *reinterpret_cast<const double2 *>(wb + so[i] + (e < nn[i] ? e : 0));
-          }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (i0 + i >= nvt) break;
-            const int ii = i0 + i;
-            const int D = __builtin_amdgcn_readlane(my_deg, ii);
-            const int64_t col = int64_t(unsigned(__builtin_amdgcn_readlane(my_col_lo, ii))) |
-                                (int64_t(__builtin_amdgcn_readlane(my_col_hi, ii)) << 32);
-            JT *dst = J + col + int64_t(4) * D * lk;
-            double *src = wb + so[i];
-            const int e = 2 * lane;   // nn is a multiple of 4, so e < nn implies e + 1 < nn
-            if (e < nn[i]) {
-              store2_nt(dst + e, val[i].x, val[i].y);
-              *reinterpret_cast<double2 *>(src + e) = make_double2(0.0, 0.0);
-            }
-            for (int f = e + 2 * WAVE; f < nn[i]; f += 2 * WAVE) {
-              const double2 w = *reinterpret_cast<const double2 *>(src + f);
-              store2_nt(dst + f, w.x, w.y);
-              *reinterpret_cast<double2 *>(src + f) = make_double2(0.0, 0.0);
-            }
-          }
-        }
-        if (lane < 8 && i0 + (lane >> 1) < nvt) {
-          const int u = vb + i0 + (lane >> 1);
-          double *rs = Rw + slot * 2 * max_tv + 2 * (u - vb) + (lane & 1);
-          if (R) R[2 * (int64_t(u) * (L + 1) + lev_k) + (lane & 1)] = *rs;
-          *rs = 0.0;
-        }
-      }
-    };
     // The copy-out runs at raised wave priority: its LDS reads and streaming stores then issue
     // ahead of the other wave's quadrature work instead of queuing behind it (FP64 R+J -2%,
     // FP32 -2.5%; raising the gather instead was slower).
     __builtin_amdgcn_s_setprio(2);
-    flush(k, cur);
-    if (k == L - 1) flush(L, nxt);
+    copy_out<JAC>(cols, k, cur, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     wave_sync();
     __builtin_amdgcn_s_setprio(0);
 
   }
 }
 
-template <int NV, bool JAC, class JT, bool N3, bool TET>
-__global__ __launch_bounds__(WAVE, NV == 3 ? 2 : 1) void owner_kernel(MeshView m, const int4 *__restrict__ tasks,
-                                                     const double *__restrict__ U, double *__restrict__ R,
-                                                     JT *__restrict__ J, int picard, int max_slot,
-                                                     int max_tv) {
+// ---- hexahedra ----------------------------------------------------------------------------
+// Four lanes per item, one per Gauss point of the base quadrilateral (two zeta points each): a
+// lane evaluates the physics of its two points once, and the entries of the item's rows are
+// formed from its own point and summed over the four lanes by two exchanges, after which every
+// lane holds a quarter of them.  Nothing of the Jacobian stays in registers across points
+// (one lane per item needed 64 accumulators and ran one wave per SIMD), so four waves share
+// a SIMD, and the horizontal map, gradients and the slopes of bed and thickness at
+// a lane's point are constants of the whole column.
+//
+// Exchanges without selections: lane bits b0 = lane & 1, b1 = lane >> 1 & 1.  A lane forms the
+// entries at level b0 as "kept" and at the other level as "sent" (lane-constant weights l_b0 and
+// l_(1-b0)), and walks the corners in the order jj -> (jj + 2 b1) & 3, so that its first two
+// are kept in the second exchange.  It ends with corners 2 b1 and 2 b1 + 1 at level b0.
+__device__ __forceinline__ int quad_xor_i(int v, bool two) {
+  return two ? __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+}
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(quad_xor_i(int(uint32_t(u)), X == 2));
+  const uint32_t hi = uint32_t(quad_xor_i(int(uint32_t(u >> 32)), X == 2));
+  return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
+}
+template <int X>
+__device__ __forceinline__ float quad_xor(float v) {
+  return __builtin_bit_cast(float, quad_xor_i(__builtin_bit_cast(int, v), X == 2));
+}
+
+constexpr int HEX_ITEMS = WAVE / 4;   // items per pass of a wave
+
+// The levels kb <= k < ke of a task's columns (and level L if ke = L).  kb > 0 starts with layer
+// kb - 1, whose lower rows belong to the range below and are dropped.
+template <bool JAC, class JT, bool N3>
+__device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, const double *__restrict__ U,
+                                         double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
+                                         int max_tv, int kb, int ke, unsigned char *smem) {
+  using AT = JT;   // derivative arithmetic type
+  double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
+  double *Rw = reinterpret_cast<double *>(smem + (JAC ? 2 * size_t(max_slot) * sizeof(double) : 0));  // [2][2 max_tv]
+  const int lane = threadIdx.x, b0 = lane & 1, b1 = (lane >> 1) & 1;
+  const int vb = task.y, ve = task.z, ib = task.w, ie = m.vc_ptr[ve];
+  const int L = m.L, nvt = ve - vb;
+  const TaskColumns cols = load_columns(m, vb, nvt, lane);
+  // this lane's base point and its basis, corners in the lane's order
+  const double xi = b0 ? G2 : G1, eta = b1 ? G2 : G1, mx = 1.0 - xi, my = 1.0 - eta;
+  double lam[4], lx[4], ly[4];
+  {
+    const double la[4] = {mx * my, xi * my, xi * eta, mx * eta};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lam[j] = b1 ? la[(j + 2) & 3] : la[j];
+  }
+  clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
+
+  // item constants: corner ids, gradients at the lane's point, weight x determinant x thickness,
+  // the slopes of s, bed and H there, and the item's own corner's basis
+  int vid[4], Dv = 0, soff = 0, rloc = 0;
+  uint32_t rk = 0u;
+  bool act = false;
+  double wH = 0, sx = 0, sy = 0, iH = 0, Bx = 0, By = 0, Hx = 0, Hy = 0, lam_a = 0, lxa = 0, lya = 0;
+  auto load_item = [&](int first) {
+    act = first + (lane >> 2) < ie;
+    const int item = act ? first + (lane >> 2) : ib;
+    const int v = m.item_vtx[item], t = m.vc_idx[item], al = (int(m.vc_pos[item]) - 2 * b1) & 3;
+    Dv = m.deg[v];
+    soff = m.slot_off[v];
+    rloc = 2 * (v - vb);
+    rk = m.item_rank[item];
+    if (b1) rk = (rk >> 16) | (rk << 16);
+    const int4 c4 = *reinterpret_cast<const int4 *>(m.cells + 4 * int64_t(t));
+    vid[0] = b1 ? c4.z : c4.x;
+    vid[1] = b1 ? c4.w : c4.y;
+    vid[2] = b1 ? c4.x : c4.z;
+    vid[3] = b1 ? c4.y : c4.w;
+    double4 g[4];
+    double s[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      g[j] = m.geo[vid[j]];
+      s[j] = m.sb[vid[j]].x;
+    }
+    // derivatives of the basis along xi and eta: (-my, my, eta, -eta), (-mx, -xi, xi, mx), the
+    // second pair's signs flipped where the corner order starts at the opposite corner
+    const double p = b1 ? eta : my, q = b1 ? my : eta, sg = b1 ? -1.0 : 1.0;
+    const double u = b1 ? xi : mx, w = b1 ? mx : xi;
+    const double dx[4] = {-sg * p, sg * p, sg * q, -sg * q}, dy[4] = {-sg * u, -sg * w, sg * w, sg * u};
+    double x_xi = 0, x_eta = 0, y_xi = 0, y_eta = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const double x = g[j].x - g[0].x, y = g[j].y - g[0].y;
+      x_xi = fma(x, dx[j], x_xi); x_eta = fma(x, dy[j], x_eta);
+      y_xi = fma(y, dx[j], y_xi); y_eta = fma(y, dy[j], y_eta);
+    }
+    const double det = x_xi * y_eta - x_eta * y_xi;
+    const double iG = rcp64(det);
+    const double i00 = y_eta * iG, i01 = -x_eta * iG, i10 = -y_xi * iG, i11 = x_xi * iG;
+    double Hq = 0.0;
+    sx = sy = Bx = By = Hx = Hy = 0.0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      lx[j] = dx[j] * i00 + dy[j] * i10;
+      ly[j] = dx[j] * i01 + dy[j] * i11;
+      sx = fma(s[j], lx[j], sx); sy = fma(s[j], ly[j], sy);
+      Bx = fma(g[j].z, lx[j], Bx); By = fma(g[j].z, ly[j], By);
+      Hx = fma(g[j].w, lx[j], Hx); Hy = fma(g[j].w, ly[j], Hy);
+      Hq = fma(g[j].w, lam[j], Hq);
+    }
+    wH = 0.125 * det * Hq;
+    iH = rcp64(Hq);
+    lam_a = sel4(al, lam[0], lam[1], lam[2], lam[3]);
+    lxa = sel4(al, lx[0], lx[1], lx[2], lx[3]);
+    lya = sel4(al, ly[0], ly[1], ly[2], ly[3]);
+    return make_double4(x_xi, x_eta, y_xi, y_eta);
+  };
+  auto gather = [&](int lev, double2 (&a)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      a[j] = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[j]) * (L + 1) + lev));
+  };
+  // slopes of u and v along x and y at the lane's point on one level
+  struct Slopes { double ux, uy, vx, vy; };
+  auto slopes = [&](const double2 (&a)[4]) {
+    Slopes f = {0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      f.ux = fma(lx[j], a[j].x, f.ux); f.uy = fma(ly[j], a[j].x, f.uy);
+      f.vx = fma(lx[j], a[j].y, f.vx); f.vy = fma(ly[j], a[j].y, f.vy);
+    }
+    return f;
+  };
+  auto sum4 = [](double v) {   // over the item's four lanes, the same in each
+    v += quad_xor<1>(v);
+    return v + quad_xor<2>(v);
+  };
+  wave_sync();
+
+  const int k0 = kb > 0 ? kb - 1 : 0;
+  const bool once = ie - ib <= HEX_ITEMS;   // more items only around a vertex with more than 16 cells
+  double2 lo[4], up[4];                     // u, v of the corners on levels k and k + 1
+  Slopes f0 = {0, 0, 0, 0};
+
+  // ---- bed friction on the lower face of the bottom layer: rows of the level-0 nodes -----------
+  if (kb == 0) {
+    for (int g = ib; g < ie; g += HEX_ITEMS) {
+      const double4 map = load_item(g);
+      gather(0, lo);
+      double br = 0.0, ur = 0.0, vr = 0.0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        br = fma(m.sb[vid[j]].y, lam[j], br);
+        ur = fma(lo[j].x, lam[j], ur);
+        vr = fma(lo[j].y, lam[j], vr);
+      }
+      // tangents of the face: z along x and y at fixed zeta, through the map
+      const double bx = fma(m.sigma[0], Hx, Bx), by = fma(m.sigma[0], Hy, By);
+      const double txx = map.x, tyx = map.y, txy = map.z, tyy = map.w;
+      const double txz = txx * bx + txy * by, tyz = tyx * bx + tyy * by;
+      const double nx_ = txy * tyz - txz * tyy, ny_ = txz * tyx - txx * tyz, nz_ = txx * tyy - txy * tyx;
+      const double wa = 0.25 * sqrt(nx_ * nx_ + ny_ * ny_ + nz_ * nz_) * br * lam_a;
+      const double Rf0 = sum4(wa * ur), Rf1 = sum4(wa * vr);
+      const double h0 = wa * lam[0] + quad_xor<2>(wa * lam[2]), h1 = wa * lam[1] + quad_xor<2>(wa * lam[3]);
+      const double own = (b0 ? h1 : h0) + quad_xor<1>(b0 ? h0 : h1);   // corner 2 b1 + b0
+      if (act) {
+        if (b1 == 0) lds_add(Rw + rloc + b0, b0 ? Rf1 : Rf0);
+        if constexpr (JAC) {
+          const int nl0 = nlev(0, L), r0 = int((rk >> (8 * b0)) & 255u);
+          lds_add(Jw + soff + r0 * 2 * nl0, double(AT(own)));
+          lds_add(Jw + soff + 2 * nl0 * Dv + r0 * 2 * nl0 + 1, double(AT(own)));
+        }
+      }
+    }
+  }
+  if (once) {
+    if (kb > 0) load_item(ib);
+    gather(k0, lo);
+    f0 = slopes(lo);
+    gather(k0 + 1, up);
+  }
+
+  // lane-constant weights of the kept and sent levels at the two zeta points, and signed basis
+  const AT lk[2] = {AT(b0 ? G1 : 1.0 - G1), AT(b0 ? G2 : 1.0 - G2)}, ls[2] = {AT(1) - lk[0], AT(1) - lk[1]};
+  for (int k = k0; k < ke; ++k) {
+    const int cur = k & 1, nxt = cur ^ 1;
+    const double s0 = m.sigma[k], ds = m.sigma[k + 1] - s0;
+    const double ids = rcp64(ds);
+    for (int g = ib; g < ie; g += HEX_ITEMS) {
+      if (!once) {
+        load_item(g);
+        gather(k, lo);
+        f0 = slopes(lo);
+        gather(k + 1, up);
+      }
+      const Slopes f1 = slopes(up);
+      double dum = 0.0, dvm = 0.0;          // differences first: exact where the levels are close
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        dum = fma(lam[j], up[j].x - lo[j].x, dum);
+        dvm = fma(lam[j], up[j].y - lo[j].y, dvm);
+        lo[j] = up[j];
+      }
+      if (once && k + 1 < ke) gather(k + 2, up);
+      const double iz = iH * ids, Wz = wH * ds;
+      const double exz = 0.5 * (iz * dum), eyz = 0.5 * (iz * dvm);
+      // the physics of the lane's two points
+      double s2[2], t2[2], E1x[2], Exy[2], E2y[2], px[2], py[2];
+#pragma unroll
+      for (int zi = 0; zi < 2; ++zi) {
+        const double zeta = zi ? G2 : G1, l0 = 1.0 - zeta, l1 = zeta;
+        const double sz = fma(zeta, ds, s0);
+        px[zi] = -fma(sz, Hx, Bx) * iz;         // d zeta / dx, d zeta / dy
+        py[zi] = -fma(sz, Hy, By) * iz;
+        const double ux = fma(l0, f0.ux, fma(l1, f1.ux, px[zi] * dum));
+        const double uy = fma(l0, f0.uy, fma(l1, f1.uy, py[zi] * dum));
+        const double vx = fma(l0, f0.vx, fma(l1, f1.vx, px[zi] * dvm));
+        const double vy = fma(l0, f0.vy, fma(l1, f1.vy, py[zi] * dvm));
+        const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx);
+        const double qq = exx * exx + eyy * eyy + exx * eyy + exy * exy + exz * exz + eyz * eyz;
+        const double qe = qq + m.eps0_sq;
+        double mu;
+        if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
+        else mu = m.visc_pref * powq(qe, m.visc_exp);
+        s2[zi] = 2.0 * mu * Wz;
+        t2[zi] = picard ? 0.0 : 2.0 * (m.visc_exp * mu * rcp64(qe)) * Wz;
+        E1x[zi] = 2.0 * exx + eyy;
+        Exy[zi] = exy;
+        E2y[zi] = exx + 2.0 * eyy;
+      }
+      f0 = f1;
+      const double gvx = Wz * m.rho_g * sx, gvy = Wz * m.rho_g * sy;
+      const AT iza = AT(iz), e1z = AT(exz), e2z = AT(eyz), half = AT(0.5);
+      const int r0 = int(rk & 255u), r1 = int((rk >> 8) & 255u);
+      double Rl[2][2] = {{0, 0}, {0, 0}};
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        // row node a: its gradient, residual, and 2 mu W grad N_a and 2 mu' W E_c . grad N_a
+        AT A[2][3], T[2][2];
+#pragma unroll
+        for (int zi = 0; zi < 2; ++zi) {
+          const double zeta = zi ? G2 : G1, l = a ? zeta : 1.0 - zeta, la = a ? lam_a : -lam_a;
+          const double ax = fma(l, lxa, la * px[zi]), ay = fma(l, lya, la * py[zi]), az = la * iz;
+          const double g0 = E1x[zi] * ax + Exy[zi] * ay + exz * az, g1 = Exy[zi] * ax + E2y[zi] * ay + eyz * az;
+          const double nb = lam_a * l;
+          Rl[a][0] = fma(s2[zi], g0, fma(gvx, nb, Rl[a][0]));
+          Rl[a][1] = fma(s2[zi], g1, fma(gvy, nb, Rl[a][1]));
+          if constexpr (JAC) {
+            A[zi][0] = AT(s2[zi] * ax); A[zi][1] = AT(s2[zi] * ay); A[zi][2] = AT(s2[zi] * az);
+            T[zi][0] = AT(t2[zi] * g0); T[zi][1] = AT(t2[zi] * g1);
+          }
+        }
+        if constexpr (JAC) {
+          // where the lane's two entries of a row go: level k sits at window position 1 unless k = 0
+          const int nl = a ? nlev(k + 1, L) : nlev(k, L);
+          double *w = Jw + (a ? nxt : cur) * max_slot + soff + 2 * (b0 + (!a && k > 0 ? 1 : 0));
+          double *w0 = w + r0 * 2 * nl, *w1 = w + r1 * 2 * nl;
+#pragma unroll
+          for (int cd = 0; cd < 4; ++cd) {
+            const int c = cd >> 1, d = cd & 1;
+            AT Kx = AT(0), Ky = AT(0), Sx = AT(0), Sy = AT(0), Bs = AT(0);
+#pragma unroll
+            for (int zi = 0; zi < 2; ++zi) {
+              const AT Ax = A[zi][0], Ay = A[zi][1], Az = A[zi][2], Tc = T[zi][c];
+              // coefficients of (bx, by, bz) in d R_(a,c) / d U_(b,d)
+              const AT ex = AT(d ? Exy[zi] : E1x[zi]), ey = AT(d ? E2y[zi] : Exy[zi]), ez = d ? e2z : e1z;
+              AT Lx, Ly, Lz;
+              if (cd == 0) { Lx = fma(Tc, ex, Ax + Ax); Ly = fma(Tc, ey, half * Ay); Lz = fma(Tc, ez, half * Az); }
+              else if (cd == 1) { Lx = fma(Tc, ex, half * Ay); Ly = fma(Tc, ey, Ax); Lz = Tc * ez; }
+              else if (cd == 2) { Lx = fma(Tc, ex, Ay); Ly = fma(Tc, ey, half * Ax); Lz = Tc * ez; }
+              else { Lx = fma(Tc, ex, half * Ax); Ly = fma(Tc, ey, Ay + Ay); Lz = fma(Tc, ez, half * Az); }
+              Kx = fma(lk[zi], Lx, Kx); Ky = fma(lk[zi], Ly, Ky);
+              Sx = fma(ls[zi], Lx, Sx); Sy = fma(ls[zi], Ly, Sy);
+              Bs = fma(Lx, AT(px[zi]), fma(Ly, AT(py[zi]), fma(Lz, iza, Bs)));
+            }
+            const AT Bk = b0 ? Bs : -Bs;      // the upper level's gradient carries +lam grad zeta
+            AT r[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const AT hx = AT(lx[j]), hy = AT(ly[j]), lb = AT(lam[j]) * Bk;
+              r[j] = fma(hx, Kx, fma(hy, Ky, lb)) + quad_xor<1>(fma(hx, Sx, fma(hy, Sy, -lb)));
+            }
+            const AT o0 = r[0] + quad_xor<2>(r[2]), o1 = r[1] + quad_xor<2>(r[3]);
+            if (act) {
+              lds_add(w0 + c * 2 * nl * Dv + d, double(o0));
+              lds_add(w1 + c * 2 * nl * Dv + d, double(o1));
+            }
+          }
+        }
+      }
+      // residual: the lane ends with row node b0, component b1
+      {
+        const double k0_ = b0 ? Rl[1][0] : Rl[0][0], k1_ = b0 ? Rl[1][1] : Rl[0][1];
+        const double s0_ = b0 ? Rl[0][0] : Rl[1][0], s1_ = b0 ? Rl[0][1] : Rl[1][1];
+        const double q0 = k0_ + quad_xor<1>(s0_), q1 = k1_ + quad_xor<1>(s1_);
+        const double own = (b1 ? q1 : q0) + quad_xor<2>(b1 ? q0 : q1);
+        if (act) lds_add(Rw + (b0 ? nxt : cur) * 2 * max_tv + rloc + b1, own);
+      }
+    }
+    wave_sync();
+    __builtin_amdgcn_s_setprio(2);
+    copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    wave_sync();
+    __builtin_amdgcn_s_setprio(0);
+  }
+}
+
+template <bool JAC, class JT, bool N3, bool TET>
+__global__ __launch_bounds__(WAVE, 2) void owner_kernel(MeshView m, const int4 *__restrict__ tasks,
+                                                        const double *__restrict__ U, double *__restrict__ R,
+                                                        JT *__restrict__ J, int picard, int max_slot, int max_tv) {
   extern __shared__ __align__(16) unsigned char smem[];
-  owner_task<NV, JAC, JT, N3, TET>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, smem);
+  owner_task<JAC, JT, N3, TET>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, smem);
+}
+
+// Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
+template <bool JAC, class JT, bool N3>
+__global__ __launch_bounds__(WAVE, 2) void hex_owner_kernel(MeshView m, const int4 *__restrict__ tasks, int lpc,
+                                                            const double *__restrict__ U, double *__restrict__ R,
+                                                            JT *__restrict__ J, int picard, int max_slot,
+                                                            int max_tv) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
+  hex_task<JAC, JT, N3>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
 }
 
 // Persistent ensemble launch: each workgroup repeatedly takes the next (member, task) pair
 // from a device counter until the combined task table is exhausted (every wave exits).
-template <int NV, bool JAC, class JT, bool N3, bool TET>
-__global__ __launch_bounds__(WAVE, NV == 3 ? 2 : 1) void ensemble_kernel(const EnsembleMember *__restrict__ mem,
-                                                        const int4 *__restrict__ tasks, int n_tasks,
-                                                        int *__restrict__ counter, int picard) {
-  extern __shared__ __align__(16) unsigned char smem[];
+template <class F>
+__device__ __forceinline__ void ensemble_loop(const EnsembleMember *__restrict__ mem, const int4 *__restrict__ tasks,
+                                              int n_tasks, int *__restrict__ counter, F run) {
   __shared__ int next;
   for (;;) {
     if (threadIdx.x == 0) next = atomicAdd(counter, 1);
@@ -935,10 +1087,29 @@ __global__ __launch_bounds__(WAVE, NV == 3 ? 2 : 1) void ensemble_kernel(const E
     __syncthreads();
     if (ti >= n_tasks) break;
     const int4 task = tasks[ti];
-    const EnsembleMember &e = mem[task.x];
-    owner_task<NV, JAC, JT, N3, TET>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot,
-                                     e.max_tv, smem);
+    run(mem[task.x], task);
   }
+}
+
+template <bool JAC, class JT, bool N3, bool TET>
+__global__ __launch_bounds__(WAVE, 2) void ensemble_kernel(const EnsembleMember *__restrict__ mem,
+                                                           const int4 *__restrict__ tasks, int n_tasks,
+                                                           int *__restrict__ counter, int picard) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
+    owner_task<JAC, JT, N3, TET>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, smem);
+  });
+}
+
+template <bool JAC, class JT, bool N3>
+__global__ __launch_bounds__(WAVE, 2) void hex_ensemble_kernel(const EnsembleMember *__restrict__ mem,
+                                                               const int4 *__restrict__ tasks, int n_tasks,
+                                                               int *__restrict__ counter, int picard) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
+    hex_task<JAC, JT, N3>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0, e.view.L,
+                          smem);
+  });
 }
 
 __global__ void fill_zero_kernel(uint4 *__restrict__ p, int64_t n16) {
@@ -967,43 +1138,72 @@ bool g_tables_ready[64] = {};
 
 fo_status ensure_tables(int device) {
   if (device >= 0 && device < 64 && g_tables_ready[device]) return FO_OK;
-  static constexpr QTable tabs[2] = {make_table(3), make_table(4)};
-  FO_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(kQ), tabs, sizeof(tabs)));
+  static constexpr QTable tab = make_table();
+  FO_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(kQ), &tab, sizeof(tab)));
   if (device >= 0 && device < 64) g_tables_ready[device] = true;
   return FO_OK;
 }
 
-// LDS of one task: two level windows (Jacobian) and two residual windows
-// Dynamic LDS of one task: the two Jacobian level windows, the two residual windows and,
-// with a Jacobian, the per-lane carry slots (WAVE x 4 FP64) that follow them.
+// Elements by kernel: prisms and their tetrahedra, one lane per item; hexahedra, four.
+enum Cell { PRISM, TETS, HEX };
+
+// Dynamic LDS of one task: the two Jacobian level windows, the two residual windows and, with a
+// Jacobian, the per-lane carry slots (WAVE x 4 FP64) that follow them on prisms.
+template <Cell C>
 size_t window_bytes(bool jac, int max_slot, int max_tv) {
-  return (jac ? 2 * size_t(max_slot) * sizeof(double) + size_t(WAVE) * 4 * sizeof(double) : 0) +
+  return (jac ? 2 * size_t(max_slot) * sizeof(double) + (C == HEX ? 0 : size_t(WAVE) * 4 * sizeof(double)) : 0) +
          2 * 2 * size_t(max_tv) * sizeof(double);
 }
 
-template <int NV, bool JAC, class JT, bool N3, bool TET>
+// Layers per block of a launch with n_tasks tasks of L layers.  A small mesh leaves the chip
+// idle while each wave walks its columns layer by layer, so the levels are split over blocks; a
+// block that does not start at the bed repeats the layer below its first level.  The cost taken
+// here is the layers of a block (the repeated one included) times the rounds of `resident`
+// waves; results do not depend on the split (every level's sums keep their order).
+int layers_per_block(int64_t n_tasks, int L, int64_t resident) {
+  int best = L;
+  double best_cost = 0.0;
+  for (int lpc = L; lpc >= 1; --lpc) {
+    const int chunks = (L + lpc - 1) / lpc;
+    const double rounds = double(n_tasks) * chunks / double(resident);
+    const double cost = (rounds > 1.0 ? rounds : 1.0) * (lpc + (chunks > 1 ? 1 : 0));
+    if (lpc == L || cost < best_cost) {
+      best = lpc;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+constexpr int64_t HEX_RESIDENT = 2048;
+
+template <Cell C, bool JAC, class JT, bool N3>
 fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int kind, hipStream_t s) {
   const MeshView &m = mesh->view;
-  const size_t lds = window_bytes(JAC, mesh->max_slot, mesh->max_task_verts);
+  const size_t lds = window_bytes<C>(JAC, mesh->max_slot, mesh->max_task_verts);
+  const int picard = kind == FO_JAC_PICARD ? 1 : 0;
   fo_status st = profile_begin(mesh, s);
   if (st != FO_OK) return st;
-  hipLaunchKernelGGL((owner_kernel<NV, JAC, JT, N3, TET>), dim3(unsigned(mesh->n_tasks)), dim3(WAVE), lds, s, m,
-                     mesh->tasks, U, R, J, kind == FO_JAC_PICARD ? 1 : 0, mesh->max_slot,
-                     mesh->max_task_verts);
+  if constexpr (C == HEX) {
+    const int lpc = layers_per_block(mesh->n_tasks, m.L, HEX_RESIDENT);
+    hipLaunchKernelGGL((hex_owner_kernel<JAC, JT, N3>), dim3(unsigned(mesh->n_tasks), unsigned((m.L + lpc - 1) / lpc)),
+                       dim3(WAVE), lds, s, m, mesh->tasks, lpc, U, R, J, picard, mesh->max_slot,
+                       mesh->max_task_verts);
+  } else {
+    hipLaunchKernelGGL((owner_kernel<JAC, JT, N3, C == TETS>), dim3(unsigned(mesh->n_tasks)), dim3(WAVE), lds, s, m,
+                       mesh->tasks, U, R, J, picard, mesh->max_slot, mesh->max_task_verts);
+  }
   FO_LAUNCH_CHECK("owner_kernel");
   return profile_end(mesh, s);
 }
 
-template <int NV, bool JAC, class JT, bool TET = false>
-fo_status launch_n(const fo_mesh *mesh, const double *U, double *R, JT *J, int kind, hipStream_t s) {
-  if (mesh->view.n_glen == 3.0) return launch_t<NV, JAC, JT, true, TET>(mesh, U, R, J, kind, s);
-  return launch_t<NV, JAC, JT, false, TET>(mesh, U, R, J, kind, s);
-}
-
-template <int NV, bool JAC, class JT, bool N3, bool TET>
+template <Cell C, bool JAC, class JT, bool N3>
 fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
-  const size_t lds = window_bytes(JAC, E.max_slot, E.max_tv);
-  auto kern = ensemble_kernel<NV, JAC, JT, N3, TET>;
+  const size_t lds = window_bytes<C>(JAC, E.max_slot, E.max_tv);
+  auto kern = [] {
+    if constexpr (C == HEX) return hex_ensemble_kernel<JAC, JT, N3>;
+    else return ensemble_kernel<JAC, JT, N3, C == TETS>;
+  }();
   int per_cu = 0;
   FO_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WAVE, lds));
   if (per_cu < 1) per_cu = 1;
@@ -1018,10 +1218,20 @@ fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
   return FO_OK;
 }
 
-template <int NV, bool JAC, class JT, bool TET = false>
-fo_status launch_ens_n(const EnsembleLaunch &E, int kind, hipStream_t s) {
-  if (E.all_n3) return launch_ens_t<NV, JAC, JT, true, TET>(E, kind, s);
-  return launch_ens_t<NV, JAC, JT, false, TET>(E, kind, s);
+// Calls f<cell, jac, value type, n = 3> for the run-time choices
+template <class F>
+fo_status by_kernel(int nv, bool tet, bool want_jac, int dtype, bool n3, F f) {
+  auto by_n = [&](auto c, auto jac, auto val) {
+    return n3 ? f(c, jac, val, std::true_type{}) : f(c, jac, val, std::false_type{});
+  };
+  auto by_type = [&](auto c) {
+    if (!want_jac) return by_n(c, std::false_type{}, double{});
+    if (dtype == FO_F32) return by_n(c, std::true_type{}, float{});
+    return by_n(c, std::true_type{}, double{});
+  };
+  if (tet) return by_type(std::integral_constant<Cell, TETS>{});
+  if (nv == 4) return by_type(std::integral_constant<Cell, HEX>{});
+  return by_type(std::integral_constant<Cell, PRISM>{});
 }
 
 }  // namespace
@@ -1039,21 +1249,9 @@ fo_status launch_front_add(const MeshView &m, int32_t n_front, const int32_t *vt
 fo_status launch_ensemble(const EnsembleLaunch &E, int dtype, int kind, bool want_jac, hipStream_t s) {
   fo_status st = ensure_tables(E.device);
   if (st != FO_OK) return st;
-  if (E.tet) {
-    if (!want_jac) return launch_ens_n<3, false, double, true>(E, kind, s);
-    if (dtype == FO_F32) return launch_ens_n<3, true, float, true>(E, kind, s);
-    return launch_ens_n<3, true, double, true>(E, kind, s);
-  }
-  if (!want_jac) {
-    if (E.nv == 3) return launch_ens_n<3, false, double>(E, kind, s);
-    return launch_ens_n<4, false, double>(E, kind, s);
-  }
-  if (dtype == FO_F32) {
-    if (E.nv == 3) return launch_ens_n<3, true, float>(E, kind, s);
-    return launch_ens_n<4, true, float>(E, kind, s);
-  }
-  if (E.nv == 3) return launch_ens_n<3, true, double>(E, kind, s);
-  return launch_ens_n<4, true, double>(E, kind, s);
+  return by_kernel(E.nv, E.tet, want_jac, dtype, E.all_n3, [&](auto c, auto jac, auto val, auto n3) {
+    return launch_ens_t<c.value, jac.value, decltype(val), n3.value>(E, kind, s);
+  });
 }
 
 fo_status launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
@@ -1087,22 +1285,11 @@ fo_status launch_assemble_cells(const fo_mesh *mesh, const double *U, double *R,
                                 int kind, bool want_jac, hipStream_t s) {
   fo_status st = ensure_tables(mesh->device);
   if (st != FO_OK) return st;
-  const int nv = mesh->view.nv;
-  if (mesh->view.tet) {
-    if (!want_jac) return launch_n<3, false, double, true>(mesh, U, R, nullptr, kind, s);
-    if (dtype == FO_F32) return launch_n<3, true, float, true>(mesh, U, R, static_cast<float *>(J), kind, s);
-    return launch_n<3, true, double, true>(mesh, U, R, static_cast<double *>(J), kind, s);
-  }
-  if (!want_jac) {
-    if (nv == 3) return launch_n<3, false, double>(mesh, U, R, nullptr, kind, s);
-    return launch_n<4, false, double>(mesh, U, R, nullptr, kind, s);
-  }
-  if (dtype == FO_F32) {
-    if (nv == 3) return launch_n<3, true, float>(mesh, U, R, static_cast<float *>(J), kind, s);
-    return launch_n<4, true, float>(mesh, U, R, static_cast<float *>(J), kind, s);
-  }
-  if (nv == 3) return launch_n<3, true, double>(mesh, U, R, static_cast<double *>(J), kind, s);
-  return launch_n<4, true, double>(mesh, U, R, static_cast<double *>(J), kind, s);
+  const MeshView &m = mesh->view;
+  return by_kernel(m.nv, m.tet != 0, want_jac, dtype, m.n_glen == 3.0, [&](auto c, auto jac, auto val, auto n3) {
+    using JT = decltype(val);
+    return launch_t<c.value, jac.value, JT, n3.value>(mesh, U, R, jac.value ? static_cast<JT *>(J) : nullptr, kind, s);
+  });
 }
 
 }  // namespace fo

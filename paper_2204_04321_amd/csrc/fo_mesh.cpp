@@ -228,8 +228,10 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
   // whose level windows (12 D entries per vertex) fit the per-wave LDS budget
   // kMaxSlot: two level windows of at most 1080 FP64 entries, the residual windows and the
   // per-lane carry slots (2 KB) keep a wave's LDS under 20 KB, so that eight waves share a
-  // compute unit
+  // compute unit.  Hexahedra take four lanes per item: 16 items a wave (a vertex with more is a
+  // task of its own and takes several passes).
   constexpr int kMaxItems = 64, kMaxSlot = 1080;
+  const int task_items = nv == 4 ? kMaxItems / 4 : kMaxItems;
   std::vector<int4> tasks;
   std::vector<int32_t> slot_off(V);
   int32_t max_slot = 0, max_tv = 0;
@@ -244,7 +246,7 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
         return fail(FO_EINVAL, "fo_mesh_create: vertex " + std::to_string(v) + " lies in more than 64 base cells");
       if (sz > kMaxSlot)
         return fail(FO_EINVAL, "fo_mesh_create: vertex " + std::to_string(v) + " has more than 90 neighbouring vertices");
-      if (v > vb && (items + ni > kMaxItems || slot + sz > kMaxSlot)) {
+      if (v > vb && (items + ni > task_items || slot + sz > kMaxSlot)) {
         tasks.push_back(make_int4(0, vb, v, vc_ptr[vb]));
         max_slot = std::max(max_slot, slot);
         max_tv = std::max(max_tv, v - vb);

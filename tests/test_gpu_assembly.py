@@ -147,6 +147,57 @@ def case(request):
     return request.param, m, U, M
 
 
+def _quad_fan(n_quads, L, seed):
+    """One vertex in n_quads quadrilaterals (more than 16 take several passes of a wave)."""
+    rng = np.random.default_rng(seed)
+    ang = np.arange(2 * n_quads) * np.pi / n_quads
+    r = np.where(np.arange(2 * n_quads) % 2 == 0, 3e3, 3.2e3 / np.cos(np.pi / n_quads))
+    xy = np.vstack([[0.0, 0.0], np.stack([r * np.cos(ang), r * np.sin(ang)], 1)])
+    cells = np.array([[0, 1 + 2 * i, 2 + 2 * i, 1 + (2 * i + 2) % (2 * n_quads)] for i in range(n_quads)],
+                     dtype=np.int32)
+    V = xy.shape[0]
+    H = 600 + 100 * rng.uniform(size=V)
+    m = ExtrudedMesh("hex", xy, cells, 200 - 0.01 * xy[:, 0] + H, H, 400 + 300 * rng.uniform(size=V),
+                     np.linspace(0, 1, L + 1) ** 1.3)
+    return m, smooth_velocity(m, rng, 60.0, 0.05)
+
+
+SPLIT_CASES = {
+    "hex_17_quads": lambda: _quad_fan(17, 4, 31), "hex_44_quads": lambda: _quad_fan(44, 2, 32),
+    "hex_16_quads": lambda: _quad_fan(16, 5, 33), "hex_2_layers": lambda: _box(7, 5, 2, "hex", 34),
+    "hex_13_layers": lambda: _box(9, 7, 13, "hex", 35), "hex_n4": lambda: (
+        lambda mu: (mu[0].with_fields(n=4.0, A=1e-20), mu[1]))(_box(5, 4, 6, "hex", 36)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SPLIT_CASES))
+def test_levels_split_over_blocks(name):
+    """Small meshes spread a column's levels over several blocks (and hexahedra an item's points
+    over four lanes): parity with the oracle as above, and every bit as from the ensemble
+    launch, which walks whole columns, in both value types and for the residual alone."""
+    from paper_2204_04321_amd.api import Ensemble
+    m, U = SPLIT_CASES[name]()
+    M = gpu_mesh(m)
+    E = Ensemble([M])
+    Ud = to_dev(U)
+    for kind in ("newton", "picard"):
+        R, J = gpu_jacobian(M, U, "f64", kind)
+        pic = kind == "picard"
+        Ro, Jo = fo.assemble(m, U, picard=pic)
+        e = parity_errors(R, J, Ro, Jo, fo.abs_scales(m, U, picard=pic), fo.element_scales(m, U, picard=pic))
+        _report(f"{name}/{kind}", e)
+        assert max(e["term"]) <= TOL64 and max(e["elem"]) <= TOL64_ELEM and max(e["plain"]) <= TOL64
+    for dtype, tdt in (("f64", torch.float64), ("f32", torch.float32)):
+        R1, J1 = M.jacobian(Ud, dtype=dtype)
+        Re, Je = torch.full_like(R1, float("nan")), torch.full((M.nnz,), float("nan"), dtype=tdt, device="cuda")
+        E.assemble([Ud], [Re], [Je], dtype=dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(R1, Re) and torch.equal(J1, Je)
+    E.assemble([Ud], [Re], None)
+    torch.cuda.synchronize()
+    assert torch.equal(M.residual(Ud), Re)
+
+
 def test_pattern_matches_oracle(case):
     name, m, U, M = case
     rowptr, colidx = M.pattern()
