@@ -20,7 +20,7 @@
 // the wave copies it into its contiguous CSR range.  No global atomics, no
 // zero fill of J or R, every value written once; results do not depend on
 // scheduling.  Each cell is evaluated by each of its vertex columns (3 or 4
-// times) in exchange.
+// times) in exchange.  Hexahedra spread an item over four lanes (hex_task below).
 //
 // Wedge kernels run two waves per SIMD (256 registers per lane, a few per-layer spills).
 // Their tangents are accumulated in factorised form (per row node and component pair:
@@ -754,10 +754,14 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
 // Four lanes per item, one per Gauss point of the base quadrilateral (two zeta points each): a
 // lane evaluates the physics of its two points once, and the entries of the item's rows are
 // formed from its own point and summed over the four lanes by two exchanges, after which every
-// lane holds a quarter of them.  Nothing of the Jacobian stays in registers across points
-// (one lane per item needed 64 accumulators and ran one wave per SIMD), so four waves share
-// a SIMD, and the horizontal map, gradients and the slopes of bed and thickness at
-// a lane's point are constants of the whole column.
+// lane holds a quarter of them.
+// Nothing of the Jacobian stays in registers across points (one lane per item needed 64
+// accumulators and ran one wave per SIMD with 40 of its 64 lanes busy, the window budget being
+// ten columns), and the horizontal map, gradients and the slopes of bed and thickness at a lane's
+// point are constants of the whole column.  Bound by FP64 issue: about 1000 vector instructions
+// a layer.  30,000 columns of 7 layers (210,000 hexahedra), FP64 R+J: 293 -> 132 us; 2000
+// hexahedra (with the levels split over blocks): 68 -> 12 us.  Compiled for three or four waves
+// per SIMD the column constants spill: 333 and 572 us.
 //
 // Exchanges without selections: lane bits b0 = lane & 1, b1 = lane >> 1 & 1.  A lane forms the
 // entries at level b0 as "kept" and at the other level as "sent" (lane-constant weights l_b0 and
@@ -1175,7 +1179,7 @@ int layers_per_block(int64_t n_tasks, int L, int64_t resident) {
   return best;
 }
 
-constexpr int64_t HEX_RESIDENT = 2048;
+constexpr int64_t HEX_RESIDENT = 2048;   // two waves on each of 1024 SIMDs
 
 template <Cell C, bool JAC, class JT, bool N3>
 fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int kind, hipStream_t s) {
