@@ -20,13 +20,9 @@
 // the wave copies it into its contiguous CSR range.  No global atomics, no
 // zero fill of J or R, every value written once; results do not depend on
 // scheduling.  Each cell is evaluated by each of its vertex columns (3 or 4
-// times) in exchange.  Hexahedra spread an item over four lanes (hex_task below).
-//
-// Wedge kernels run two waves per SIMD (256 registers per lane, a few per-layer spills).
-// Their tangents are accumulated in factorised form (per row node and component pair:
-// two weighted sums of the row coefficients and one projection per triangle point), and
-// the twelve column blocks are formed once per layer; the level windows are FP64 for
-// either Jacobian value type.
+// times) in exchange.  Prisms spread an item over two lanes (prism_task below), hexahedra over
+// four (hex_task).  The level windows are FP64 for either
+// Jacobian value type.
 //
 // CSR slot of row (v, level kr, comp c) and column (vertex of rank r in v's sorted
 // neighbour list, level kc, comp d): colptr[v] + 4 D_v cumlev(kr) + c 2 nlev(kr) D_v
@@ -111,6 +107,16 @@ __device__ __forceinline__ void lds_add(T *p, T v) {
   atomicAdd(p, v);   // LDS atomics: lanes of one wave may hit the same entry
 }
 
+// A table that no kernel writes, in scalar registers: read with scalar loads, which do not wait for
+// the vector loads in flight (sigma read through a generic pointer made every layer wait for the
+// next layer's velocities).
+typedef const double __attribute__((address_space(4))) *ScalarTable;
+__device__ __forceinline__ ScalarTable scalar_table(const double *p) {
+  uint64_t v = reinterpret_cast<uint64_t>(p);
+  asm volatile("" : "+s"(v));     // a register pair of its own, apart from the kernel arguments' block
+  return reinterpret_cast<ScalarTable>(v);
+}
+
 // The block is one wave: a workgroup barrier orders its LDS traffic.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -131,6 +137,14 @@ __device__ __forceinline__ double sel4(int i, double a, double b, double c, doub
                 (__builtin_bit_cast(u64, c) & m2) | (__builtin_bit_cast(u64, d) & m3);
   return __builtin_bit_cast(double, r);
 }
+
+// v with its sign flipped where sign = 0x80000000 (0: as it is)
+__device__ __forceinline__ double flip(double v, uint32_t sign) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ (uint64_t(sign) << 32));
+}
+
+// i ? b : a without a branch (both operands in registers)
+__device__ __forceinline__ double sel2(int i, double a, double b) { return sel4(i, a, b, b, b); }
 
 // Two consecutive Jacobian entries as one streaming (nontemporal) store; p is 8-entry aligned.
 template <class JT>
@@ -286,6 +300,70 @@ __device__ __forceinline__ void clear_windows(const MeshView &m, double *Jw, dou
     for (int e = lane; e < slot_size; e += WAVE) { Jw[e] = 0.0; Jw[max_slot + e] = 0.0; }
   }
   for (int e = lane; e < 2 * (ve - vb); e += WAVE) { Rw[e] = 0.0; Rw[2 * max_tv + e] = 0.0; }
+}
+
+// Where a lane's share of an interior level goes.  On three levels a column's rows fill its whole
+// slot (12 D entries), so a task's window is one contiguous run; lane l moves the entry pairs
+// 2 l + 128 i.  off[i]: the pair's place on level 1, in entries from the task's first; deg: its
+// column's degree, 8 bits per i.  Each further level lies 12 D entries on.
+constexpr int FLAT_PARTS = 4;
+struct FlatCopy {
+  uint32_t off[FLAT_PARTS], deg;
+  int slot_size;      // 0: the window or the offsets are too large, columns are copied one by one
+  int64_t base;       // colptr of the task's first column
+};
+
+template <bool JAC>
+__device__ __forceinline__ FlatCopy flat_copy(const MeshView &m, const TaskColumns &cols, int vb, int nvt, int lane) {
+  FlatCopy f = {{0u, 0u, 0u, 0u}, 0u, 0, 0};
+  if constexpr (!JAC) return f;
+  const int n = __builtin_amdgcn_readlane(cols.soff, nvt - 1) + 12 * __builtin_amdgcn_readlane(cols.deg, nvt - 1);
+  f.base = int64_t(unsigned(__builtin_amdgcn_readlane(cols.col_lo, 0))) |
+           (int64_t(__builtin_amdgcn_readlane(cols.col_hi, 0)) << 32);
+  if (n > 128 * FLAT_PARTS || m.L > 4096) return f;
+  f.slot_size = n;
+  for (int c = 0; c < nvt; ++c) {
+    const int so = __builtin_amdgcn_readlane(cols.soff, c), D = __builtin_amdgcn_readlane(cols.deg, c);
+    const uint32_t start = uint32_t(__builtin_amdgcn_readlane(cols.col_lo, c)) - uint32_t(f.base) + 8u * uint32_t(D);
+#pragma unroll
+    for (int i = 0; i < FLAT_PARTS; ++i) {
+      const int e = 2 * lane + 128 * i;
+      if (e >= so) {
+        f.off[i] = start + uint32_t(e - so);
+        f.deg = (f.deg & ~(255u << (8 * i))) | (uint32_t(D) << (8 * i));
+      }
+    }
+  }
+  return f;
+}
+
+// Copies a finished interior level's window to its CSR rows and clears it for level + 2
+// (store = false: clears it only); all LDS reads are issued before the first store.
+template <bool JAC, class JT>
+__device__ __forceinline__ void copy_out_flat(const FlatCopy &f, int lev, int slot, bool store, int vb, int nvt, int L,
+                                              double *Jw, double *Rw, int max_slot, int max_tv, int lane,
+                                              double *__restrict__ R, JT *__restrict__ J) {
+  if constexpr (JAC) {
+    double *wb = Jw + slot * max_slot + 2 * lane;
+    JT *dst = J + f.base;
+    const uint32_t up = 12u * uint32_t(lev - 1);
+    double2 val[FLAT_PARTS];
+#pragma unroll
+    for (int i = 0; i < FLAT_PARTS; ++i)
+      if (128 * i < f.slot_size)     // past the window's end: other LDS of the task, not stored
+        val[i] = *reinterpret_cast<const double2 *>(wb + (2 * lane + 128 * i < f.slot_size ? 128 * i : 0));
+#pragma unroll
+    for (int i = 0; i < FLAT_PARTS; ++i)
+      if (128 * i < f.slot_size && 2 * lane + 128 * i < f.slot_size) {
+        if (store) store2_nt(dst + (f.off[i] + up * ((f.deg >> (8 * i)) & 255u)), val[i].x, val[i].y);
+        *reinterpret_cast<double2 *>(wb + 128 * i) = make_double2(0.0, 0.0);
+      }
+  }
+  for (int e = lane; e < 2 * nvt; e += WAVE) {
+    double *rs = Rw + slot * 2 * max_tv + e;
+    if (R && store) R[2 * (int64_t(vb + (e >> 1)) * (L + 1) + lev) + (e & 1)] = *rs;
+    *rs = 0.0;
+  }
 }
 
 // Copies a finished level's window to its CSR rows and clears it for level + 2 (store = false:
@@ -750,6 +828,362 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
   }
 }
 
+// Value of lane (lane ^ X), X = 1 or 2
+__device__ __forceinline__ int quad_xor_i(int v, bool two) {
+  return two ? __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+}
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = uint32_t(quad_xor_i(int(uint32_t(u)), X == 2));
+  const uint32_t hi = uint32_t(quad_xor_i(int(uint32_t(u >> 32)), X == 2));
+  return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
+}
+template <int X>
+__device__ __forceinline__ float quad_xor(float v) {
+  return __builtin_bit_cast(float, quad_xor_i(__builtin_bit_cast(int, v), X == 2));
+}
+
+// ---- prisms ----------------------------------------------------------------------------------
+// Two lanes per item, one per zeta Gauss point (three triangle points each): a lane evaluates the
+// physics of its three points, accumulates its share of the item's tangents, and one exchange
+// leaves each lane half of the entries.  One lane per item needs 56 accumulators for its six
+// points and loops over zeta; here zeta is fixed, so 40 do: with b the gradient of a column node,
+// every entry is sum_q L_q . b_q, where L_q (three numbers per row node a and component pair
+// cd) depends on the row only.  For a prism, b = l h_j -+ lam_j p with h_j = (dN_j/dx, dN_j/dy, 0)
+// constant over the cell, l = 1 - zeta, zeta the level's weight and p = grad zeta the same for
+// all corners: so the lane sums L (x, y parts) over its points, and L . p per triangle point.
+// The slopes of bed and thickness, 1/H at the points and the horizontal gradients are constants
+// of the whole column.
+//
+// z = lane & 1.  Of row node a (0 lower, 1 upper) a lane ends with the entries at level a ^ z: the
+// weight of the kept level is then G2 (a = 0) or G1 (a = 1) in either lane, and only the sign of
+// p differs.  Lane z = 0 holds the upper row's entries at the upper level, which the next layer's
+// lower row adds to the same places: they are carried in registers (a quarter fewer LDS adds).
+// The cell's corners are taken in cyclic order from the item's own vertex, which is thus always
+// corner 0.
+//
+// With a Jacobian it is bound by FP64 issue and the LDS adds alike (ice sheet of 125,000 columns of
+// 10 layers: vector units 76% busy while two waves share a SIMD, the LDS 66% of the kernel's
+// time); the residual alone, four waves per SIMD, by vector issue.  R+J 705 -> 574 us in FP64 and
+// 670 -> 528 us with FP32 values, residual 180 -> 173 us, against one lane per item.  The parts:
+// the split itself, with the constants in LDS, -7%; items of one vertex spread over the wave
+// (below) -5%; sigma through scalar loads and the wait before the copy-out -2%; the copy-out of a
+// level in one piece -6%.
+constexpr int PRISM_WAVES = 2;
+constexpr int PRISM_CONST = 18;         // FP64 constants of an item (144 bytes: its 16-byte reads spread over all banks)
+constexpr int PRISM_ITEMS = WAVE / 2;   // items per pass of a wave
+
+// The levels kb <= k < ke of a task's columns (and level L if ke = L).  kb > 0 starts with layer
+// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: a task may hold
+// more items than one pass of a wave takes (a vertex in more cells than that is a task of its
+// own), so the item constants are reloaded for every layer and pass.
+template <bool JAC, class JT, bool N3, bool PASSES>
+__device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, const double *__restrict__ U,
+                                           double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
+                                           int max_tv, int kb, int ke, unsigned char *smem) {
+  using AT = JT;   // derivative arithmetic type
+  // The level windows accumulate in FP64 for either value type: FP32 LDS atomics on this
+  // scatter pattern saturate the LDS data path (measured), FP64 ones do not.
+  double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
+  double *Rw = reinterpret_cast<double *>(smem + (JAC ? 2 * size_t(max_slot) * sizeof(double) : 0));  // [2][2 max_tv]
+  const double tfac = picard ? 0.0 : m.visc_exp;
+  double *const item_c = Rw + 4 * size_t(max_tv);   // [PRISM_ITEMS][PRISM_CONST]
+  const ScalarTable sigma = scalar_table(m.sigma);
+  const int lane = threadIdx.x, z = lane & 1;
+  // items of one vertex add to the same places: neighbours in the list go to different quarters of
+  // the wave, which the LDS takes one after another
+  const int slot = 4 * ((lane >> 1) & 7) + (lane >> 4);
+  const uint32_t minus = z ? 0u : 0x80000000u;
+  const int vb = task.y, ve = task.z, ib = task.w, ie = m.vc_ptr[ve];
+  const int L = m.L, nvt = ve - vb;
+  const TaskColumns cols = load_columns(m, vb, nvt, lane);
+  const FlatCopy flat = flat_copy<JAC>(m, cols, vb, nvt, lane);
+  clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
+  const double zeta = z ? G2 : G1;
+
+  // item constants in LDS (in registers they spill): horizontal gradients, slopes of bed and H,
+  // gravity's row sums, 2 visc_pref x weight x determinant x thickness and 1/H at the triangle points
+  enum { LX = 0, LY = 3, BED = 6, THK = 8, GRAV = 10, WH = 12, INVH = 15 };
+  double *const c_ = item_c + PRISM_CONST * slot;
+  int vid[3] = {0, 0, 0}, Dv = 0, soff = 0, rloc = 0;
+  uint32_t rk = 0u;
+  bool act = false;
+  auto load_item = [&](int first) {
+    act = first + slot < ie;
+    const int item = act ? first + slot : ib;
+    const int v = m.item_vtx[item], t = m.vc_idx[item], rot = m.vc_pos[item];
+    Dv = m.deg[v];
+    soff = m.slot_off[v];
+    rloc = 2 * (v - vb);
+    rk = m.item_rank[item];
+    rk = (rk >> (8 * rot)) | (rk << (8 * (3 - rot)));   // the low three bytes
+#pragma unroll
+    for (int i = 0; i < 3; ++i) vid[i] = m.cells[3 * int64_t(t) + (i + rot >= 3 ? i + rot - 3 : i + rot)];
+    double4 g[3];
+    double s[3], lx[3], ly[3], c[PRISM_CONST];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      g[i] = m.geo[vid[i]];
+      s[i] = m.sb[vid[i]].x;
+    }
+    const double x_xi = g[1].x - g[0].x, x_eta = g[2].x - g[0].x;
+    const double y_xi = g[1].y - g[0].y, y_eta = g[2].y - g[0].y;
+    const double det = x_xi * y_eta - x_eta * y_xi;
+    const double iG = rcp64(det);
+    lx[1] = y_eta * iG; lx[2] = -y_xi * iG; lx[0] = -(lx[1] + lx[2]);
+    ly[1] = -x_eta * iG; ly[2] = x_xi * iG; ly[0] = -(ly[1] + ly[2]);
+    const double wd = det * (1.0 / 12.0), Hm = (g[0].w + g[1].w + g[2].w) * (1.0 / 6.0);
+    double sx = 0.0, sy = 0.0, Hl = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[BED + i] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      c[LX + i] = lx[i];
+      c[LY + i] = ly[i];
+      sx = fma(s[i], lx[i], sx); sy = fma(s[i], ly[i], sy);
+      c[BED] = fma(g[i].z, lx[i], c[BED]); c[BED + 1] = fma(g[i].z, ly[i], c[BED + 1]);
+      c[THK] = fma(g[i].w, lx[i], c[THK]); c[THK + 1] = fma(g[i].w, ly[i], c[THK + 1]);
+      const double Hp = fma(0.5, g[i].w, Hm);     // point i: 2/3 of corner i and 1/6 of the others
+      Hl = fma(i == 0 ? 2.0 / 3.0 : 1.0 / 6.0, Hp, Hl);
+      c[WH + i] = 2.0 * m.visc_pref * wd * Hp;
+      c[INVH + i] = rcp64(Hp);
+    }
+    c[GRAV] = m.rho_g * sx * (wd * Hl);
+    c[GRAV + 1] = m.rho_g * sy * (wd * Hl);
+    if (z == 0) {
+#pragma unroll
+      for (int i = 0; i < PRISM_CONST; i += 2)
+        *reinterpret_cast<double2 *>(c_ + i) = make_double2(c[i], c[i + 1]);
+    }
+    wave_sync();
+  };
+  auto gather = [&](int lev, double2 (&a)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      a[i] = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[i]) * (L + 1) + lev));
+  };
+  // slopes of u and v along x and y on one level
+  struct Slopes { double ux, uy, vx, vy; };
+  auto slopes = [&](const double2 (&a)[3]) {
+    Slopes f = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const double lx = c_[LX + i], ly = c_[LY + i];
+      f.ux = fma(lx, a[i].x, f.ux); f.uy = fma(ly, a[i].x, f.uy);
+      f.vx = fma(lx, a[i].y, f.vx); f.vy = fma(ly, a[i].y, f.vy);
+    }
+    return f;
+  };
+  wave_sync();
+
+  const int k0 = kb > 0 ? kb - 1 : 0;
+  double2 lo[3], up[3];                       // u, v of the corners on levels k and k + 1
+  Slopes f0 = {0, 0, 0, 0};
+  // a layer's upper velocities are kept for the next one's lower level, and those above loaded a
+  // layer ahead; the general power's constants leave no registers for either
+  constexpr bool AHEAD = N3 && !PASSES;
+  constexpr bool CARRY = sizeof(JT) == 4;
+  AT carry[4][3];                             // lane z = 0: the upper row at the upper level of the layer below
+#pragma unroll
+  for (int cd = 0; cd < 4; ++cd)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) carry[cd][j] = AT(0);
+
+  // ---- bed friction on the lower face of the bottom layer: rows of the level-0 nodes, lane z
+  // component z -------------------------------------------------------------------------------
+  if (kb == 0) {
+    for (int g = ib; PASSES ? g < ie : g == ib; g += PRISM_ITEMS) {
+      load_item(g);
+      gather(0, lo);
+      // face normal from the slopes of its z; basis products at the three points (2/3, 1/6, 1/6)
+      const double bx = fma(m.sigma[0], c_[THK], c_[BED]), by = fma(m.sigma[0], c_[THK + 1], c_[BED + 1]);
+      // the cell's doubled base area from its gradients: 1 / (lx_1 ly_2 - lx_2 ly_1)
+      const double det = rcp64(c_[LX + 1] * c_[LY + 2] - c_[LX + 2] * c_[LY + 1]);
+      const double area = det * sqrt(fma(bx, bx, fma(by, by, 1.0)));
+      double be[3], q[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        be[i] = m.sb[vid[i]].y;
+        q[i] = sel2(z, lo[i].x, lo[i].y);
+      }
+      const double bm = (be[0] + be[1] + be[2]) * (1.0 / 6.0), qm = (q[0] + q[1] + q[2]) * (1.0 / 6.0);
+      double Rf = 0.0, Jf[3] = {0, 0, 0};
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const double w = area * (1.0 / 6.0) * fma(0.5, be[r], bm) * (r == 0 ? 2.0 / 3.0 : 1.0 / 6.0);
+        Rf = fma(w, fma(0.5, q[r], qm), Rf);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) Jf[j] = fma(w, r == j ? 2.0 / 3.0 : 1.0 / 6.0, Jf[j]);
+      }
+      if (act) {
+        lds_add(Rw + rloc + z, Rf);
+        if constexpr (JAC) {
+          const int nl0 = nlev(0, L);
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            lds_add(Jw + soff + z * 2 * nl0 * Dv + int((rk >> (8 * j)) & 255u) * 2 * nl0 + z, double(AT(Jf[j])));
+        }
+      }
+    }
+  }
+  if constexpr (!PASSES) {
+    if (kb > 0) load_item(ib);
+    if constexpr (AHEAD) {
+      gather(k0, lo);
+      f0 = slopes(lo);
+      gather(k0 + 1, up);
+      asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));   // waited for here, as below
+    }
+  }
+
+  for (int k = k0; k < ke; ++k) {
+    const int cur = k & 1, nxt = cur ^ 1;
+    const double s0 = sigma[k], ds = sigma[k + 1] - s0;
+    const double ids = rcp64(ds);
+    for (int g = ib; PASSES ? g < ie : g == ib; g += PRISM_ITEMS) {
+      if constexpr (PASSES) load_item(g);
+      if constexpr (!AHEAD) {
+        gather(k, lo);
+        f0 = slopes(lo);
+        gather(k + 1, up);
+      }
+      // nothing derived from the ids is kept across layers (hoisted addresses spill)
+      asm volatile("" : "+v"(vid[0]), "+v"(vid[1]), "+v"(vid[2]), "+v"(Dv), "+v"(soff), "+v"(rloc), "+v"(rk));
+      const Slopes f1 = slopes(up);
+      // differences first: exact where the levels are close
+      double du[3], dv[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        du[i] = up[i].x - lo[i].x;
+        dv[i] = up[i].y - lo[i].y;
+        lo[i] = up[i];
+      }
+      if (AHEAD && k + 1 < ke) gather(k + 2, up);
+      const double dum_ = (du[0] + du[1] + du[2]) * (1.0 / 6.0), dvm_ = (dv[0] + dv[1] + dv[2]) * (1.0 / 6.0);
+      const double l0 = 1.0 - zeta, l1 = zeta, sz = fma(zeta, ds, s0);
+      const double zxs = fma(sz, c_[THK], c_[BED]), zys = fma(sz, c_[THK + 1], c_[BED + 1]);
+      const double ucx = fma(l0, f0.ux, l1 * f1.ux), ucy = fma(l0, f0.uy, l1 * f1.uy);
+      const double vcx = fma(l0, f0.vx, l1 * f1.vx), vcy = fma(l0, f0.vy, l1 * f1.vy);
+      f0 = f1;
+      const double gx = ds * c_[GRAV], gy = ds * c_[GRAV + 1], lx0 = c_[LX], ly0 = c_[LY];
+      AT S[2][4][2], B[2][4][3];     // sums of L (x, y) and, per triangle point, of L . p (signed by the lane)
+      double Rl[2][2] = {{l0 * gx, l0 * gy}, {l1 * gx, l1 * gy}};
+#pragma unroll
+      for (int tp = 0; tp < 3; ++tp) {
+        const double iz = c_[INVH + tp] * ids, W = c_[WH + tp] * ds, lam_a = tp == 0 ? 2.0 / 3.0 : 1.0 / 6.0;
+        const double dum = fma(0.5, du[tp], dum_), dvm = fma(0.5, dv[tp], dvm_);
+        const double px = -zxs * iz, py = -zys * iz;        // d zeta / dx, d zeta / dy
+        const double ux = fma(px, dum, ucx), uy = fma(py, dum, ucy);
+        const double vx = fma(px, dvm, vcx), vy = fma(py, dvm, vcy);
+        const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = 0.5 * (iz * dum), eyz = 0.5 * (iz * dvm);
+        const double qe = fma(exx, exx, fma(eyy, exx + eyy, fma(exy, exy, fma(exz, exz, fma(eyz, eyz, m.eps0_sq)))));
+        // 2 mu W, and 2 mu' W = 2 visc_exp mu W / q; for n = 3, mu is q^(-1/3) and 1/q its cube
+        double s2, t2;
+        if constexpr (N3) {
+          const double y = rcbrt64(qe);
+          s2 = y * W;
+          t2 = (s2 * tfac) * (y * y * y);
+        } else {
+          s2 = powq(qe, m.visc_exp) * W;
+          t2 = (s2 * tfac) * rcp64(qe);
+        }
+        const double E1x = 2.0 * exx + eyy, E2y = exx + 2.0 * eyy;
+        const AT spx = AT(flip(px, minus)), spy = AT(flip(py, minus)), spz = AT(flip(iz, minus));
+        const AT e1x = AT(E1x), e1y = AT(exy), e2y = AT(E2y), e1z = AT(exz), e2z = AT(eyz), half = AT(0.5);
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          const double l = a ? l1 : l0, la = a ? lam_a : -lam_a;
+          const double ax = fma(l, lx0, la * px), ay = fma(l, ly0, la * py), az = la * iz;
+          const double g0 = E1x * ax + exy * ay + exz * az, g1 = exy * ax + E2y * ay + eyz * az;
+          Rl[a][0] = fma(s2, g0, Rl[a][0]);
+          Rl[a][1] = fma(s2, g1, Rl[a][1]);
+          if constexpr (JAC) {
+            const AT Ax = AT(s2 * ax), Ay = AT(s2 * ay), Az = AT(s2 * az), T0 = AT(t2 * g0), T1 = AT(t2 * g1);
+            const AT hAx = half * Ax, hAy = half * Ay, hAz = half * Az;
+            // L for uu, uv, vu, vv: coefficients of (bx, by, bz) in d R_(a,c) / d U_(b,d)
+            const AT Lx[4] = {fma(T0, e1x, Ax + Ax), fma(T0, e1y, hAy), fma(T1, e1x, Ay), fma(T1, e1y, hAx)};
+            const AT Ly[4] = {fma(T0, e1y, hAy), fma(T0, e2y, Ax), fma(T1, e1y, hAx), fma(T1, e2y, Ay + Ay)};
+            const AT Lz[4] = {fma(T0, e1z, hAz), T0 * e2z, T1 * e1z, fma(T1, e2z, hAz)};
+#pragma unroll
+            for (int cd = 0; cd < 4; ++cd) {
+              S[a][cd][0] = tp == 0 ? Lx[cd] : S[a][cd][0] + Lx[cd];
+              S[a][cd][1] = tp == 0 ? Ly[cd] : S[a][cd][1] + Ly[cd];
+              B[a][cd][tp] = fma(Lx[cd], spx, fma(Ly[cd], spy, Lz[cd] * spz));
+            }
+          }
+        }
+      }
+      __builtin_amdgcn_s_setprio(1);
+      // residual: lane z ends with row node z
+      {
+        const double k0_ = z ? Rl[1][0] : Rl[0][0], k1_ = z ? Rl[1][1] : Rl[0][1];
+        const double s0_ = z ? Rl[0][0] : Rl[1][0], s1_ = z ? Rl[0][1] : Rl[1][1];
+        const double r0 = k0_ + quad_xor<1>(s0_), r1 = k1_ + quad_xor<1>(s1_);
+        if (act) {
+          double *r = Rw + (z ? nxt : cur) * 2 * max_tv + rloc;
+          lds_add(r, r0);
+          lds_add(r + 1, r1);
+        }
+      }
+      if constexpr (JAC) {
+        AT hx[3], hy[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          hx[j] = AT(c_[LX + j]);
+          hy[j] = AT(c_[LY + j]);
+        }
+#pragma unroll
+        for (int a = 0; a < 2; ++a) {
+          // level k sits at window position 1 unless k = 0
+          const int nl = a ? nlev(k + 1, L) : nlev(k, L);
+          double *w = Jw + (a ? nxt : cur) * max_slot + soff + 2 * ((a ^ z) + (!a && k > 0 ? 1 : 0));
+          double *wj[3];
+#pragma unroll
+          for (int j = 0; j < 3; ++j) wj[j] = w + int((rk >> (8 * j)) & 255u) * 2 * nl;
+          const bool add = act && (a == 0 || !CARRY || z == 1 || k + 1 == L || PASSES);
+          const AT lkept = AT(a ? G1 : G2), lsent = AT(a ? G2 : G1), sixth = AT(1.0 / 6.0), half = AT(0.5);
+#pragma unroll
+          for (int cd = 0; cd < 4; ++cd) {
+            const AT bm = sixth * (B[a][cd][0] + B[a][cd][1] + B[a][cd][2]);
+            AT e[3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+              const AT h = fma(hx[j], S[a][cd][0], hy[j] * S[a][cd][1]);
+              const AT lb = fma(half, B[a][cd][j], bm);
+              e[j] = fma(lkept, h, a ? -lb : lb) + quad_xor<1>(fma(lsent, h, a ? lb : -lb));
+              if (CARRY && a == 0) e[j] += carry[cd][j];
+            }
+            const int off = (cd >> 1) * 2 * nl * Dv + (cd & 1);
+            if (add) {
+#pragma unroll
+              for (int j = 0; j < 3; ++j) lds_add(wj[j] + off, double(e[j]));
+            }
+            if (CARRY && a == 1) {
+#pragma unroll
+              for (int j = 0; j < 3; ++j) carry[cd][j] = z || PASSES ? AT(0) : e[j];
+            }
+          }
+        }
+      }
+    }
+    // the next level's velocities are waited for here: after the copy-out the wait would be for its
+    // stores too, which retire through the same counter
+    if constexpr (AHEAD) asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));
+    wave_sync();
+    // The copy-out runs at raised wave priority (2), the window adds at 1: the copy-out's LDS reads
+    // and streaming stores then issue ahead of the other waves' work instead of queuing behind it.
+    __builtin_amdgcn_s_setprio(2);
+    if (k > 0 && (!JAC || flat.slot_size > 0))
+      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    else
+      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    wave_sync();
+    __builtin_amdgcn_s_setprio(0);
+  }
+}
+
 // ---- hexahedra ----------------------------------------------------------------------------
 // Four lanes per item, one per Gauss point of the base quadrilateral (two zeta points each): a
 // lane evaluates the physics of its two points once, and the entries of the item's rows are
@@ -767,33 +1201,23 @@ __device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, c
 // entries at level b0 as "kept" and at the other level as "sent" (lane-constant weights l_b0 and
 // l_(1-b0)), and walks the corners in the order jj -> (jj + 2 b1) & 3, so that its first two
 // are kept in the second exchange.  It ends with corners 2 b1 and 2 b1 + 1 at level b0.
-__device__ __forceinline__ int quad_xor_i(int v, bool two) {
-  return two ? __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
-}
-template <int X>
-__device__ __forceinline__ double quad_xor(double v) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = uint32_t(quad_xor_i(int(uint32_t(u)), X == 2));
-  const uint32_t hi = uint32_t(quad_xor_i(int(uint32_t(u >> 32)), X == 2));
-  return __builtin_bit_cast(double, uint64_t(lo) | (uint64_t(hi) << 32));
-}
-template <int X>
-__device__ __forceinline__ float quad_xor(float v) {
-  return __builtin_bit_cast(float, quad_xor_i(__builtin_bit_cast(int, v), X == 2));
-}
-
 constexpr int HEX_ITEMS = WAVE / 4;   // items per pass of a wave
 
 // The levels kb <= k < ke of a task's columns (and level L if ke = L).  kb > 0 starts with layer
-// kb - 1, whose lower rows belong to the range below and are dropped.
-template <bool JAC, class JT, bool N3>
+// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: a task may hold
+// more items than one pass of a wave takes (a vertex in more cells than that is a task of its
+// own), so the item constants are reloaded for every layer and pass.
+template <bool JAC, class JT, bool N3, bool PASSES>
 __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, const double *__restrict__ U,
                                          double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
                                          int max_tv, int kb, int ke, unsigned char *smem) {
   using AT = JT;   // derivative arithmetic type
   double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
   double *Rw = reinterpret_cast<double *>(smem + (JAC ? 2 * size_t(max_slot) * sizeof(double) : 0));  // [2][2 max_tv]
+  const double tfac = picard ? 0.0 : 2.0 * m.visc_exp;   // 2 mu' = 2 visc_exp mu / q
+  const ScalarTable sigma = scalar_table(m.sigma);
   const int lane = threadIdx.x, b0 = lane & 1, b1 = (lane >> 1) & 1;
+  const int slot = 4 * ((lane >> 2) & 3) + (lane >> 4);   // as for prisms
   const int vb = task.y, ve = task.z, ib = task.w, ie = m.vc_ptr[ve];
   const int L = m.L, nvt = ve - vb;
   const TaskColumns cols = load_columns(m, vb, nvt, lane);
@@ -805,6 +1229,7 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
 #pragma unroll
     for (int j = 0; j < 4; ++j) lam[j] = b1 ? la[(j + 2) & 3] : la[j];
   }
+  const FlatCopy flat = flat_copy<JAC>(m, cols, vb, nvt, lane);
   clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
 
   // item constants: corner ids, gradients at the lane's point, weight x determinant x thickness,
@@ -814,8 +1239,8 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
   bool act = false;
   double wH = 0, sx = 0, sy = 0, iH = 0, Bx = 0, By = 0, Hx = 0, Hy = 0, lam_a = 0, lxa = 0, lya = 0;
   auto load_item = [&](int first) {
-    act = first + (lane >> 2) < ie;
-    const int item = act ? first + (lane >> 2) : ib;
+    act = first + slot < ie;
+    const int item = act ? first + slot : ib;
     const int v = m.item_vtx[item], t = m.vc_idx[item], al = (int(m.vc_pos[item]) - 2 * b1) & 3;
     Dv = m.deg[v];
     soff = m.slot_off[v];
@@ -890,13 +1315,12 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
   wave_sync();
 
   const int k0 = kb > 0 ? kb - 1 : 0;
-  const bool once = ie - ib <= HEX_ITEMS;   // more items only around a vertex with more than 16 cells
   double2 lo[4], up[4];                     // u, v of the corners on levels k and k + 1
   Slopes f0 = {0, 0, 0, 0};
 
   // ---- bed friction on the lower face of the bottom layer: rows of the level-0 nodes -----------
   if (kb == 0) {
-    for (int g = ib; g < ie; g += HEX_ITEMS) {
+    for (int g = ib; PASSES ? g < ie : g == ib; g += HEX_ITEMS) {
       const double4 map = load_item(g);
       gather(0, lo);
       double br = 0.0, ur = 0.0, vr = 0.0;
@@ -925,21 +1349,22 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
       }
     }
   }
-  if (once) {
+  if constexpr (!PASSES) {
     if (kb > 0) load_item(ib);
     gather(k0, lo);
     f0 = slopes(lo);
     gather(k0 + 1, up);
+    asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y), "+v"(up[3].x), "+v"(up[3].y));   // waited for here, as below
   }
 
   // lane-constant weights of the kept and sent levels at the two zeta points, and signed basis
   const AT lk[2] = {AT(b0 ? G1 : 1.0 - G1), AT(b0 ? G2 : 1.0 - G2)}, ls[2] = {AT(1) - lk[0], AT(1) - lk[1]};
   for (int k = k0; k < ke; ++k) {
     const int cur = k & 1, nxt = cur ^ 1;
-    const double s0 = m.sigma[k], ds = m.sigma[k + 1] - s0;
+    const double s0 = sigma[k], ds = sigma[k + 1] - s0;
     const double ids = rcp64(ds);
-    for (int g = ib; g < ie; g += HEX_ITEMS) {
-      if (!once) {
+    for (int g = ib; PASSES ? g < ie : g == ib; g += HEX_ITEMS) {
+      if constexpr (PASSES) {
         load_item(g);
         gather(k, lo);
         f0 = slopes(lo);
@@ -953,7 +1378,7 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
         dvm = fma(lam[j], up[j].y - lo[j].y, dvm);
         lo[j] = up[j];
       }
-      if (once && k + 1 < ke) gather(k + 2, up);
+      if (!PASSES && k + 1 < ke) gather(k + 2, up);
       const double iz = iH * ids, Wz = wH * ds;
       const double exz = 0.5 * (iz * dum), eyz = 0.5 * (iz * dvm);
       // the physics of the lane's two points
@@ -975,7 +1400,7 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
         if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
         else mu = m.visc_pref * powq(qe, m.visc_exp);
         s2[zi] = 2.0 * mu * Wz;
-        t2[zi] = picard ? 0.0 : 2.0 * (m.visc_exp * mu * rcp64(qe)) * Wz;
+        t2[zi] = (mu * rcp64(qe)) * (tfac * Wz);
         E1x[zi] = 2.0 * exx + eyy;
         Exy[zi] = exy;
         E2y[zi] = exx + 2.0 * eyy;
@@ -1050,9 +1475,15 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
         if (act) lds_add(Rw + (b0 ? nxt : cur) * 2 * max_tv + rloc + b1, own);
       }
     }
+    // the next level's velocities are waited for here: after the copy-out the wait would be for its
+    // stores too, which retire through the same counter
+    if constexpr (!PASSES) asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y), "+v"(up[3].x), "+v"(up[3].y));
     wave_sync();
     __builtin_amdgcn_s_setprio(2);
-    copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k > 0 && (!JAC || flat.slot_size > 0))
+      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    else
+      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     wave_sync();
     __builtin_amdgcn_s_setprio(0);
@@ -1068,14 +1499,25 @@ __global__ __launch_bounds__(WAVE, 2) void owner_kernel(MeshView m, const int4 *
 }
 
 // Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
-template <bool JAC, class JT, bool N3>
+template <bool JAC, class JT, bool N3, bool PASSES>
+__global__ __launch_bounds__(WAVE, PRISM_WAVES) void prism_owner_kernel(MeshView m, const int4 *__restrict__ tasks, int lpc,
+                                                              const double *__restrict__ U, double *__restrict__ R,
+                                                              JT *__restrict__ J, int picard, int max_slot,
+                                                              int max_tv) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
+  prism_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+}
+
+// Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
+template <bool JAC, class JT, bool N3, bool PASSES>
 __global__ __launch_bounds__(WAVE, 2) void hex_owner_kernel(MeshView m, const int4 *__restrict__ tasks, int lpc,
                                                             const double *__restrict__ U, double *__restrict__ R,
                                                             JT *__restrict__ J, int picard, int max_slot,
                                                             int max_tv) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
-  hex_task<JAC, JT, N3>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+  hex_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
 }
 
 // Persistent ensemble launch: each workgroup repeatedly takes the next (member, task) pair
@@ -1105,13 +1547,24 @@ __global__ __launch_bounds__(WAVE, 2) void ensemble_kernel(const EnsembleMember 
   });
 }
 
-template <bool JAC, class JT, bool N3>
+template <bool JAC, class JT, bool N3, bool PASSES>
+__global__ __launch_bounds__(WAVE, PRISM_WAVES) void prism_ensemble_kernel(const EnsembleMember *__restrict__ mem,
+                                                                 const int4 *__restrict__ tasks, int n_tasks,
+                                                                 int *__restrict__ counter, int picard) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
+    prism_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0,
+                            e.view.L, smem);
+  });
+}
+
+template <bool JAC, class JT, bool N3, bool PASSES>
 __global__ __launch_bounds__(WAVE, 2) void hex_ensemble_kernel(const EnsembleMember *__restrict__ mem,
                                                                const int4 *__restrict__ tasks, int n_tasks,
                                                                int *__restrict__ counter, int picard) {
   extern __shared__ __align__(16) unsigned char smem[];
   ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
-    hex_task<JAC, JT, N3>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0, e.view.L,
+    hex_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0, e.view.L,
                           smem);
   });
 }
@@ -1155,8 +1608,8 @@ enum Cell { PRISM, TETS, HEX };
 // Jacobian, the per-lane carry slots (WAVE x 4 FP64) that follow them on prisms.
 template <Cell C>
 size_t window_bytes(bool jac, int max_slot, int max_tv) {
-  return (jac ? 2 * size_t(max_slot) * sizeof(double) + (C == HEX ? 0 : size_t(WAVE) * 4 * sizeof(double)) : 0) +
-         2 * 2 * size_t(max_tv) * sizeof(double);
+  return (jac ? 2 * size_t(max_slot) * sizeof(double) + (C != TETS ? 0 : size_t(WAVE) * 4 * sizeof(double)) : 0) +
+         2 * 2 * size_t(max_tv) * sizeof(double) + (C == PRISM ? size_t(PRISM_ITEMS) * PRISM_CONST * sizeof(double) : 0);
 }
 
 // Layers per block of a launch with n_tasks tasks of L layers.  A small mesh leaves the chip
@@ -1179,18 +1632,22 @@ int layers_per_block(int64_t n_tasks, int L, int64_t resident) {
   return best;
 }
 
-constexpr int64_t HEX_RESIDENT = 2048;   // two waves on each of 1024 SIMDs
+constexpr int64_t RESIDENT = 2048;   // two waves on each of 1024 SIMDs
 
-template <Cell C, bool JAC, class JT, bool N3>
+template <Cell C, bool JAC, class JT, bool N3, bool PASSES>
 fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int kind, hipStream_t s) {
   const MeshView &m = mesh->view;
   const size_t lds = window_bytes<C>(JAC, mesh->max_slot, mesh->max_task_verts);
   const int picard = kind == FO_JAC_PICARD ? 1 : 0;
   fo_status st = profile_begin(mesh, s);
   if (st != FO_OK) return st;
-  if constexpr (C == HEX) {
-    const int lpc = layers_per_block(mesh->n_tasks, m.L, HEX_RESIDENT);
-    hipLaunchKernelGGL((hex_owner_kernel<JAC, JT, N3>), dim3(unsigned(mesh->n_tasks), unsigned((m.L + lpc - 1) / lpc)),
+  if constexpr (C != TETS) {
+    const int lpc = layers_per_block(mesh->n_tasks, m.L, RESIDENT);
+    auto kern = [] {
+      if constexpr (C == HEX) return hex_owner_kernel<JAC, JT, N3, PASSES>;
+      else return prism_owner_kernel<JAC, JT, N3, PASSES>;
+    }();
+    hipLaunchKernelGGL(kern, dim3(unsigned(mesh->n_tasks), unsigned((m.L + lpc - 1) / lpc)),
                        dim3(WAVE), lds, s, m, mesh->tasks, lpc, U, R, J, picard, mesh->max_slot,
                        mesh->max_task_verts);
   } else {
@@ -1201,11 +1658,12 @@ fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int k
   return profile_end(mesh, s);
 }
 
-template <Cell C, bool JAC, class JT, bool N3>
+template <Cell C, bool JAC, class JT, bool N3, bool PASSES>
 fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
   const size_t lds = window_bytes<C>(JAC, E.max_slot, E.max_tv);
   auto kern = [] {
-    if constexpr (C == HEX) return hex_ensemble_kernel<JAC, JT, N3>;
+    if constexpr (C == HEX) return hex_ensemble_kernel<JAC, JT, N3, PASSES>;
+    else if constexpr (C == PRISM) return prism_ensemble_kernel<JAC, JT, N3, PASSES>;
     else return ensemble_kernel<JAC, JT, N3, C == TETS>;
   }();
   int per_cu = 0;
@@ -1222,11 +1680,16 @@ fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
   return FO_OK;
 }
 
-// Calls f<cell, jac, value type, n = 3> for the run-time choices
+// Calls f<cell, jac, value type, n = 3, several passes> for the run-time choices
 template <class F>
-fo_status by_kernel(int nv, bool tet, bool want_jac, int dtype, bool n3, F f) {
+fo_status by_kernel(int nv, bool tet, bool want_jac, int dtype, bool n3, bool passes, F f) {
+  auto by_pass = [&](auto c, auto jac, auto val, auto n) {
+    if constexpr (c.value != TETS)
+      if (passes) return f(c, jac, val, n, std::true_type{});
+    return f(c, jac, val, n, std::false_type{});
+  };
   auto by_n = [&](auto c, auto jac, auto val) {
-    return n3 ? f(c, jac, val, std::true_type{}) : f(c, jac, val, std::false_type{});
+    return n3 ? by_pass(c, jac, val, std::true_type{}) : by_pass(c, jac, val, std::false_type{});
   };
   auto by_type = [&](auto c) {
     if (!want_jac) return by_n(c, std::false_type{}, double{});
@@ -1253,8 +1716,8 @@ fo_status launch_front_add(const MeshView &m, int32_t n_front, const int32_t *vt
 fo_status launch_ensemble(const EnsembleLaunch &E, int dtype, int kind, bool want_jac, hipStream_t s) {
   fo_status st = ensure_tables(E.device);
   if (st != FO_OK) return st;
-  return by_kernel(E.nv, E.tet, want_jac, dtype, E.all_n3, [&](auto c, auto jac, auto val, auto n3) {
-    return launch_ens_t<c.value, jac.value, decltype(val), n3.value>(E, kind, s);
+  return by_kernel(E.nv, E.tet, want_jac, dtype, E.all_n3, E.passes, [&](auto c, auto jac, auto val, auto n3, auto ps) {
+    return launch_ens_t<c.value, jac.value, decltype(val), n3.value, ps.value>(E, kind, s);
   });
 }
 
@@ -1290,10 +1753,12 @@ fo_status launch_assemble_cells(const fo_mesh *mesh, const double *U, double *R,
   fo_status st = ensure_tables(mesh->device);
   if (st != FO_OK) return st;
   const MeshView &m = mesh->view;
-  return by_kernel(m.nv, m.tet != 0, want_jac, dtype, m.n_glen == 3.0, [&](auto c, auto jac, auto val, auto n3) {
-    using JT = decltype(val);
-    return launch_t<c.value, jac.value, JT, n3.value>(mesh, U, R, jac.value ? static_cast<JT *>(J) : nullptr, kind, s);
-  });
+  return by_kernel(m.nv, m.tet != 0, want_jac, dtype, m.n_glen == 3.0, mesh->passes,
+                   [&](auto c, auto jac, auto val, auto n3, auto ps) {
+                     using JT = decltype(val);
+                     return launch_t<c.value, jac.value, JT, n3.value, ps.value>(
+                         mesh, U, R, jac.value ? static_cast<JT *>(J) : nullptr, kind, s);
+                   });
 }
 
 }  // namespace fo

@@ -36,7 +36,7 @@ extern "C" fo_status fo_ensemble_create(const fo_mesh *const *members, int32_t n
   if (!members || n_members < 1) return fail(FO_EINVAL, "fo_ensemble_create: need at least one member");
   const int nv = members[0] ? members[0]->view.nv : 0;
   int64_t total = 0;
-  bool all_n3 = true;
+  bool all_n3 = true, passes = false;
   int32_t max_slot = 0, max_tv = 0;
   for (int i = 0; i < n_members; ++i) {
     const fo_mesh *m = members[i];
@@ -45,6 +45,7 @@ extern "C" fo_status fo_ensemble_create(const fo_mesh *const *members, int32_t n
       return fail(FO_EINVAL, "fo_ensemble_create: members must share the element type");
     total += m->n_tasks;
     all_n3 = all_n3 && m->view.n_glen == 3.0;
+    passes = passes || m->passes;
     max_slot = std::max(max_slot, m->max_slot);
     max_tv = std::max(max_tv, m->max_task_verts);
   }
@@ -81,6 +82,7 @@ extern "C" fo_status fo_ensemble_create(const fo_mesh *const *members, int32_t n
   L.nv = nv;
   L.tet = members[0]->view.tet != 0;
   L.all_n3 = all_n3;
+  L.passes = passes;
   L.max_slot = max_slot;
   L.max_tv = max_tv;
   L.n_cu = n_cu;

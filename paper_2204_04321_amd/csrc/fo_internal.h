@@ -96,6 +96,7 @@ struct fo_mesh {
   std::vector<int4> tasks_host; // host copy, for building ensembles
   int32_t max_slot = 0;         // largest LDS level window (entries) over tasks
   int32_t max_task_verts = 0;
+  bool passes = false;          // some task holds more items than one pass of a wave takes
   int64_t *rowptr = nullptr;    // [n_dofs + 1]
   int32_t *colidx = nullptr;    // [nnz]
   int device = 0;
@@ -124,6 +125,7 @@ struct EnsembleLaunch {
   int32_t nv;
   bool tet;
   bool all_n3;
+  bool passes;
   int32_t max_slot, max_tv;
   int32_t n_cu;
   int device;

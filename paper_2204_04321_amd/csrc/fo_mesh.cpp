@@ -228,13 +228,14 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
   // whose level windows (12 D entries per vertex) fit the per-wave LDS budget
   // kMaxSlot: two level windows of at most 1080 FP64 entries, the residual windows and the
   // per-lane carry slots (2 KB) keep a wave's LDS under 20 KB, so that eight waves share a
-  // compute unit.  Hexahedra take four lanes per item: 16 items a wave (a vertex with more is a
-  // task of its own and takes several passes).
+  // compute unit.  Hexahedra take four lanes per item and prisms two: 16 and 32 items a wave (a
+  // vertex with more is a task of its own and takes several passes).
   constexpr int kMaxItems = 64, kMaxSlot = 1080;
-  const int task_items = nv == 4 ? kMaxItems / 4 : kMaxItems;
+  const int task_items = nv == 4 ? kMaxItems / 4 : d->elem == FO_WEDGE6 ? kMaxItems / 2 : kMaxItems;
   std::vector<int4> tasks;
   std::vector<int32_t> slot_off(V);
   int32_t max_slot = 0, max_tv = 0;
+  bool passes = false;
   {
     int32_t vb = 0, items = 0, slot = 0;
     for (int32_t v = 0; v < int32_t(V); ++v) {
@@ -244,6 +245,7 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
         return fail(FO_EDEGENERATE, "fo_mesh_create: vertex " + std::to_string(v) + " lies in no base cell");
       if (ni > kMaxItems)
         return fail(FO_EINVAL, "fo_mesh_create: vertex " + std::to_string(v) + " lies in more than 64 base cells");
+      passes = passes || ni > task_items;
       if (sz > kMaxSlot)
         return fail(FO_EINVAL, "fo_mesh_create: vertex " + std::to_string(v) + " has more than 90 neighbouring vertices");
       if (v > vb && (items + ni > task_items || slot + sz > kMaxSlot)) {
@@ -332,6 +334,7 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
   m->tasks_host = tasks;
   m->max_slot = max_slot;
   m->max_task_verts = max_tv;
+  m->passes = passes;
   mv.rho_g = d->rho * d->g;
   mv.visc_pref = 0.5 * std::pow(d->A, -1.0 / d->n);
   mv.visc_exp = (1.0 - d->n) / (2.0 * d->n);
