@@ -21,8 +21,8 @@
 // zero fill of J or R, every value written once; results do not depend on
 // scheduling.  Each cell is evaluated by each of its vertex columns (3 or 4
 // times) in exchange.  Prisms spread an item over two lanes (prism_task below), hexahedra over
-// four (hex_task).  The level windows are FP64 for either
-// Jacobian value type.
+// four (hex_task); base triangles split into tetrahedra take one lane (tet_task).  The level
+// windows are FP64 for either Jacobian value type.
 //
 // CSR slot of row (v, level kr, comp c) and column (vertex of rank r in v's sorted
 // neighbour list, level kc, comp d): colptr[v] + 4 D_v cumlev(kr) + c 2 nlev(kr) D_v
@@ -45,35 +45,6 @@ constexpr int WAVE = 64;
 
 constexpr double G1 = 0.21132486540518711775;   // 1/2 - 1/(2 sqrt 3)
 constexpr double G2 = 0.78867513459481288225;   // 1/2 + 1/(2 sqrt 3)
-
-// Quadrature of a prism (the unit triangle times zeta in [0,1]: a degree-2 rule of three points
-// times two Gauss points) and of its lower face: weights, zeta, 2D basis values and reference
-// derivatives at each point.
-constexpr int NQ = 6, NQB = 3;
-struct QTable {
-  double w[NQ], zeta[NQ], lam[NQ][3];
-  double bw[NQB], blam[NQB][3], bdlx[NQB][3], bdly[NQB][3];
-};
-
-__constant__ QTable kQ;
-
-constexpr QTable make_table() {
-  QTable t{};
-  for (int q = 0; q < NQ; ++q) {
-    const int tq = q % 3;
-    const double xi = (tq == 1) ? 2.0 / 3.0 : 1.0 / 6.0, eta = (tq == 2) ? 2.0 / 3.0 : 1.0 / 6.0;
-    t.w[q] = 1.0 / 12.0;
-    t.zeta[q] = (q < 3) ? G1 : G2;
-    t.lam[q][0] = 1.0 - xi - eta; t.lam[q][1] = xi; t.lam[q][2] = eta;
-  }
-  for (int r = 0; r < NQB; ++r) {
-    t.bw[r] = 1.0 / 6.0;
-    for (int i = 0; i < 3; ++i) t.blam[r][i] = t.lam[r][i];
-    t.bdlx[r][0] = -1.0; t.bdlx[r][1] = 1.0;
-    t.bdly[r][0] = -1.0; t.bdly[r][2] = 1.0;
-  }
-  return t;
-}
 
 __device__ __forceinline__ int nlev(int k, int L) { return (k == 0 || k == L) ? 2 : 3; }
 __device__ __forceinline__ int cumlev(int k) { return k == 0 ? 0 : 3 * k - 1; }
@@ -156,125 +127,6 @@ __device__ __forceinline__ void store2_nt(JT *p, double x, double y) {
   __builtin_nontemporal_store(t, reinterpret_cast<v2 *>(p));
 }
 
-// Tetrahedral extrusion: one layer of a base triangle's prism, split into three
-// tetrahedra by the global order of its corners (the corners arrive sorted, so corner r
-// has the r-th smallest vertex id): (0,1,2,0'), (1,2,0',1'), (2,0',1',2'), primes one level
-// up.  Linear basis: gradients, strain rate and viscosity are constant on a tetrahedron,
-// so every integral is exact (V times the integrand, int phi_a = V/4).  Adds the residual
-// rows of the item's two nodes (corner ra at the lower and upper level) and their
-// derivatives along the prism's 12 dofs: Jx[row level][c][d][corner][level].
-constexpr int TET_R[3][4] = {{0, 1, 2, 0}, {1, 2, 0, 1}, {2, 0, 1, 2}};   // corner of node a
-constexpr int TET_L[3][4] = {{0, 0, 0, 1}, {0, 0, 1, 1}, {0, 1, 1, 1}};   // level of node a
-
-template <class AT, bool JAC, bool N3>
-__device__ __forceinline__ void tet_layer(const MeshView &m, int ra, int picard, const double *xr, const double *yr,
-                                          const double *zlo, const double *dz, const double *ulo,
-                                          const double *du, const double *vlo, const double *dv,
-                                          const double *sv, double &Rb0, double &Rb1, double &Rt0, double &Rt1,
-                                          AT (&Jx)[2][2][2][3][2]) {
-#pragma unroll
-  for (int q = 0; q < 3; ++q) {
-    double X[4][3], ua[4], va[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const int r = TET_R[q][a], l = TET_L[q][a];
-      X[a][0] = xr[r];
-      X[a][1] = yr[r];
-      X[a][2] = l ? zlo[r] + dz[r] : zlo[r];
-      ua[a] = l ? ulo[r] + du[r] : ulo[r];
-      va[a] = l ? vlo[r] + dv[r] : vlo[r];
-    }
-    // rows of M: edges from node 0; columns of M^-1 are the gradients of phi_1..3
-    double e[3][3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-#pragma unroll
-      for (int i = 0; i < 3; ++i) e[j][i] = X[j + 1][i] - X[0][i];
-    double cr[3][3];   // cr[j] = e[j+1] x e[j+2]
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      const double *p = e[(j + 1) % 3], *w = e[(j + 2) % 3];
-      cr[j][0] = p[1] * w[2] - p[2] * w[1];
-      cr[j][1] = p[2] * w[0] - p[0] * w[2];
-      cr[j][2] = p[0] * w[1] - p[1] * w[0];
-    }
-    const double det = e[0][0] * cr[0][0] + e[0][1] * cr[0][1] + e[0][2] * cr[0][2];
-    const double idet = rcp64(det);
-    double g[4][3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      g[1][i] = cr[0][i] * idet;
-      g[2][i] = cr[1][i] * idet;
-      g[3][i] = cr[2][i] * idet;
-      g[0][i] = -(g[1][i] + g[2][i] + g[3][i]);
-    }
-    const double V = fabs(det) * (1.0 / 6.0);
-    double ux = 0, uy = 0, uz = 0, vx = 0, vy = 0, vz = 0, sx = 0, sy = 0;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      ux = fma(ua[a], g[a][0], ux); uy = fma(ua[a], g[a][1], uy); uz = fma(ua[a], g[a][2], uz);
-      vx = fma(va[a], g[a][0], vx); vy = fma(va[a], g[a][1], vy); vz = fma(va[a], g[a][2], vz);
-      sx = fma(sv[TET_R[q][a]], g[a][0], sx); sy = fma(sv[TET_R[q][a]], g[a][1], sy);
-    }
-    const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = 0.5 * uz, eyz = 0.5 * vz;
-    const double qq = exx * exx + eyy * eyy + exx * eyy + exy * exy + exz * exz + eyz * eyz;
-    const double qe = qq + m.eps0_sq;
-    double mu;
-    if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
-    else mu = m.visc_pref * powq(qe, m.visc_exp);
-    const double s2 = 2.0 * mu * V;
-    const double t2 = picard ? 0.0 : 2.0 * (m.visc_exp * mu * rcp64(qe)) * V;
-    const double E[2][3] = {{2.0 * exx + eyy, exy, exz}, {exy, exx + 2.0 * eyy, eyz}};
-    const double gq = 0.25 * V * m.rho_g;       // rho g int phi_a / (d s)
-    // the item's two nodes: gradient on this tetrahedron (zero if not one of its nodes)
-    double gr[2][3] = {{0, 0, 0}, {0, 0, 0}}, in[2] = {0, 0};
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const double hit = TET_R[q][a] == ra ? 1.0 : 0.0;
-      const int l = TET_L[q][a];
-      in[l] += hit;
-#pragma unroll
-      for (int i = 0; i < 3; ++i) gr[l][i] = fma(hit, g[a][i], gr[l][i]);
-    }
-    double Rr[2][2];
-#pragma unroll
-    for (int l = 0; l < 2; ++l)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-        Rr[l][c] = fma(s2, E[c][0] * gr[l][0] + E[c][1] * gr[l][1] + E[c][2] * gr[l][2],
-                       gq * in[l] * (c ? sy : sx));
-    Rb0 += Rr[0][0]; Rb1 += Rr[0][1];
-    Rt0 += Rr[1][0]; Rt1 += Rr[1][1];
-    if constexpr (JAC) {
-      const AT s2a = AT(s2), t2a = AT(t2);
-#pragma unroll
-      for (int l = 0; l < 2; ++l) {
-        const AT ax = AT(gr[l][0]), ay = AT(gr[l][1]), az = AT(gr[l][2]);
-        const AT Ax = s2a * ax, Ay = s2a * ay, Az = s2a * az;
-        const AT T0 = t2a * AT(E[0][0] * gr[l][0] + E[0][1] * gr[l][1] + E[0][2] * gr[l][2]);
-        const AT T1 = t2a * AT(E[1][0] * gr[l][0] + E[1][1] * gr[l][1] + E[1][2] * gr[l][2]);
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          const int r = TET_R[q][b], lb = TET_L[q][b];
-          const AT bx = AT(g[b][0]), by = AT(g[b][1]), bz = AT(g[b][2]);
-          const AT Gu = AT(E[0][0]) * bx + AT(E[0][1]) * by + AT(E[0][2]) * bz;   // d(eps_e^2)/dU_(b,u)
-          const AT Gv = AT(E[1][0]) * bx + AT(E[1][1]) * by + AT(E[1][2]) * bz;   // d(eps_e^2)/dU_(b,v)
-          AT &uu = Jx[l][0][0][r][lb], &uv = Jx[l][0][1][r][lb];
-          AT &vu = Jx[l][1][0][r][lb], &vv = Jx[l][1][1][r][lb];
-          // K_uu = 2 ax bx + 1/2 ay by + 1/2 az bz, K_uv = ax by + 1/2 ay bx,
-          // K_vu = ay bx + 1/2 ax by, K_vv = 1/2 ax bx + 2 ay by + 1/2 az bz
-          uu = fma(Ax + Ax, bx, uu); uu = fma(AT(0.5) * Ay, by, uu); uu = fma(AT(0.5) * Az, bz, uu);
-          uu = fma(T0, Gu, uu);
-          uv = fma(Ax, by, uv); uv = fma(AT(0.5) * Ay, bx, uv); uv = fma(T0, Gv, uv);
-          vu = fma(Ay, bx, vu); vu = fma(AT(0.5) * Ax, by, vu); vu = fma(T1, Gu, vu);
-          vv = fma(AT(0.5) * Ax, bx, vv); vv = fma(Ay + Ay, by, vv); vv = fma(AT(0.5) * Az, bz, vv);
-          vv = fma(T1, Gv, vv);
-        }
-      }
-    }
-  }
-}
-
 // Metadata of a task's vertex columns, one column per lane (a task has at most 64)
 struct TaskColumns {
   int deg, soff, col_lo, col_hi;
@@ -306,31 +158,32 @@ __device__ __forceinline__ void clear_windows(const MeshView &m, double *Jw, dou
 // slot (12 D entries), so a task's window is one contiguous run; lane l moves the entry pairs
 // 2 l + 128 i.  off[i]: the pair's place on level 1, in entries from the task's first; deg: its
 // column's degree, 8 bits per i.  Each further level lies 12 D entries on.
-constexpr int FLAT_PARTS = 4;
+// N parts: 4 hold the windows of 32 items around vertices of up to six or seven cells, 8 those of 64.
+template <int N>
 struct FlatCopy {
-  uint32_t off[FLAT_PARTS], deg;
+  uint32_t off[N], deg[N / 4];
   int slot_size;      // 0: the window or the offsets are too large, columns are copied one by one
   int64_t base;       // colptr of the task's first column
 };
 
-template <bool JAC>
-__device__ __forceinline__ FlatCopy flat_copy(const MeshView &m, const TaskColumns &cols, int vb, int nvt, int lane) {
-  FlatCopy f = {{0u, 0u, 0u, 0u}, 0u, 0, 0};
+template <bool JAC, int N>
+__device__ __forceinline__ FlatCopy<N> flat_copy(const MeshView &m, const TaskColumns &cols, int vb, int nvt, int lane) {
+  FlatCopy<N> f = {};
   if constexpr (!JAC) return f;
   const int n = __builtin_amdgcn_readlane(cols.soff, nvt - 1) + 12 * __builtin_amdgcn_readlane(cols.deg, nvt - 1);
   f.base = int64_t(unsigned(__builtin_amdgcn_readlane(cols.col_lo, 0))) |
            (int64_t(__builtin_amdgcn_readlane(cols.col_hi, 0)) << 32);
-  if (n > 128 * FLAT_PARTS || m.L > 4096) return f;
+  if (n > 128 * N || m.L > 4096) return f;
   f.slot_size = n;
   for (int c = 0; c < nvt; ++c) {
     const int so = __builtin_amdgcn_readlane(cols.soff, c), D = __builtin_amdgcn_readlane(cols.deg, c);
     const uint32_t start = uint32_t(__builtin_amdgcn_readlane(cols.col_lo, c)) - uint32_t(f.base) + 8u * uint32_t(D);
 #pragma unroll
-    for (int i = 0; i < FLAT_PARTS; ++i) {
+    for (int i = 0; i < N; ++i) {
       const int e = 2 * lane + 128 * i;
       if (e >= so) {
         f.off[i] = start + uint32_t(e - so);
-        f.deg = (f.deg & ~(255u << (8 * i))) | (uint32_t(D) << (8 * i));
+        f.deg[i / 4] = (f.deg[i / 4] & ~(255u << (8 * (i & 3)))) | (uint32_t(D) << (8 * (i & 3)));
       }
     }
   }
@@ -339,23 +192,23 @@ __device__ __forceinline__ FlatCopy flat_copy(const MeshView &m, const TaskColum
 
 // Copies a finished interior level's window to its CSR rows and clears it for level + 2
 // (store = false: clears it only); all LDS reads are issued before the first store.
-template <bool JAC, class JT>
-__device__ __forceinline__ void copy_out_flat(const FlatCopy &f, int lev, int slot, bool store, int vb, int nvt, int L,
+template <bool JAC, int N, class JT>
+__device__ __forceinline__ void copy_out_flat(const FlatCopy<N> &f, int lev, int slot, bool store, int vb, int nvt, int L,
                                               double *Jw, double *Rw, int max_slot, int max_tv, int lane,
                                               double *__restrict__ R, JT *__restrict__ J) {
   if constexpr (JAC) {
     double *wb = Jw + slot * max_slot + 2 * lane;
     JT *dst = J + f.base;
     const uint32_t up = 12u * uint32_t(lev - 1);
-    double2 val[FLAT_PARTS];
+    double2 val[N];
 #pragma unroll
-    for (int i = 0; i < FLAT_PARTS; ++i)
+    for (int i = 0; i < N; ++i)
       if (128 * i < f.slot_size)     // past the window's end: other LDS of the task, not stored
         val[i] = *reinterpret_cast<const double2 *>(wb + (2 * lane + 128 * i < f.slot_size ? 128 * i : 0));
 #pragma unroll
-    for (int i = 0; i < FLAT_PARTS; ++i)
+    for (int i = 0; i < N; ++i)
       if (128 * i < f.slot_size && 2 * lane + 128 * i < f.slot_size) {
-        if (store) store2_nt(dst + (f.off[i] + up * ((f.deg >> (8 * i)) & 255u)), val[i].x, val[i].y);
+        if (store) store2_nt(dst + (f.off[i] + up * ((f.deg[i / 4] >> (8 * (i & 3))) & 255u)), val[i].x, val[i].y);
         *reinterpret_cast<double2 *>(wb + 128 * i) = make_double2(0.0, 0.0);
       }
   }
@@ -420,414 +273,6 @@ __device__ __forceinline__ void copy_out(const TaskColumns &cols, int lev, int s
   }
 }
 
-// One wave = one task (a run of vertex columns); one lane = one (v, t) item.
-// N3 selects the n = 3 viscosity power; JAC adds the Jacobian; JT is its value type
-// (double, or float with FP32 derivative arithmetic over the FP64 primal).
-template <bool JAC, class JT, bool N3, bool TET>
-__device__ __forceinline__ void owner_task(const MeshView &m, const int4 task, const double *__restrict__ U,
-                                           double *__restrict__ R, JT *__restrict__ J, int picard,
-                                           int max_slot, int max_tv, unsigned char *smem) {
-  constexpr int NV = 3;
-  using AT = JT;   // derivative arithmetic type
-  const QTable &Q = kQ;
-  // The level windows accumulate in FP64 for either value type: FP32 LDS atomics on this
-  // scatter pattern saturate the LDS data path (measured), FP64 ones do not.
-  double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
-  double *Rw = reinterpret_cast<double *>(smem + (JAC ? 2 * size_t(max_slot) * sizeof(double) : 0));  // [2][2 max_tv]
-  const int lane = threadIdx.x;
-  const int vb = task.y, ve = task.z, ib = task.w;
-  const int ie = m.vc_ptr[ve];
-  const bool act = ib + lane < ie;
-  const int item = act ? ib + lane : ib;
-  const int L = m.L;
-  const int v = act ? m.item_vtx[item] : vb;
-  const int t = act ? m.vc_idx[item] : 0;
-  const int al = act ? m.vc_pos[item] : 0;
-  // Prisms take their cell's corners in cyclic order starting at the item's own vertex, so
-  // that vertex is always corner 0 (a cyclic rotation keeps the triangle's orientation, and
-  // the triangle rules are invariant under it): its selections become constants and its
-  // Jacobian entries can be carried from layer to layer in registers (below).
-  constexpr bool ROT = !TET;
-  const int rot = ROT ? al : 0;
-  const int al_own = ROT ? 0 : al;
-  const int Dv = m.deg[v];
-  const int soff = m.slot_off[v];
-  // per-item integers fixed over the layers, packed: slot offset (12 bits, < 2048), degree
-  // (8), column position in the task (6, a task has at most 64 columns), corner (2).  Each
-  // layer re-derives them, the corner ranks and the corners' addresses from this word, the
-  // rank word and the vertex ids, passed through an empty asm statement: otherwise the
-  // compiler hoists the derived addresses out of the layer loop and spills them, and every
-  // reload costs a scratch round trip that serialises the layer's gather loads.
-  const uint32_t imeta_base = uint32_t(soff) | (uint32_t(Dv) << 12) | (uint32_t(v - vb) << 20);
-  const uint32_t imeta_cell = imeta_base | (uint32_t(al_own) << 26);
-  // 8 bits per corner: its rank in v's neighbour list
-  uint32_t irank = act ? m.item_rank[item] : 0u;
-  if constexpr (ROT) irank = ((irank >> (8 * rot)) | (irank << (8 * (3 - rot)))) & 0xFFFFFFu;
-
-  // ---- per-item constants -----------------------------------------------------------------
-  int vid[NV];
-  double xl[NV], yl[NV], bed[NV], Hh[NV], su[NV];
-  // horizontal coordinates relative to the cell's first corner, the bed, H and s
-  auto load_geo = [&](double *xl_, double *yl_, double *bed_, double *H_, double *s_) {
-    double x0 = 0, y0 = 0;
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const double4 g = m.geo[vid[i]];
-      if (i == 0) { x0 = g.x; y0 = g.y; }
-      xl_[i] = g.x - x0;
-      yl_[i] = g.y - y0;
-      bed_[i] = g.z;
-      H_[i] = g.w;
-      s_[i] = m.sb[vid[i]].x;
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int ci = ROT ? (i + rot >= 3 ? i + rot - 3 : i + rot) : i;
-    vid[i] = m.cells[int64_t(t) * NV + ci];
-  }
-  load_geo(xl, yl, bed, Hh, su);
-  // The layer loop walks the corners in lvid order with their neighbour ranks in lrank and
-  // the item's corner al_loop: the cell's own order, or for tetrahedra the order of the
-  // vertex ids (which fixes the split of each prism).
-  int lvid[NV];
-  uint32_t lrank = irank, imeta = imeta_cell;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) lvid[i] = vid[i];
-  if constexpr (TET) {
-    int rk_of[3];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) rk_of[i] = int(vid[i] > vid[(i + 1) % 3]) + int(vid[i] > vid[(i + 2) % 3]);
-    lrank = 0u;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      int vr = 0;
-      uint32_t br = 0u;
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        const int hit = int(rk_of[i] == r);
-        vr += hit * vid[i];
-        br += uint32_t(hit) * ((irank >> (8 * i)) & 255u);
-      }
-      lvid[r] = vr;
-      lrank |= br << (8 * r);
-    }
-    // lanes without an item take corner 3, which no tetrahedron node has: their rows get
-    // exact zeros, so the layer loop's adds need no divergent branch (see below)
-    const int al_loop = act ? rk_of[0] * int(al == 0) + rk_of[1] * int(al == 1) + rk_of[2] * int(al == 2) : 3;
-    imeta = imeta_base | (uint32_t(al_loop) << 26);
-  }
-  // P1 triangles: the horizontal basis gradients and the map determinant are constant
-  double lxc[NV], lyc[NV], detc = 0, sxc = 0, syc = 0;
-  {
-    const double x_xi = xl[1] - xl[0], x_eta = xl[2] - xl[0];
-    const double y_xi = yl[1] - yl[0], y_eta = yl[2] - yl[0];
-    detc = x_xi * y_eta - x_eta * y_xi;
-    const double iG = rcp64(detc);
-    lxc[1] = y_eta * iG; lxc[2] = -y_xi * iG; lxc[0] = -(lxc[1] + lxc[2]);
-    lyc[1] = -x_eta * iG; lyc[2] = x_xi * iG; lyc[0] = -(lyc[1] + lyc[2]);
-#pragma unroll
-    for (int i = 0; i < NV; ++i) { sxc += su[i] * lxc[i]; syc += su[i] * lyc[i]; }
-  }
-  const double lx_al = ROT ? lxc[0] : sel4(al, lxc[0], lxc[1], lxc[2], 0.0);
-  const double ly_al = ROT ? lyc[0] : sel4(al, lyc[0], lyc[1], lyc[2], 0.0);
-
-  const int nvt = ve - vb;
-  const TaskColumns cols = load_columns(m, vb, nvt, lane);
-  clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
-  wave_sync();
-
-  // ---- bed friction on the lower face of the bottom layer: rows of v's level-0 node, added
-  // to the level-0 windows before the layer loop ----------------------------------------------
-  if (act) {
-    double bx_[NV], by_[NV], bb_[NV], bH_[NV], bs_[NV], be[NV], zb[NV], ub[NV], vb_[NV];
-    load_geo(bx_, by_, bb_, bH_, bs_);
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      be[i] = m.sb[vid[i]].y;
-      zb[i] = bb_[i] + m.sigma[0] * bH_[i];
-      const double2 a0 = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[i]) * (L + 1)));
-      ub[i] = a0.x; vb_[i] = a0.y;
-    }
-    double Rf0 = 0, Rf1 = 0;
-    AT Jf[NV];
-#pragma unroll
-    for (int j = 0; j < NV; ++j) Jf[j] = AT(0);
-#pragma unroll
-    for (int r = 0; r < NQB; ++r) {
-      double txx = 0, txy = 0, txz = 0, tyx = 0, tyy = 0, tyz = 0, br = 0, ur = 0, vr = 0;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const double dx = Q.bdlx[r][i], dy = Q.bdly[r][i], lm = Q.blam[r][i];
-        txx += bx_[i] * dx; txy += by_[i] * dx; txz += zb[i] * dx;
-        tyx += bx_[i] * dy; tyy += by_[i] * dy; tyz += zb[i] * dy;
-        br += be[i] * lm; ur += ub[i] * lm; vr += vb_[i] * lm;
-      }
-      const double nx = txy * tyz - txz * tyy, ny = txz * tyx - txx * tyz, nz = txx * tyy - txy * tyx;
-      const double wb = Q.bw[r] * sqrt(nx * nx + ny * ny + nz * nz) * br;
-      const double la = ROT ? Q.blam[r][0] : sel4(al, Q.blam[r][0], Q.blam[r][1], Q.blam[r][2], Q.blam[r][NV - 1]);
-      Rf0 += wb * ur * la;
-      Rf1 += wb * vr * la;
-#pragma unroll
-      for (int j = 0; j < NV; ++j) Jf[j] += AT(wb * la * Q.blam[r][j]);
-    }
-    const int rl0 = 2 * (v - vb);
-    lds_add(Rw + rl0, Rf0);
-    lds_add(Rw + rl0 + 1, Rf1);
-    if constexpr (JAC) {
-      // row (v, 0, c), column (corner j, level 0, component c)
-      const int nl0 = nlev(0, L);
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int j = 0; j < NV; ++j)
-          lds_add(Jw + soff + c * 2 * nl0 * Dv + int((irank >> (8 * j)) & 255u) * 2 * nl0 + c, double(Jf[j]));
-    }
-  }
-
-  // FP32 tangents: the upper row's entries at the upper level of layer k are kept in
-  // registers and added together with layer k + 1's lower-row entries at the same places,
-  // a quarter fewer LDS adds.  The FP64 kernel has no registers to spare for them (spills
-  // made it slower); on prisms it carries the four of the item's own vertex (corner 0),
-  // which every item of a vertex adds to the same window places, in a per-lane LDS slot
-  // after the residual windows (registers spilled them to scratch every layer).
-  constexpr bool CARRY = JAC && sizeof(JT) == 4;
-  constexpr bool CARRY0 = JAC && ROT && !CARRY;
-  AT carry[2][2][NV];
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int d = 0; d < 2; ++d)
-#pragma unroll
-      for (int j = 0; j < NV; ++j) carry[c][d][j] = AT(0);
-  double *carry0 = Rw + 4 * size_t(max_tv) + 4 * lane;   // [c][d] of this lane
-
-  for (int k = 0; k < L; ++k) {
-    const int cur = k & 1, nxt = cur ^ 1;
-    uint32_t ipy = lrank, imt = imeta;
-    int vidk[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) vidk[i] = lvid[i];
-    // one statement, so that reloads of spilled operands are issued together
-    asm volatile("" : "+v"(ipy), "+v"(imt), "+v"(vidk[0]), "+v"(vidk[1]), "+v"(vidk[2]));
-    const int al = int(imt >> 26), soff = int(imt & 4095u), Dv = int((imt >> 12) & 255u);
-    const int rloc = 2 * int((imt >> 20) & 63u);
-    // gather levels k and k+1 (repeat loads hit the cache)
-    double zlo[NV], ulo[NV], vlo[NV], dz[NV], du[NV], dv[NV], xr[NV], yr[NV], sv[NV];
-    const double s0 = m.sigma[k], s1 = m.sigma[k + 1];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const double4 g = m.geo[vidk[i]];
-      if constexpr (TET) {   // corner positions relative to the first, and s
-        const double4 g0 = m.geo[vidk[0]];
-        xr[i] = g.x - g0.x;
-        yr[i] = g.y - g0.y;
-        sv[i] = m.sb[vidk[i]].x;
-      }
-      zlo[i] = g.z + s0 * g.w;
-      dz[i] = (g.z + s1 * g.w) - zlo[i];
-      const double2 a0 = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vidk[i]) * (L + 1) + k));
-      const double2 a1 = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vidk[i]) * (L + 1) + k + 1));
-      ulo[i] = a0.x; vlo[i] = a0.y;
-      du[i] = a1.x - a0.x;
-      dv[i] = a1.y - a0.y;
-    }
-    // wedges: x/y slopes of z, u, v at fixed zeta are (level-k sum) + zeta (increment sum)
-    double HS[12];
-    if constexpr (!TET) {
-#pragma unroll
-      for (int h = 0; h < 12; ++h) HS[h] = 0.0;
-#pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        HS[0] = fma(lxc[i], zlo[i], HS[0]); HS[1] = fma(lxc[i], dz[i], HS[1]);
-        HS[2] = fma(lyc[i], zlo[i], HS[2]); HS[3] = fma(lyc[i], dz[i], HS[3]);
-        HS[4] = fma(lxc[i], ulo[i], HS[4]); HS[5] = fma(lxc[i], du[i], HS[5]);
-        HS[6] = fma(lyc[i], ulo[i], HS[6]); HS[7] = fma(lyc[i], du[i], HS[7]);
-        HS[8] = fma(lxc[i], vlo[i], HS[8]); HS[9] = fma(lxc[i], dv[i], HS[9]);
-        HS[10] = fma(lyc[i], vlo[i], HS[10]); HS[11] = fma(lyc[i], dv[i], HS[11]);
-      }
-    }
-
-    // residual rows of v's lower (index 0) and upper (index 1) node, and their tangents:
-    // Jx[a][c][d][j][lev] = d R_(a,c) / d U_(node (j, lev), d)
-    double Rb0 = 0, Rb1 = 0, Rt0 = 0, Rt1 = 0;
-    AT Jx[2][2][2][NV][2];
-    if constexpr (JAC) {
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int d = 0; d < 2; ++d)
-#pragma unroll
-            for (int j = 0; j < NV; ++j) { Jx[a][c][d][j][0] = AT(0); Jx[a][c][d][j][1] = AT(0); }
-    }
-
-    AT FA[2][4][2], FH[2][4][2], FB[2][4][3];
-    if constexpr (TET) {
-      tet_layer<AT, JAC, N3>(m, al, picard, xr, yr, zlo, dz, ulo, du, vlo, dv, sv, Rb0, Rb1, Rt0, Rt1, Jx);
-    } else {
-      // Wedges.  The residual-only kernel runs the same loop without the tangents, so
-      // both kernels produce the same residual bits.  The tangents are accumulated in
-      // factorised form.  Every tangent
-      // entry is sum_q L_q . b_q, where L_q (3 numbers per row node a and component pair
-      // cd) depends on the row only and b_q is the column node's gradient.  For a wedge
-      // column j, b = l0 h_j - lam_j p at the lower level and l1 h_j + lam_j p at the
-      // upper one, with h_j = (dN_j/dx, dN_j/dy, 0) constant over the cell and
-      // p = (d zeta/dx, d zeta/dy, d zeta/dz) the same for all j.  So it suffices to sum
-      // l0 L and L (x, y parts) over all points, and L . p per triangle point; the six
-      // column blocks are formed after the loop.
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int cd = 0; cd < 4; ++cd) {
-          FA[a][cd][0] = FA[a][cd][1] = AT(0);
-          FH[a][cd][0] = FH[a][cd][1] = AT(0);
-          FB[a][cd][0] = FB[a][cd][1] = FB[a][cd][2] = AT(0);
-        }
-#pragma unroll
-      for (int tp = 0; tp < 3; ++tp) {
-        // the two points above triangle point tp share lam, z_zeta and the u, v increments
-        double zze = 0, dum = 0, dvm = 0;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-          const double li = Q.lam[tp][i];
-          zze = fma(li, dz[i], zze);
-          dum = fma(li, du[i], dum);
-          dvm = fma(li, dv[i], dvm);
-        }
-        const double iz = rcp64(zze);
-        const double lam_a = ROT ? Q.lam[tp][0] : sel4(al, Q.lam[tp][0], Q.lam[tp][1], Q.lam[tp][2], 0.0);
-        const double uz = iz * dum, vz = iz * dvm;
-#pragma unroll 1
-        for (int zi = 0; zi < 2; ++zi) {
-          const int q = tp + 3 * zi;
-          const double zeta = Q.zeta[q], l0 = 1.0 - zeta, l1 = zeta;
-          const double zxs = fma(zeta, HS[1], HS[0]), zys = fma(zeta, HS[3], HS[2]);
-          const double ucx = fma(zeta, HS[5], HS[4]), ucy = fma(zeta, HS[7], HS[6]);
-          const double vcx = fma(zeta, HS[9], HS[8]), vcy = fma(zeta, HS[11], HS[10]);
-          const double px = -zxs * iz, py = -zys * iz;        // d zeta / dx, d zeta / dy
-          const double W = Q.w[q] * detc * zze;
-          const double ux = ucx + px * dum, uy = ucy + py * dum;
-          const double vx = vcx + px * dvm, vy = vcy + py * dvm;
-          const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = 0.5 * uz, eyz = 0.5 * vz;
-          const double qq = exx * exx + eyy * eyy + exx * eyy + exy * exy + exz * exz + eyz * eyz;
-          const double qe = qq + m.eps0_sq;
-          double mu;
-          if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
-          else mu = m.visc_pref * powq(qe, m.visc_exp);
-          const double s2 = 2.0 * mu * W;
-          const double t2 = picard ? 0.0 : 2.0 * (m.visc_exp * mu * rcp64(qe)) * W;
-          const double e1x = 2.0 * exx + eyy, e1y = exy, e1z = exz;
-          const double e2x = exy, e2y = exx + 2.0 * eyy, e2z = eyz;
-          const double gvx = W * m.rho_g * sxc, gvy = W * m.rho_g * syc;
-          const double abx = l0 * lx_al - lam_a * px, aby = l0 * ly_al - lam_a * py, abz = -lam_a * iz;
-          const double atx = l1 * lx_al + lam_a * px, aty = l1 * ly_al + lam_a * py, atz = lam_a * iz;
-          const double gb0 = e1x * abx + e1y * aby + e1z * abz, gb1 = e2x * abx + e2y * aby + e2z * abz;
-          const double gt0 = e1x * atx + e1y * aty + e1z * atz, gt1 = e2x * atx + e2y * aty + e2z * atz;
-          const double nb = lam_a * l0, nt = lam_a * l1;
-          Rb0 = fma(s2, gb0, fma(gvx, nb, Rb0));
-          Rb1 = fma(s2, gb1, fma(gvy, nb, Rb1));
-          Rt0 = fma(s2, gt0, fma(gvx, nt, Rt0));
-          Rt1 = fma(s2, gt1, fma(gvy, nt, Rt1));
-          if constexpr (!JAC) continue;
-          const AT l0a = AT(l0), pxa = AT(px), pya = AT(py), iza = AT(iz);
-          const AT e1xa = AT(e1x), e1ya = AT(e1y), e1za = AT(e1z);
-          const AT e2xa = AT(e2x), e2ya = AT(e2y), e2za = AT(e2z);
-#pragma unroll
-          for (int a = 0; a < 2; ++a) {
-            const AT Ax = AT(s2 * (a ? atx : abx)), Ay = AT(s2 * (a ? aty : aby)), Az = AT(s2 * (a ? atz : abz));
-            const AT T0 = AT(t2 * (a ? gt0 : gb0)), T1 = AT(t2 * (a ? gt1 : gb1));
-            const AT hAx = AT(0.5) * Ax, hAy = AT(0.5) * Ay, hAz = AT(0.5) * Az;
-            // L for uu, uv, vu, vv: coefficients of (bx, by, bz) in d R_(a,c) / d U_(b,d)
-            const AT Lx[4] = {fma(T0, e1xa, Ax + Ax), fma(T0, e2xa, hAy), fma(T1, e1xa, Ay), fma(T1, e2xa, hAx)};
-            const AT Ly[4] = {fma(T0, e1ya, hAy), fma(T0, e2ya, Ax), fma(T1, e1ya, hAx), fma(T1, e2ya, Ay + Ay)};
-            const AT Lz[4] = {fma(T0, e1za, hAz), T0 * e2za, T1 * e1za, fma(T1, e2za, hAz)};
-#pragma unroll
-            for (int cd = 0; cd < 4; ++cd) {
-              FA[a][cd][0] = fma(l0a, Lx[cd], FA[a][cd][0]);
-              FA[a][cd][1] = fma(l0a, Ly[cd], FA[a][cd][1]);
-              FH[a][cd][0] += Lx[cd];
-              FH[a][cd][1] += Ly[cd];
-              FB[a][cd][tp] = fma(Lx[cd], pxa, fma(Ly[cd], pya, fma(Lz[cd], iza, FB[a][cd][tp])));
-            }
-          }
-        }
-      }
-    }
-
-    // The window adds run at wave priority 1 and the copy-out at 2 (below): the other wave's
-    // quadrature work then fills the LDS queue's gaps (about -1% each; priority for the adds
-    // above the copy-out's, or for the quadrature loop, was slower).
-    __builtin_amdgcn_s_setprio(1);
-    // ---- add v's rows into the level windows ------------------------------------------------
-    // (tetrahedra: every lane adds, lanes without an item add zeros to in-range entries; the
-    // register allocator placed spills of live values inside the branch on `act` there)
-    if (act || TET) {
-      double *Rcur = Rw + cur * 2 * max_tv, *Rnxt = Rw + nxt * 2 * max_tv;
-      lds_add(Rcur + rloc, Rb0);
-      lds_add(Rcur + rloc + 1, Rb1);
-      lds_add(Rnxt + rloc, Rt0);
-      lds_add(Rnxt + rloc + 1, Rt1);
-      if constexpr (JAC) {
-        int rk[NV];
-#pragma unroll
-        for (int i = 0; i < NV; ++i) rk[i] = int((ipy >> (8 * i)) & 255u);
-        const int nlk = nlev(k, L), nl1 = nlev(k + 1, L);
-        const int offk = k > 0 ? 1 : 0;     // level k sits at window position 1 unless k = 0
-        double *Wk = Jw + cur * max_slot + soff, *Wk1 = Jw + nxt * max_slot + soff;
-        // each (row node, component pair)'s column blocks are added as soon as they are formed
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int cd = 0; cd < 4; ++cd) {
-            const int c = cd >> 1, d = cd & 1;
-            if constexpr (!TET) {
-              const AT Ux = FH[a][cd][0] - FA[a][cd][0], Uy = FH[a][cd][1] - FA[a][cd][1];
-#pragma unroll
-              for (int j = 0; j < NV; ++j) {
-                const AT lam = fma(AT(Q.lam[0][j]), FB[a][cd][0],
-                                   fma(AT(Q.lam[1][j]), FB[a][cd][1], AT(Q.lam[2][j]) * FB[a][cd][2]));
-                const AT hx = AT(lxc[j]), hy = AT(lyc[j]);
-                Jx[a][c][d][j][0] = fma(hx, FA[a][cd][0], fma(hy, FA[a][cd][1], -lam));
-                Jx[a][c][d][j][1] = fma(hx, Ux, fma(hy, Uy, lam));
-              }
-            }
-#pragma unroll
-            for (int j = 0; j < NV; ++j)
-#pragma unroll
-              for (int lev = 0; lev < 2; ++lev) {
-                if (a == 0) {
-                  AT lo = Jx[0][c][d][j][lev];
-                  if (CARRY && lev == 0) lo += carry[c][d][j];
-                  if (CARRY0 && lev == 0 && j == 0 && k > 0) lo += carry0[2 * c + d];
-                  lds_add(Wk + c * 2 * nlk * Dv + rk[j] * 2 * nlk + 2 * (lev + offk) + d, double(lo));
-                } else if (CARRY && lev == 1 && k + 1 < L) {
-                  carry[c][d][j] = Jx[1][c][d][j][1];
-                } else if (CARRY0 && lev == 1 && j == 0 && k + 1 < L) {
-                  carry0[2 * c + d] = double(Jx[1][c][d][0][1]);
-                } else {
-                  lds_add(Wk1 + c * 2 * nl1 * Dv + rk[j] * 2 * nl1 + 2 * lev + d, double(Jx[1][c][d][j][lev]));
-                }
-              }
-          }
-      }
-    }
-    wave_sync();
-
-    // ---- level k is complete: copy it to its CSR rows and clear it for level k+2 ------------
-    // The copy-out runs at raised wave priority: its LDS reads and streaming stores then issue
-    // ahead of the other wave's quadrature work instead of queuing behind it (FP64 R+J -2%,
-    // FP32 -2.5%; raising the gather instead was slower).
-    __builtin_amdgcn_s_setprio(2);
-    copy_out<JAC>(cols, k, cur, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    wave_sync();
-    __builtin_amdgcn_s_setprio(0);
-
-  }
-}
-
 // Value of lane (lane ^ X), X = 1 or 2
 __device__ __forceinline__ int quad_xor_i(int v, bool two) {
   return two ? __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true) : __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
@@ -869,7 +314,7 @@ __device__ __forceinline__ float quad_xor(float v) {
 // 670 -> 528 us with FP32 values, residual 180 -> 173 us, against one lane per item.  The parts:
 // the split itself, with the constants in LDS, -7%; items of one vertex spread over the wave
 // (below) -5%; sigma through scalar loads and the wait before the copy-out -2%; the copy-out of a
-// level in one piece -6%.
+// level in one piece -6%.  Carrying the shared entries in FP64 too spills (+5%).
 constexpr int PRISM_WAVES = 2;
 constexpr int PRISM_CONST = 18;         // FP64 constants of an item (144 bytes: its 16-byte reads spread over all banks)
 constexpr int PRISM_ITEMS = WAVE / 2;   // items per pass of a wave
@@ -898,7 +343,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
   const int vb = task.y, ve = task.z, ib = task.w, ie = m.vc_ptr[ve];
   const int L = m.L, nvt = ve - vb;
   const TaskColumns cols = load_columns(m, vb, nvt, lane);
-  const FlatCopy flat = flat_copy<JAC>(m, cols, vb, nvt, lane);
+  const FlatCopy<4> flat = flat_copy<JAC, 4>(m, cols, vb, nvt, lane);
   clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
   const double zeta = z ? G2 : G1;
 
@@ -1229,7 +674,7 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
 #pragma unroll
     for (int j = 0; j < 4; ++j) lam[j] = b1 ? la[(j + 2) & 3] : la[j];
   }
-  const FlatCopy flat = flat_copy<JAC>(m, cols, vb, nvt, lane);
+  const FlatCopy<4> flat = flat_copy<JAC, 4>(m, cols, vb, nvt, lane);
   clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
 
   // item constants: corner ids, gradients at the lane's point, weight x determinant x thickness,
@@ -1490,12 +935,284 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
   }
 }
 
-template <bool JAC, class JT, bool N3, bool TET>
-__global__ __launch_bounds__(WAVE, 2) void owner_kernel(MeshView m, const int4 *__restrict__ tasks,
-                                                        const double *__restrict__ U, double *__restrict__ R,
-                                                        JT *__restrict__ J, int picard, int max_slot, int max_tv) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  owner_task<JAC, JT, N3, TET>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, smem);
+// ---- tetrahedra --------------------------------------------------------------------------
+// Each layer of a base triangle's prism is split into three tetrahedra by the global order of its
+// corners (taken sorted, so corner r has the r-th smallest vertex id): (0,1,2,0'), (1,2,0',1'),
+// (2,0',1',2'), primes one level up.  Linear basis: gradients, strain rate and viscosity are
+// constant on a tetrahedron, so every integral is exact (V times the integrand, int phi_a = V/4).
+//
+// Tetrahedron q holds the vertical edge of column q and one node of each other column j: its lower
+// one for j > q, its upper one for j < q.  With lam_j the barycentric coordinates of the base
+// triangle, h_j their gradients, and z = Pi_q(x, y) the plane through the nodes but q's upper
+// one, the upper node of q has the basis (z - Pi_q) / dz_q, of gradient P_q = (-grad Pi_q, 1) / dz_q,
+// the lower one lam_q minus that, and the others lam_j.  So a column's entries are those of a
+// prism with one point per tetrahedron: h_j . L, and -+ P_q . L for j = q, and the slopes of u, v
+// and z on the planes follow from one tetrahedron to the next by adding h_q times column q's rise.
+//
+// One lane per item.  Row node (r, lower) lies in tetrahedra q <= r, (r, upper) in q >= r; r
+// varies by lane, so both rows are formed on all three tetrahedra with weights 0 and 1.  The
+// physics of the three stays in registers while one row node and component pair after the other
+// is formed and added, without accumulators.  With a Jacobian it is bound by the LDS adds (82% of
+// the kernel's time before the structural zeros were left out).  Ice sheet of 7.5M tetrahedra,
+// FP64 R+J: 715 us with each tetrahedron's gradients from cross products into 48 accumulators,
+// 469 us with the planes, 439 us without adding structural zeros, 413 us with tasks that let
+// eight waves share a compute unit's LDS.
+constexpr int TET_WAVES = 2;
+constexpr int TET_CONST = 10;      // FP64 constants of an item in LDS
+
+template <bool JAC, class JT, bool N3>
+__device__ __forceinline__ void tet_task(const MeshView &m, const int4 task, const double *__restrict__ U,
+                                         double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
+                                         int max_tv, int kb, int ke, unsigned char *smem) {
+  using AT = JT;   // derivative arithmetic type
+  double *Jw = reinterpret_cast<double *>(smem);                                               // [2][max_slot]
+  double *Rw = reinterpret_cast<double *>(smem + (JAC ? 2 * size_t(max_slot) * sizeof(double) : 0));  // [2][2 max_tv]
+  // item constants in LDS (in registers they spill), [constant][lane]: slopes of bed and H, H at the
+  // corners, 2/3 visc_pref x base area, gravity's x and y scale
+  enum { BED = 0, THK = 2, HC = 4, VISC = 7, GRAV = 8 };
+  double *const c_ = Rw + 4 * size_t(max_tv) + threadIdx.x;
+  const double tfac = picard ? 0.0 : m.visc_exp;
+  const ScalarTable sigma = scalar_table(m.sigma);
+  const int lane = threadIdx.x, slot = 4 * (lane & 15) + (lane >> 4);   // as for prisms
+  const int vb = task.y, ve = task.z, ib = task.w, ie = m.vc_ptr[ve];
+  const int L = m.L, nvt = ve - vb;
+  const TaskColumns cols = load_columns(m, vb, nvt, lane);
+  const FlatCopy<8> flat = flat_copy<JAC, 8>(m, cols, vb, nvt, lane);
+  clear_windows<JAC>(m, Jw, Rw, vb, ve, max_slot, max_tv, lane);
+
+  // item constants, corners sorted by vertex id
+  const bool act = ib + slot < ie;
+  const int item = act ? ib + slot : ib;
+  const int v = m.item_vtx[item], t = m.vc_idx[item];
+  int Dv = m.deg[v], soff = m.slot_off[v], rloc = 2 * (v - vb);
+  int vid[3];
+  uint32_t rk = 0u;
+  int own;
+  {
+    int c[3];
+    const uint32_t ranks = m.item_rank[item];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) c[i] = m.cells[3 * int64_t(t) + i];
+    int at[3];    // sorted position of each corner
+#pragma unroll
+    for (int i = 0; i < 3; ++i) at[i] = int(c[i] > c[(i + 1) % 3]) + int(c[i] > c[(i + 2) % 3]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      vid[r] = at[0] == r ? c[0] : at[1] == r ? c[1] : c[2];
+      const uint32_t b = at[0] == r ? ranks : at[1] == r ? ranks >> 8 : ranks >> 16;
+      rk |= (b & 255u) << (8 * r);
+    }
+    const int al = m.vc_pos[item];
+    own = al == 0 ? at[0] : al == 1 ? at[1] : at[2];
+  }
+  double lx[3], ly[3], hx, hy;
+  // 0/1 weights: the own corner lies at or above q (a_q: lower row), below q (1 - a_q for q > 0: upper row)
+  const double a1 = own >= 1 ? 1.0 : 0.0, a2 = own >= 2 ? 1.0 : 0.0;
+  {
+    double4 g[3];
+    double sx = 0, sy = 0, Bx = 0, By = 0, Hx = 0, Hy = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) g[i] = m.geo[vid[i]];
+    const double x_xi = g[1].x - g[0].x, x_eta = g[2].x - g[0].x;
+    const double y_xi = g[1].y - g[0].y, y_eta = g[2].y - g[0].y;
+    const double det = x_xi * y_eta - x_eta * y_xi;      // either sign: the sorted corners may run clockwise
+    const double iG = rcp64(det);
+    lx[1] = y_eta * iG; lx[2] = -y_xi * iG; lx[0] = -(lx[1] + lx[2]);
+    ly[1] = -x_eta * iG; ly[2] = x_xi * iG; ly[0] = -(ly[1] + ly[2]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const double s = m.sb[vid[i]].x;
+      sx = fma(s, lx[i], sx); sy = fma(s, ly[i], sy);
+      Bx = fma(g[i].z, lx[i], Bx); By = fma(g[i].z, ly[i], By);
+      Hx = fma(g[i].w, lx[i], Hx); Hy = fma(g[i].w, ly[i], Hy);
+      c_[(HC + i) * WAVE] = g[i].w;
+    }
+    const double area2 = fabs(det), grav = m.rho_g * area2 * (1.0 / 24.0);
+    c_[BED * WAVE] = Bx; c_[(BED + 1) * WAVE] = By;
+    c_[THK * WAVE] = Hx; c_[(THK + 1) * WAVE] = Hy;
+    c_[VISC * WAVE] = area2 * (1.0 / 3.0) * m.visc_pref;
+    c_[GRAV * WAVE] = grav * sx; c_[(GRAV + 1) * WAVE] = grav * sy;
+    hx = own == 0 ? lx[0] : own == 1 ? lx[1] : lx[2];
+    hy = own == 0 ? ly[0] : own == 1 ? ly[1] : ly[2];
+  }
+  auto gather = [&](int lev, double2 (&a)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      a[i] = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[i]) * (L + 1) + lev));
+  };
+  wave_sync();
+
+  const int k0 = kb > 0 ? kb - 1 : 0;
+  double2 lo[3], up[3];                       // u, v of the corners on levels k and k + 1
+  // ---- bed friction on the lower face of the bottom layer: rows of the level-0 nodes -----------
+  if (kb == 0) {
+    gather(0, lo);
+    const double bx = fma(sigma[0], c_[THK * WAVE], c_[BED * WAVE]);
+    const double by = fma(sigma[0], c_[(THK + 1) * WAVE], c_[(BED + 1) * WAVE]);
+    const double area = fabs(rcp64(lx[1] * ly[2] - lx[2] * ly[1])) * sqrt(fma(bx, bx, fma(by, by, 1.0)));
+    double be[3], Rf0 = 0.0, Rf1 = 0.0, Jf[3] = {0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) be[i] = m.sb[vid[i]].y;
+    const double bm = (be[0] + be[1] + be[2]) * (1.0 / 6.0);
+    const double um = (lo[0].x + lo[1].x + lo[2].x) * (1.0 / 6.0), vm = (lo[0].y + lo[1].y + lo[2].y) * (1.0 / 6.0);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {     // point r: 2/3 of corner r and 1/6 of the others
+      const double w = area * (1.0 / 6.0) * fma(0.5, be[r], bm) * (r == own ? 2.0 / 3.0 : 1.0 / 6.0);
+      Rf0 = fma(w, fma(0.5, lo[r].x, um), Rf0);
+      Rf1 = fma(w, fma(0.5, lo[r].y, vm), Rf1);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) Jf[j] = fma(w, r == j ? 2.0 / 3.0 : 1.0 / 6.0, Jf[j]);
+    }
+    if (act) {
+      lds_add(Rw + rloc, Rf0);
+      lds_add(Rw + rloc + 1, Rf1);
+      if constexpr (JAC) {
+        const int nl0 = nlev(0, L);
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            lds_add(Jw + soff + c * 2 * nl0 * Dv + int((rk >> (8 * j)) & 255u) * 2 * nl0 + c, double(AT(Jf[j])));
+      }
+    }
+  }
+  constexpr bool AHEAD = N3;      // as for prisms
+  if constexpr (AHEAD) {
+    gather(k0, lo);
+    gather(k0 + 1, up);
+    asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));
+  }
+
+  for (int k = k0; k < ke; ++k) {
+    const int cur = k & 1, nxt = cur ^ 1;
+    const double s0 = sigma[k], ds = sigma[k + 1] - s0;
+    asm volatile("" : "+v"(vid[0]), "+v"(vid[1]), "+v"(vid[2]), "+v"(Dv), "+v"(soff), "+v"(rloc), "+v"(rk));
+    if constexpr (!AHEAD) {
+      gather(k, lo);
+      gather(k + 1, up);
+    }
+    double ux = 0, uy = 0, vx = 0, vy = 0;      // slopes of u and v on the plane of tetrahedron q
+    double zx = fma(s0, c_[THK * WAVE], c_[BED * WAVE]), zy = fma(s0, c_[(THK + 1) * WAVE], c_[(BED + 1) * WAVE]);
+    const double visc = c_[VISC * WAVE] * ds;
+    double dz[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      ux = fma(lx[i], lo[i].x, ux); uy = fma(ly[i], lo[i].x, uy);
+      vx = fma(lx[i], lo[i].y, vx); vy = fma(ly[i], lo[i].y, vy);
+    }
+    // the physics of the three tetrahedra
+    double s2[3], t2[3], E1x[3], Exy[3], E2y[3], Exz[3], Eyz[3], Px[3], Py[3], Pz[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double du = up[q].x - lo[q].x, dv = up[q].y - lo[q].y, Hq = c_[(HC + q) * WAVE];
+      dz[q] = ds * Hq;
+      Pz[q] = rcp64(dz[q]);
+      Px[q] = -zx * Pz[q];
+      Py[q] = -zy * Pz[q];
+      const double exx = fma(Px[q], du, ux), eyy = fma(Py[q], dv, vy);
+      const double exy = 0.5 * (fma(Py[q], du, uy) + fma(Px[q], dv, vx));
+      const double exz = 0.5 * (Pz[q] * du), eyz = 0.5 * (Pz[q] * dv);
+      const double qe = fma(exx, exx, fma(eyy, exx + eyy, fma(exy, exy, fma(exz, exz, fma(eyz, eyz, m.eps0_sq)))));
+      const double W = visc * Hq;     // 2 visc_pref V
+      if constexpr (N3) {      // mu is q^(-1/3) and 1/q its cube
+        const double y = rcbrt64(qe);
+        s2[q] = y * W;
+        t2[q] = (s2[q] * tfac) * (y * y * y);
+      } else {
+        s2[q] = powq(qe, m.visc_exp) * W;
+        t2[q] = (s2[q] * tfac) * rcp64(qe);
+      }
+      E1x[q] = 2.0 * exx + eyy; Exy[q] = exy; E2y[q] = exx + 2.0 * eyy; Exz[q] = exz; Eyz[q] = eyz;
+      if (q < 2) {      // on to the next plane: column q's node moves up
+        ux = fma(lx[q], du, ux); uy = fma(ly[q], du, uy);
+        vx = fma(lx[q], dv, vx); vy = fma(ly[q], dv, vy);
+        zx = fma(lx[q], dz[q], zx); zy = fma(ly[q], dz[q], zy);
+      }
+      lo[q] = up[q];
+    }
+    if (AHEAD && k + 1 < ke) gather(k + 2, up);
+    __builtin_amdgcn_s_setprio(1);
+    const int r0 = int(rk & 255u), r1 = int((rk >> 8) & 255u), r2 = int((rk >> 16) & 255u);
+    const double in[2][3] = {{1.0, a1, a2}, {0.0, 1.0 - a1, 1.0 - a2}};       // row node's own gradient h
+    const double rows[2] = {dz[0] + a1 * dz[1] + a2 * dz[2], (1.0 - a1) * dz[0] + (1.0 - a2) * dz[1] + dz[2]};
+    const double apex[3] = {1.0 - a1, a1 - a2, a2};                          // and -+ P on its vertical edge
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      double Ra0 = rows[a] * c_[GRAV * WAVE], Ra1 = rows[a] * c_[(GRAV + 1) * WAVE];
+      AT A[3][3], T[3][2];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const double w = a ? apex[q] : -apex[q];
+        const double ax = fma(w, Px[q], in[a][q] * hx), ay = fma(w, Py[q], in[a][q] * hy), az = w * Pz[q];
+        const double g0 = E1x[q] * ax + Exy[q] * ay + Exz[q] * az, g1 = Exy[q] * ax + E2y[q] * ay + Eyz[q] * az;
+        Ra0 = fma(s2[q], g0, Ra0);
+        Ra1 = fma(s2[q], g1, Ra1);
+        if constexpr (JAC) {
+          A[q][0] = AT(s2[q] * ax); A[q][1] = AT(s2[q] * ay); A[q][2] = AT(s2[q] * az);
+          T[q][0] = AT(t2[q] * g0); T[q][1] = AT(t2[q] * g1);
+        }
+      }
+      if (act) {
+        double *r = Rw + (a ? nxt : cur) * 2 * max_tv + rloc;
+        lds_add(r, Ra0);
+        lds_add(r + 1, Ra1);
+      }
+      if constexpr (JAC) {
+        const AT half = AT(0.5);
+        const int nl = a ? nlev(k + 1, L) : nlev(k, L);
+        // level k sits at window position 1 unless k = 0
+        double *w = Jw + (a ? nxt : cur) * max_slot + soff + (!a && k > 0 ? 2 : 0);
+        double *w0 = w + r0 * 2 * nl, *w1 = w + r1 * 2 * nl, *w2 = w + r2 * 2 * nl;
+#pragma unroll
+        for (int cd = 0; cd < 4; ++cd) {
+          const int c = cd >> 1, d = cd & 1;
+          AT Lx[3], Ly[3], B[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            const AT Ax = A[q][0], Ay = A[q][1], Az = A[q][2], Tc = T[q][c];
+            // coefficients of (bx, by, bz) in d R_(a,c) / d U_(b,d)
+            const AT ex = AT(d ? Exy[q] : E1x[q]), ey = AT(d ? E2y[q] : Exy[q]), ez = AT(d ? Eyz[q] : Exz[q]);
+            AT Lz;
+            if (cd == 0) { Lx[q] = fma(Tc, ex, Ax + Ax); Ly[q] = fma(Tc, ey, half * Ay); Lz = fma(Tc, ez, half * Az); }
+            else if (cd == 1) { Lx[q] = fma(Tc, ex, half * Ay); Ly[q] = fma(Tc, ey, Ax); Lz = Tc * ez; }
+            else if (cd == 2) { Lx[q] = fma(Tc, ex, Ay); Ly[q] = fma(Tc, ey, half * Ax); Lz = Tc * ez; }
+            else { Lx[q] = fma(Tc, ex, half * Ax); Ly[q] = fma(Tc, ey, Ay + Ay); Lz = fma(Tc, ez, half * Az); }
+            B[q] = fma(Lx[q], AT(Px[q]), fma(Ly[q], AT(Py[q]), Lz * AT(Pz[q])));
+          }
+          // column j's lower node lies in tetrahedra q <= j, its upper one in q >= j
+          const AT x01 = Lx[0] + Lx[1], y01 = Ly[0] + Ly[1], x12 = Lx[1] + Lx[2], y12 = Ly[1] + Ly[2];
+          const AT l0 = fma(AT(lx[0]), Lx[0], fma(AT(ly[0]), Ly[0], -B[0]));
+          const AT l1 = fma(AT(lx[1]), x01, fma(AT(ly[1]), y01, -B[1]));
+          const AT l2 = fma(AT(lx[2]), x01 + Lx[2], fma(AT(ly[2]), y01 + Ly[2], -B[2]));
+          const AT u0 = fma(AT(lx[0]), x12, fma(AT(ly[0]), y12, B[0]));
+          const AT u1 = fma(AT(lx[1]), Lx[2], fma(AT(ly[1]), Ly[2], B[1]));
+          const AT u2 = B[2];
+          // the lower row shares no tetrahedron with upper nodes above its own corner, the upper row
+          // none with lower nodes below it: those entries stay zero
+          const int off = c * 2 * nl * Dv + d;
+          if (act) {
+            if (a == 0) { lds_add(w0 + off, double(l0)); lds_add(w1 + off, double(l1)); }
+            else { lds_add(w1 + off + 2, double(u1)); lds_add(w2 + off + 2, double(u2)); }
+            lds_add(w0 + off + 2, double(u0));
+            lds_add(w2 + off, double(l2));
+          }
+          if (act && own == (a ? 0 : 2)) lds_add(a ? w0 + off : w2 + off + 2, double(a ? l0 : u2));
+          if (act && (a == 0 ? own >= 1 : own <= 1)) lds_add(a ? w1 + off : w1 + off + 2, double(a ? l1 : u1));
+        }
+      }
+    }
+    if constexpr (AHEAD)
+      asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));
+    wave_sync();
+    __builtin_amdgcn_s_setprio(2);
+    if (k > 0 && (!JAC || flat.slot_size > 0))
+      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    else
+      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    wave_sync();
+    __builtin_amdgcn_s_setprio(0);
+  }
 }
 
 // Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
@@ -1520,6 +1237,16 @@ __global__ __launch_bounds__(WAVE, 2) void hex_owner_kernel(MeshView m, const in
   hex_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
 }
 
+template <bool JAC, class JT, bool N3>
+__global__ __launch_bounds__(WAVE, TET_WAVES) void tet_owner_kernel(MeshView m, const int4 *__restrict__ tasks, int lpc,
+                                                                    const double *__restrict__ U,
+                                                                    double *__restrict__ R, JT *__restrict__ J,
+                                                                    int picard, int max_slot, int max_tv) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
+  tet_task<JAC, JT, N3>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+}
+
 // Persistent ensemble launch: each workgroup repeatedly takes the next (member, task) pair
 // from a device counter until the combined task table is exhausted (every wave exits).
 template <class F>
@@ -1537,13 +1264,14 @@ __device__ __forceinline__ void ensemble_loop(const EnsembleMember *__restrict__
   }
 }
 
-template <bool JAC, class JT, bool N3, bool TET>
-__global__ __launch_bounds__(WAVE, 2) void ensemble_kernel(const EnsembleMember *__restrict__ mem,
-                                                           const int4 *__restrict__ tasks, int n_tasks,
-                                                           int *__restrict__ counter, int picard) {
+template <bool JAC, class JT, bool N3>
+__global__ __launch_bounds__(WAVE, TET_WAVES) void tet_ensemble_kernel(const EnsembleMember *__restrict__ mem,
+                                                                       const int4 *__restrict__ tasks, int n_tasks,
+                                                                       int *__restrict__ counter, int picard) {
   extern __shared__ __align__(16) unsigned char smem[];
   ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
-    owner_task<JAC, JT, N3, TET>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, smem);
+    tet_task<JAC, JT, N3>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0, e.view.L,
+                          smem);
   });
 }
 
@@ -1591,25 +1319,16 @@ __global__ void front_add_kernel(int n_front, int L, const int32_t *__restrict__
   R[2 * int64_t(vtx[f]) * (L + 1) + r] += load[i];
 }
 
-bool g_tables_ready[64] = {};
-
-fo_status ensure_tables(int device) {
-  if (device >= 0 && device < 64 && g_tables_ready[device]) return FO_OK;
-  static constexpr QTable tab = make_table();
-  FO_HIP_TRY(hipMemcpyToSymbol(HIP_SYMBOL(kQ), &tab, sizeof(tab)));
-  if (device >= 0 && device < 64) g_tables_ready[device] = true;
-  return FO_OK;
-}
-
-// Elements by kernel: prisms and their tetrahedra, one lane per item; hexahedra, four.
 enum Cell { PRISM, TETS, HEX };
 
-// Dynamic LDS of one task: the two Jacobian level windows, the two residual windows and, with a
-// Jacobian, the per-lane carry slots (WAVE x 4 FP64) that follow them on prisms.
+// Dynamic LDS of one task: the two Jacobian level windows, the two residual windows and, for
+// prisms and tetrahedra, the item constants.
 template <Cell C>
 size_t window_bytes(bool jac, int max_slot, int max_tv) {
-  return (jac ? 2 * size_t(max_slot) * sizeof(double) + (C != TETS ? 0 : size_t(WAVE) * 4 * sizeof(double)) : 0) +
-         2 * 2 * size_t(max_tv) * sizeof(double) + (C == PRISM ? size_t(PRISM_ITEMS) * PRISM_CONST * sizeof(double) : 0);
+  return (jac ? 2 * size_t(max_slot) * sizeof(double) : 0) + 2 * 2 * size_t(max_tv) * sizeof(double) +
+         (C == PRISM  ? size_t(PRISM_ITEMS) * PRISM_CONST * sizeof(double)
+          : C == TETS ? size_t(WAVE) * TET_CONST * sizeof(double)
+                      : 0);
 }
 
 // Layers per block of a launch with n_tasks tasks of L layers.  A small mesh leaves the chip
@@ -1641,19 +1360,14 @@ fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int k
   const int picard = kind == FO_JAC_PICARD ? 1 : 0;
   fo_status st = profile_begin(mesh, s);
   if (st != FO_OK) return st;
-  if constexpr (C != TETS) {
-    const int lpc = layers_per_block(mesh->n_tasks, m.L, RESIDENT);
-    auto kern = [] {
-      if constexpr (C == HEX) return hex_owner_kernel<JAC, JT, N3, PASSES>;
-      else return prism_owner_kernel<JAC, JT, N3, PASSES>;
-    }();
-    hipLaunchKernelGGL(kern, dim3(unsigned(mesh->n_tasks), unsigned((m.L + lpc - 1) / lpc)),
-                       dim3(WAVE), lds, s, m, mesh->tasks, lpc, U, R, J, picard, mesh->max_slot,
-                       mesh->max_task_verts);
-  } else {
-    hipLaunchKernelGGL((owner_kernel<JAC, JT, N3, C == TETS>), dim3(unsigned(mesh->n_tasks)), dim3(WAVE), lds, s, m,
-                       mesh->tasks, U, R, J, picard, mesh->max_slot, mesh->max_task_verts);
-  }
+  const int lpc = layers_per_block(mesh->n_tasks, m.L, RESIDENT);
+  auto kern = [] {
+    if constexpr (C == HEX) return hex_owner_kernel<JAC, JT, N3, PASSES>;
+    else if constexpr (C == PRISM) return prism_owner_kernel<JAC, JT, N3, PASSES>;
+    else return tet_owner_kernel<JAC, JT, N3>;
+  }();
+  hipLaunchKernelGGL(kern, dim3(unsigned(mesh->n_tasks), unsigned((m.L + lpc - 1) / lpc)), dim3(WAVE), lds, s, m,
+                     mesh->tasks, lpc, U, R, J, picard, mesh->max_slot, mesh->max_task_verts);
   FO_LAUNCH_CHECK("owner_kernel");
   return profile_end(mesh, s);
 }
@@ -1664,7 +1378,7 @@ fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
   auto kern = [] {
     if constexpr (C == HEX) return hex_ensemble_kernel<JAC, JT, N3, PASSES>;
     else if constexpr (C == PRISM) return prism_ensemble_kernel<JAC, JT, N3, PASSES>;
-    else return ensemble_kernel<JAC, JT, N3, C == TETS>;
+    else return tet_ensemble_kernel<JAC, JT, N3>;
   }();
   int per_cu = 0;
   FO_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WAVE, lds));
@@ -1714,8 +1428,6 @@ fo_status launch_front_add(const MeshView &m, int32_t n_front, const int32_t *vt
 }
 
 fo_status launch_ensemble(const EnsembleLaunch &E, int dtype, int kind, bool want_jac, hipStream_t s) {
-  fo_status st = ensure_tables(E.device);
-  if (st != FO_OK) return st;
   return by_kernel(E.nv, E.tet, want_jac, dtype, E.all_n3, E.passes, [&](auto c, auto jac, auto val, auto n3, auto ps) {
     return launch_ens_t<c.value, jac.value, decltype(val), n3.value, ps.value>(E, kind, s);
   });
@@ -1750,8 +1462,6 @@ fo_status launch_assemble(const fo_mesh *mesh, const double *U, double *R, void 
 
 fo_status launch_assemble_cells(const fo_mesh *mesh, const double *U, double *R, void *J, int dtype,
                                 int kind, bool want_jac, hipStream_t s) {
-  fo_status st = ensure_tables(mesh->device);
-  if (st != FO_OK) return st;
   const MeshView &m = mesh->view;
   return by_kernel(m.nv, m.tet != 0, want_jac, dtype, m.n_glen == 3.0, mesh->passes,
                    [&](auto c, auto jac, auto val, auto n3, auto ps) {

@@ -224,14 +224,16 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
         rank[(t * nv + a) * nv + b] = uint8_t(it - beg);
       }
     }
-  // wave tasks: runs of consecutive vertex columns with at most 64 items (one lane each)
-  // whose level windows (12 D entries per vertex) fit the per-wave LDS budget
-  // kMaxSlot: two level windows of at most 1080 FP64 entries, the residual windows and the
-  // per-lane carry slots (2 KB) keep a wave's LDS under 20 KB, so that eight waves share a
-  // compute unit.  Hexahedra take four lanes per item and prisms two: 16 and 32 items a wave (a
-  // vertex with more is a task of its own and takes several passes).
+  // wave tasks: runs of consecutive vertex columns, cut where a pass of the wave has no lane left
+  // (a hexahedral item takes four lanes, a prism's two, a base triangle's tetrahedra one; a vertex
+  // with more cells is a task of its own and takes several passes) or where the level windows
+  // (12 D entries per vertex) outgrow what a level is copied out with in one piece (512 entries,
+  // tetrahedra 1024) or a wave's share of LDS when eight share a compute unit (20 KB: two windows
+  // of 900 entries, the residual windows and 5 KB of tetrahedral item constants).  A window of a
+  // single vertex may reach 1080 entries.
   constexpr int kMaxItems = 64, kMaxSlot = 1080;
-  const int task_items = nv == 4 ? kMaxItems / 4 : d->elem == FO_WEDGE6 ? kMaxItems / 2 : kMaxItems;
+  const int task_items = d->elem == FO_HEX8 ? kMaxItems / 4 : d->elem == FO_WEDGE6 ? kMaxItems / 2 : kMaxItems;
+  const int task_slot = d->elem == FO_TET4 ? 900 : 512;
   std::vector<int4> tasks;
   std::vector<int32_t> slot_off(V);
   int32_t max_slot = 0, max_tv = 0;
@@ -248,7 +250,7 @@ extern "C" fo_status fo_mesh_create(const fo_mesh_desc *d, void *stream, fo_mesh
       passes = passes || ni > task_items;
       if (sz > kMaxSlot)
         return fail(FO_EINVAL, "fo_mesh_create: vertex " + std::to_string(v) + " has more than 90 neighbouring vertices");
-      if (v > vb && (items + ni > task_items || slot + sz > kMaxSlot)) {
+      if (v > vb && (items + ni > task_items || slot + sz > task_slot)) {
         tasks.push_back(make_int4(0, vb, v, vc_ptr[vb]));
         max_slot = std::max(max_slot, slot);
         max_tv = std::max(max_tv, v - vb);
