@@ -9,6 +9,7 @@
 // derivative use the unrounded FP32 values.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -572,7 +573,7 @@ LLayout llayout(const fo_mesh *m) {
   L.Us = take(8 * n);
   L.R = take(8 * n);
   L.D = take(8 * 2 * n);
-  L.partial = take(8 * size_t(multidot_blocks(int64_t(n))));
+  L.partial = take(8 * size_t(std::min<int64_t>(std::max<int64_t>((int64_t(n) + 4095) / 4096, 1), 512)));
   L.dots = take(16);
   L.flag = take(16);
   L.total = off;
@@ -595,11 +596,13 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   const LLayout L = llayout(m);
   if (ws_bytes < L.total) return fail(FO_EINVAL, "fo_initial_guess_learned: workspace too small");
   char *w = static_cast<char *>(ws);
-  float *F = reinterpret_cast<float *>(w + L.F), *acts = reinterpret_cast<float *>(w + L.acts);
+  float *F = reinterpret_cast<float *>(w + L.F);
   float *Y = reinterpret_cast<float *>(w + L.Y);
   double *Us = reinterpret_cast<double *>(w + L.Us), *R = reinterpret_cast<double *>(w + L.R);
   double *D0 = reinterpret_cast<double *>(w + L.D);
-  double *part = reinterpret_cast<double *>(w + L.partial), *dots = reinterpret_cast<double *>(w + L.dots);
+  // The dot products' partial sums (up to 512) lie where a training pass keeps its activations, which
+  // inference does not store; the layout's sizes are part of what callers were told and stay.
+  double *part = reinterpret_cast<double *>(w + L.acts), *dots = reinterpret_cast<double *>(w + L.dots);
   int *flag = reinterpret_cast<int *>(w + L.flag);
   const int V = m->view.V;
   const int64_t n = m->view.n_dofs;
@@ -607,7 +610,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   fo_status st;
   if ((st = launch_sia(m, Us, s)) != FO_OK) return st;
   if ((st = fo_column_features(m, norm, F, s)) != FO_OK) return st;
-  if ((st = mlp_forward_impl(P, F, V, acts, Y, s)) != FO_OK) return st;
+  if ((st = mlp_forward_impl(P, F, V, nullptr, Y, s)) != FO_OK) return st;
   if ((st = launch_fill_zero(flag, 16, s)) != FO_OK) return st;
   const unsigned nb = unsigned((n + 255) / 256);
   hipLaunchKernelGGL(correction_kernel, dim3(nb), dim3(256), 0, s, n, Y, D0);
@@ -627,7 +630,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   if (fallback == 1) {
     if ((st = launch_assemble(m, Us, R, nullptr, FO_F64, FO_JAC_NEWTON, false, s)) != FO_OK) return st;
     if (n_residuals) ++*n_residuals;
-    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, s)) != FO_OK) return st;
+    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, s)) != FO_OK) return st;
     FO_HIP_TRY(hipMemcpyAsync(&hv[1], dots, sizeof(double), hipMemcpyDeviceToHost, s));
   }
   FO_HIP_TRY(hipStreamSynchronize(s));
@@ -635,7 +638,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   if (use_nn && fallback == 1) {
     if ((st = launch_assemble(m, U, R, nullptr, FO_F64, FO_JAC_NEWTON, false, s)) != FO_OK) return st;
     if (n_residuals) ++*n_residuals;
-    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, s)) != FO_OK) return st;
+    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, s)) != FO_OK) return st;
     FO_HIP_TRY(hipMemcpyAsync(&hv[0], dots, sizeof(double), hipMemcpyDeviceToHost, s));
     FO_HIP_TRY(hipStreamSynchronize(s));
     use_nn = std::isfinite(hv[0]) && hv[0] <= hv[1];

@@ -50,7 +50,7 @@ Layout layout(const fo_mesh *m, const fo_newton_opts *o) {
   L.V = take(L.V_bytes);
   L.partial = take(8 * std::max(size_t(multidot_blocks(int64_t(n))) * size_t(mres + 2),
                                  2 * size_t(dot2_blocks(int64_t(n)))));
-  L.dots = take(8 * std::max(size_t(mres + 2), size_t(8)));   // GMRES: h and norms; CG: 6 scalars
+  L.dots = take(8 * std::max(size_t(mres + 3), size_t(8)));   // GMRES: h, norms and scale; CG: 6 scalars
   L.total = off;
   return L;
 }
@@ -71,7 +71,7 @@ struct Ctx {
 
 // ||x||_2 with a deterministic device reduction
 fo_status norm2(Ctx &c, const double *x, double &out) {
-  fo_status st = multidot(c.n, nullptr, 0, 0, x, c.dptr(c.L.partial), c.dptr(c.L.dots), c.s);
+  fo_status st = multidot(c.n, nullptr, 0, 0, x, c.dptr(c.L.partial), c.dptr(c.L.dots), 0.0, c.s);
   if (st != FO_OK) return st;
   FO_HIP_TRY(hipMemcpyAsync(c.host, c.dptr(c.L.dots), sizeof(double), hipMemcpyDeviceToHost, c.s));
   FO_HIP_TRY(hipStreamSynchronize(c.s));
@@ -84,6 +84,9 @@ fo_status precondition(Ctx &c, const fo_newton_opts *o, const double *r, double 
   if (o->preconditioner == FO_PREC_MDSC) return fo_mdsc_apply(o->mdsc, r, z, c.s);
   return colblock_apply(c.m, reinterpret_cast<const float *>(c.ws + c.L.fac), r, z, c.s);
 }
+
+// A projection that leaves less than this share of ||w||^2 is repeated (see below)
+constexpr double REORTH = 1e-6;
 
 // GMRES(m), right preconditioned: solve J x = b, x0 = 0.  Returns iterations in `its`.
 fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b, double *x, int64_t &its,
@@ -121,23 +124,25 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
       // eps kappa, and the norm from ||w - V h||^2 = ||w||^2 - ||h||^2 is then good to
       // about eps kappa^2; the second pass runs when kappa > 1e3 (both bounds near 1e-10)
       double hsum[512];
+      // The projected vector goes to V_(j+1), scaled to unit length by the norm formed on the
+      // device (left unscaled where a second pass follows, which works on it in place).
+      double *vn = vj + n;
       for (int pass = 0; pass < 2; ++pass) {
-        if ((st = multidot(n, V, n, j + 1, w, c.dptr(c.L.partial), c.dptr(c.L.dots), c.s)) != FO_OK) return st;
-        if ((st = multiaxpy(n, V, n, j + 1, c.dptr(c.L.dots), w, -1.0, c.s)) != FO_OK) return st;
-        FO_HIP_TRY(hipMemcpyAsync(c.host, c.dptr(c.L.dots), sizeof(double) * (j + 2), hipMemcpyDeviceToHost, c.s));
+        const double *src = pass == 0 ? w : vn;
+        double *dots = c.dptr(c.L.dots);
+        if ((st = multidot(n, V, n, j + 1, src, c.dptr(c.L.partial), dots, pass == 0 ? REORTH : 0.0, c.s)) != FO_OK)
+          return st;
+        if ((st = multiaxpy(n, V, n, j + 1, dots, dots + j + 2, src, vn, -1.0, c.s)) != FO_OK) return st;
+        FO_HIP_TRY(hipMemcpyAsync(c.host, dots, sizeof(double) * (j + 3), hipMemcpyDeviceToHost, c.s));
         FO_HIP_TRY(hipStreamSynchronize(c.s));
         for (int i = 0; i <= j; ++i) hsum[i] = (pass == 0 ? 0.0 : hsum[i]) + c.host[i];
-        double h2 = 0.0;
-        for (int i = 0; i <= j; ++i) h2 += c.host[i] * c.host[i];
-        const double wn2 = c.host[j + 1] - h2;   // ||w||^2 after this projection
-        H[size_t(j + 1) * mres + j] = std::sqrt(wn2 > 0 ? wn2 : 0.0);
-        if (pass == 0 && wn2 > 1e-6 * c.host[j + 1]) break;
+        const double scale = c.host[j + 2];      // 1 / ||w|| after this projection, 0 for a zero vector
+        H[size_t(j + 1) * mres + j] = scale > 0.0 ? 1.0 / scale : scale;
+        if (scale != 1.0) break;                 // 1: left unscaled for the second pass
       }
       for (int i = 0; i <= j; ++i) H[size_t(i) * mres + j] = hsum[i];
       const double hn = H[size_t(j + 1) * mres + j];
       if (!std::isfinite(hn)) return fail(FO_ENONFINITE, "gmres: non-finite Krylov vector");
-      if (hn > 0 && j + 1 <= mres)
-        if ((st = axpby(n, 1.0 / hn, w, 0.0, V + int64_t(j + 1) * n, c.s)) != FO_OK) return st;
       // Givens rotations
       for (int i = 0; i < j; ++i) {
         const double a = H[size_t(i) * mres + j], bb = H[size_t(i + 1) * mres + j];
@@ -170,8 +175,7 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
     }
     std::memcpy(c.host, y.data(), sizeof(double) * k);
     FO_HIP_TRY(hipMemcpyAsync(c.dptr(c.L.dots), c.host, sizeof(double) * k, hipMemcpyHostToDevice, c.s));
-    if ((st = launch_fill_zero(t, sizeof(double) * n, c.s)) != FO_OK) return st;
-    if ((st = multiaxpy(n, V, n, k, c.dptr(c.L.dots), t, 1.0, c.s)) != FO_OK) return st;
+    if ((st = multiaxpy(n, V, n, k, c.dptr(c.L.dots), nullptr, nullptr, t, 1.0, c.s)) != FO_OK) return st;
     if ((st = precondition(c, o, t, z)) != FO_OK) return st;
     if ((st = axpby(n, 1.0, z, 1.0, x, c.s)) != FO_OK) return st;
     if (!done) {

@@ -12,16 +12,18 @@ fo_status colblock_apply(const fo_mesh *mesh, const float *fac, const double *r,
 fo_status colblock_apply_correction(const fo_mesh *mesh, const float *fac, const float *W32, const float *JP,
                                     const double *y, const double *r, double *z, hipStream_t s);
 int multidot_blocks(int64_t n);
-// out[0..nv-1] = V_i . w, out[nv] = w . w (partial: multidot_blocks(n) * (nv + 1) doubles;
-// n and ld even, FO_EINVAL otherwise)
+// out[0..nv-1] = V_i . w, out[nv] = w . w, out[nv + 1] = 1 / ||w - V h|| from the first two (1 if
+// ||w - V h||^2 <= drop ||w||^2 with drop > 0; 0 if it is not positive with drop = 0).  partial:
+// multidot_blocks(n) * (nv + 1) doubles, out: nv + 2; n and ld even, FO_EINVAL otherwise.
 fo_status multidot(int64_t n, const double *V, int64_t ld, int nv, const double *w, double *partial,
-                   double *out, hipStream_t s);
+                   double *out, double drop, hipStream_t s);
 int dot2_blocks(int64_t n);
 // out[0] = a . w, out[1] = w . w (partial: 2 dot2_blocks(n) doubles; n even, FO_EINVAL otherwise)
 fo_status dot2(int64_t n, const double *a, const double *w, double *partial, double *out, hipStream_t s);
-// w += sign * sum_i h_i V_i (n and ld even, FO_EINVAL otherwise)
-fo_status multiaxpy(int64_t n, const double *V, int64_t ld, int nv, const double *h, double *w, double sign,
-                    hipStream_t s);
+// out = scale[0] (w + sign * sum_i h_i V_i), scale NULL for 1, w NULL for 0, out may be w (n and ld
+// even, FO_EINVAL otherwise)
+fo_status multiaxpy(int64_t n, const double *V, int64_t ld, int nv, const double *h, const double *scale,
+                    const double *w, double *out, double sign, hipStream_t s);
 // x += alpha p, r -= alpha q with alpha = num[0] / den[0] read on the device
 fo_status cg_step(int64_t n, const double *num, const double *den, const double *p, const double *q, double *x,
                   double *r, hipStream_t s);

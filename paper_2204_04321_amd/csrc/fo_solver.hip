@@ -18,8 +18,9 @@ namespace {
 __device__ __forceinline__ int nlev(int k, int L) { return (k == 0 || k == L) ? 2 : 3; }
 __device__ __forceinline__ int cumlev(int k) { return k == 0 ? 0 : 3 * k - 1; }
 
-constexpr int SPMV_LANES = 8;   // lanes per node (pair of rows)
-constexpr int APPLY_MAX_COLS = 64;      // columns per preconditioner-apply block
+constexpr int SPMV_LANES = 8;   // lanes per node (pair of rows); a wave per column with its neighbours' x and the
+                                // products in LDS reads the values as one run but is slower (198 -> 214 us)
+constexpr int APPLY_COLS = 64;          // most columns of a preconditioner-apply block
 constexpr int APPLY_THREADS = 256;      // its threads: all stage and copy, one per column sweeps
 
 template <class JT> struct Pair2;
@@ -153,23 +154,22 @@ __global__ __launch_bounds__(128) void colblock_factor_kernel(MeshView m, const 
 }
 
 // Forward then backward block substitution of one vertical line, in place on its 2 (L+1)
-// values zv (r in, z = M^{-1} r out).  The factors are stored level-major with the vertex index
-// fastest, so a wave's loads of one factor field are contiguous.
-__device__ __forceinline__ void column_sweep(const float *__restrict__ fac, int64_t Vl, int L, int64_t v, double *zv) {
-  // forward: y_k = r_k - Lo_k S_{k-1}^{-1} y_{k-1}; keep w_k = S_k^{-1} y_k.  The next
-  // level's factors are loaded one level ahead.
+// values zv (r in, z = M^{-1} r out).  F(f, k) is factor field f of level k; the next level's are
+// taken one level ahead.
+template <class F>
+__device__ __forceinline__ void column_sweep(int L, double *zv, F fac) {
+  // forward: y_k = r_k - Lo_k S_{k-1}^{-1} y_{k-1}; keep w_k = S_k^{-1} y_k
   double f[8], fn[8];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) fn[i] = double(fac[int64_t(i) * Vl + v]);
+  for (int i = 0; i < 8; ++i) fn[i] = double(fac(i, 0));
   double w0 = 0, w1 = 0;
   for (int k = 0; k <= L; ++k) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) f[i] = fn[i];
     double y0 = zv[2 * k], y1 = zv[2 * k + 1];
     if (k < L) {
-      const float *Fn = fac + int64_t(k + 1) * 12 * Vl + v;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) fn[i] = double(Fn[i * Vl]);
+      for (int i = 0; i < 8; ++i) fn[i] = double(fac(i, k + 1));
     }
     if (k > 0) {
       y0 -= f[4] * w0 + f[5] * w1;
@@ -183,18 +183,14 @@ __device__ __forceinline__ void column_sweep(const float *__restrict__ fac, int6
   // backward: z_k = w_k - G_k z_{k+1}, G_k = S_k^{-1} Up_k
   double z0 = zv[2 * L], z1 = zv[2 * L + 1];
   double g[4], gn[4];
-  {
-    const float *Fk = fac + int64_t(L - 1 >= 0 ? L - 1 : 0) * 12 * Vl + v;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) gn[i] = double(Fk[(8 + i) * Vl]);
-  }
+  for (int i = 0; i < 4; ++i) gn[i] = double(fac(8 + i, L - 1 >= 0 ? L - 1 : 0));
   for (int k = L - 1; k >= 0; --k) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) g[i] = gn[i];
     if (k > 0) {
-      const float *Fn = fac + int64_t(k - 1) * 12 * Vl + v;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) gn[i] = double(Fn[(8 + i) * Vl]);
+      for (int i = 0; i < 4; ++i) gn[i] = double(fac(8 + i, k - 1));
     }
     const double n0 = zv[2 * k] - (g[0] * z0 + g[1] * z1);
     const double n1 = zv[2 * k + 1] - (g[2] * z0 + g[3] * z1);
@@ -205,20 +201,53 @@ __device__ __forceinline__ void column_sweep(const float *__restrict__ fac, int6
   }
 }
 
+// The sweeps of a block's nv columns (v0 on), whose values lie in col [nv][2 (L+1)].  STAGED: all
+// threads first copied the columns' factors to LDS (stage_factors), so the 2 (L+1) dependent
+// steps wait for LDS and not for memory; otherwise a thread reads its column's from memory (a
+// wave's loads of one field are contiguous, the vertex index being fastest).
+template <bool STAGED>
+__device__ __forceinline__ void sweep_columns(int V, int L, int64_t v0, int nv, const float *__restrict__ fac,
+                                              double *col, const float *fsh) {
+  const int t = threadIdx.x;
+  if (t >= nv) return;
+  if constexpr (STAGED) {
+    const float *mine = fsh + t * 12 * (L + 1);
+    column_sweep(L, col + t * 2 * (L + 1), [&](int f, int k) { return mine[12 * k + f]; });
+  } else {
+    const int64_t Vl = V, v = v0 + t;
+    column_sweep(L, col + t * 2 * (L + 1), [&](int f, int k) { return fac[(int64_t(k) * 12 + f) * Vl + v]; });
+  }
+}
+
+// fsh [cols][12 (L+1)] = the factors of columns v0 .. v0 + nv - 1
+__device__ __forceinline__ void stage_factors(int V, int L, int cols, int64_t v0, int nv,
+                                              const float *__restrict__ fac, float *fsh) {
+  const int rows = 12 * (L + 1), shift = 31 - __clz(cols);     // cols is a power of two
+#pragma unroll 4
+  for (int e = threadIdx.x; e < rows * cols; e += blockDim.x) {
+    const int row = e >> shift, c = e & (cols - 1);
+    if (c < nv) fsh[c * rows + row] = fac[int64_t(row) * V + v0 + c];
+  }
+}
+
 // z = M^{-1} r for every vertical line.  A block's `cols` columns are contiguous in r and z
-// (2 (L+1) values each): all its threads copy them through LDS with coalesced loads and
-// stores, and one thread per column runs the column's two sweeps in place in LDS.
+// (2 (L+1) values each): all its threads copy them, and if STAGED their factors, to LDS with
+// coalesced loads, and one thread per column runs the column's two sweeps in place there
+// (apply_shape: which launch takes which form).
+template <bool STAGED>
 __global__ __launch_bounds__(APPLY_THREADS) void colblock_apply_kernel(int V, int L, int cols,
                                                                        const float *__restrict__ fac,
                                                                        const double *__restrict__ r,
                                                                        double *__restrict__ z) {
-  extern __shared__ double col_sh[];   // [cols][2 (L + 1)]
+  extern __shared__ double col_sh[];   // [cols][2 (L + 1)], then the factors
   const int n = 2 * (L + 1);
+  float *fsh = reinterpret_cast<float *>(col_sh + size_t(cols) * n);
   const int64_t v0 = int64_t(blockIdx.x) * cols;
   const int nv = int(V - v0 < int64_t(cols) ? V - v0 : int64_t(cols));
   for (int e = threadIdx.x; e < nv * n; e += blockDim.x) col_sh[e] = r[v0 * n + e];
+  if constexpr (STAGED) stage_factors(V, L, cols, v0, nv, fac, fsh);
   __syncthreads();
-  if (int(threadIdx.x) < nv) column_sweep(fac, V, L, v0 + threadIdx.x, col_sh + threadIdx.x * n);
+  sweep_columns<STAGED>(V, L, v0, nv, fac, col_sh, fsh);
   __syncthreads();
   for (int e = threadIdx.x; e < nv * n; e += blockDim.x) z[v0 * n + e] = col_sh[e];
 }
@@ -229,15 +258,18 @@ __global__ __launch_bounds__(APPLY_THREADS) void colblock_apply_kernel(int V, in
 // row q at (2 r + d) 2 (L+1) + q, so consecutive rows of a column are consecutive for each
 // entry); after the sweeps each row adds its prolongation sum_c W[v][k][c'][c] y[(v, c)] (FP32
 // weights, the two c of a row next to each other).
+template <bool STAGED>
 __global__ __launch_bounds__(APPLY_THREADS) void colblock_correction_kernel(
     int V, int L, int cols, const int32_t *__restrict__ nbr_ptr, const int32_t *__restrict__ nbr_idx,
     const float *__restrict__ fac, const float *__restrict__ W32, const float *__restrict__ JP,
     const double *__restrict__ y, const double *__restrict__ r, double *__restrict__ z) {
-  extern __shared__ double col_sh[];   // [cols][2 (L + 1)]
+  extern __shared__ double col_sh[];   // [cols][2 (L + 1)], then the factors
   const int n = 2 * (L + 1);
+  float *fsh = reinterpret_cast<float *>(col_sh + size_t(cols) * n);
   const int64_t v0 = int64_t(blockIdx.x) * cols;
   const int nv = int(V - v0 < int64_t(cols) ? V - v0 : int64_t(cols));
   const double2 *y2 = reinterpret_cast<const double2 *>(y);
+  if constexpr (STAGED) stage_factors(V, L, cols, v0, nv, fac, fsh);
   for (int e = threadIdx.x; e < nv * n; e += blockDim.x) {
     const int64_t v = v0 + e / n;
     const int q = e - (e / n) * n;
@@ -251,7 +283,7 @@ __global__ __launch_bounds__(APPLY_THREADS) void colblock_correction_kernel(
     col_sh[e] = s;
   }
   __syncthreads();
-  if (int(threadIdx.x) < nv) column_sweep(fac, V, L, v0 + threadIdx.x, col_sh + threadIdx.x * n);
+  sweep_columns<STAGED>(V, L, v0, nv, fac, col_sh, fsh);
   __syncthreads();
   const float2 *W2 = reinterpret_cast<const float2 *>(W32);
   for (int e = threadIdx.x; e < nv * n; e += blockDim.x) {
@@ -266,53 +298,116 @@ constexpr int RED_BLOCK = 256;
 
 constexpr int MD_GROUP = 24;   // dot products per pass over a block's chunk
 
-// partial[b * (nv + 1) + i] = sum over block b's rows of V_i . w (i < nv), and w . w (i = nv).
-// Vectors are taken MD_GROUP at a time, so each pass loads w once for all of them and has
-// 2 MD_GROUP independent loads in flight per iteration: each lane takes two consecutive
-// entries (16-byte loads; n and ld are even) at two places a grid stride apart.  Blocks
-// stride through the vectors together
-// (grid-stride), so at any time the grid reads one window of each vector (DRAM page
-// locality); the summation order is fixed.
+// Sums of MD_GROUP values over a wave's 64 lanes: three exchanges halve the values a lane holds
+// (24 -> 12 -> 6 -> 3) while they add over half the lanes each, then the last three add over eight
+// lanes: 30 exchanges instead of 6 for each value.  Lane l ends with the sums of values
+// 3 (l >> 3) .. 3 (l >> 3) + 2, bit order 5, 4, 3.
+__device__ __forceinline__ void wave_sums(double (&s)[MD_GROUP], double (&out)[3]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int half = MD_GROUP / 2, bit = 32; half >= 3; half /= 2, bit /= 2) {
+    const bool hi = (lane & bit) != 0;
+#pragma unroll
+    for (int i = 0; i < half; ++i) {
+      const double keep = hi ? s[half + i] : s[i], send = hi ? s[i] : s[half + i];
+      s[i] = keep + __shfl_xor(send, bit);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    double t = s[i];
+    for (int bit = 4; bit > 0; bit >>= 1) t += __shfl_xor(t, bit);
+    out[i] = t;
+  }
+}
+
+// One pass of multidot_kernel: G vectors at a time, all their loads in flight at once (a test per
+// vector would make every load wait for the one before).  Past the last vector w itself is read,
+// which is in the cache, and its sum dropped.
+template <int G>
+__device__ __forceinline__ void dot_pass(int64_t n2, const double *__restrict__ V, int64_t ld, int nv,
+                                         const double *__restrict__ w, int i0, double (&s)[MD_GROUP]) {
+  const int64_t stride = int64_t(gridDim.x) * RED_BLOCK;
+  const double2 *w2 = reinterpret_cast<const double2 *>(w);
+  for (int64_t p = int64_t(blockIdx.x) * RED_BLOCK + threadIdx.x; p < n2; p += 2 * stride) {
+    const bool two = p + stride < n2;
+    const int64_t p1 = two ? p + stride : p;
+    const double2 wp = w2[p];
+    double2 wq = w2[p1];
+    if (!two) wq = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const double2 *Vi = reinterpret_cast<const double2 *>(i0 + q < nv ? V + int64_t(i0 + q) * ld : w);
+      const double2 a = Vi[p], b = Vi[p1];
+      s[q] = fma(a.x, wp.x, fma(a.y, wp.y, fma(b.x, wq.x, fma(b.y, wq.y, s[q]))));
+    }
+  }
+}
+
+// partial[i gridDim + b] = sum over block b's rows of V_i . w (i < nv), and w . w (i = nv).
+// Vectors are taken MD_GROUP at a time, so each pass loads w once for all of them: each lane takes
+// two consecutive entries (16-byte loads; n and ld are even) at two places a grid stride apart.
+// Blocks stride through the vectors together, so at any time the grid reads one window of each
+// vector (DRAM page locality); the summation order is fixed.
 __global__ __launch_bounds__(RED_BLOCK) void multidot_kernel(int64_t n2, const double *__restrict__ V, int64_t ld,
                                                              int nv, const double *__restrict__ w,
                                                              double *__restrict__ partial) {
   __shared__ double red[MD_GROUP][RED_BLOCK / 64];
-  const int64_t stride = int64_t(gridDim.x) * RED_BLOCK;
-  const double2 *w2 = reinterpret_cast<const double2 *>(w);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int i0 = 0; i0 <= nv; i0 += MD_GROUP) {
     const int g = nv + 1 - i0 < MD_GROUP ? nv + 1 - i0 : MD_GROUP;
     double s[MD_GROUP];
 #pragma unroll
     for (int q = 0; q < MD_GROUP; ++q) s[q] = 0.0;
-    for (int64_t p = int64_t(blockIdx.x) * RED_BLOCK + threadIdx.x; p < n2; p += 2 * stride) {
-      const int64_t p1 = p + stride;
-      const bool two = p1 < n2;
-      const double2 wp = w2[p];
-      const double2 wq = two ? w2[p1] : make_double2(0.0, 0.0);
+    if (g <= 2) dot_pass<2>(n2, V, ld, nv, w, i0, s);
+    else if (g <= 6) dot_pass<6>(n2, V, ld, nv, w, i0, s);
+    else if (g <= 12) dot_pass<12>(n2, V, ld, nv, w, i0, s);
+    else if (g <= 18) dot_pass<18>(n2, V, ld, nv, w, i0, s);
+    else dot_pass<24>(n2, V, ld, nv, w, i0, s);
+    double t[3];
+    wave_sums(s, t);
+    if ((lane & 7) == 0) {
 #pragma unroll
-      for (int q = 0; q < MD_GROUP; ++q) {
-        if (q < g) {
-          const int i = i0 + q;
-          const double2 *Vi = reinterpret_cast<const double2 *>(V + int64_t(i) * ld);
-          const double2 a = i < nv ? Vi[p] : wp;
-          const double2 b = two ? (i < nv ? Vi[p1] : wq) : make_double2(0.0, 0.0);
-          s[q] = fma(a.x, wp.x, fma(a.y, wp.y, fma(b.x, wq.x, fma(b.y, wq.y, s[q]))));
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < MD_GROUP; ++q) {
-      double t = s[q];
-      for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off);
-      if ((threadIdx.x & 63) == 0) red[q][threadIdx.x >> 6] = t;
+      for (int i = 0; i < 3; ++i) red[3 * (lane >> 3) + i][wave] = t[i];
     }
     __syncthreads();
     if (threadIdx.x < g) {
-      double t = 0.0;
-      for (int q = 0; q < RED_BLOCK / 64; ++q) t += red[threadIdx.x][q];
-      partial[int64_t(blockIdx.x) * (nv + 1) + i0 + threadIdx.x] = t;
+      double u = 0.0;
+      for (int q = 0; q < RED_BLOCK / 64; ++q) u += red[threadIdx.x][q];
+      partial[int64_t(i0 + threadIdx.x) * gridDim.x + blockIdx.x] = u;
     }
     __syncthreads();
+  }
+}
+
+// One block: out[i] = sum_b partial[i nb + b] (i <= nv) in a fixed order, one wave per i, and
+// out[nv + 1], the factor that brings w - V h to unit length: 1 / sqrt(w . w - |h|^2), or 1 where
+// that difference has lost too much to cancellation (not above drop w . w; the caller then
+// projects once more) and 0 where it is not positive.
+__global__ __launch_bounds__(1024) void reduce_dots_kernel(int nb, int nv, const double *__restrict__ partial,
+                                                           double drop, double *__restrict__ out) {
+  __shared__ double h2[16], ww;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  double mine = 0.0;
+  for (int i = wave; i <= nv; i += 16) {
+    const double *row = partial + int64_t(i) * nb;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = lane; b < nb; b += 64) s += row[b];
+    for (int bit = 32; bit > 0; bit >>= 1) s += __shfl_xor(s, bit);
+    if (lane == 0) {
+      out[i] = s;
+      if (i < nv) mine += s * s;
+      else ww = s;
+    }
+  }
+  if (lane == 0) h2[wave] = mine;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double sum = 0.0;
+    for (int q = 0; q < 16; ++q) sum += h2[q];
+    const double left = ww - sum;
+    out[nv + 1] = left > drop * ww ? 1.0 / sqrt(left) : drop > 0.0 ? 1.0 : 0.0;
   }
 }
 
@@ -364,23 +459,27 @@ __global__ void reduce_partials_kernel(int nb, int stride, const double *__restr
   }
 }
 
-// w = w + sign sum_i h_i V_i  (h on the device), two consecutive entries per lane
+// out = scale (w + sign sum_i h_i V_i) (h, and scale where not NULL, on the device; w may be NULL
+// for zero, or out), two consecutive entries per lane.  Walking the vectors from their ends, where
+// the dot products before have just been, is no faster (90 against 86 us for 21 vectors of 2.75M).
 __global__ __launch_bounds__(256) void multiaxpy_kernel(int64_t n2, const double *__restrict__ V, int64_t ld,
                                                         int nv, const double *__restrict__ h,
-                                                        double *__restrict__ w, double sign) {
+                                                        const double *__restrict__ scale, const double *w,
+                                                        double *out, double sign) {
   const int64_t stride = int64_t(gridDim.x) * blockDim.x;
-  double2 *w2 = reinterpret_cast<double2 *>(w);
+  const double2 *w2 = reinterpret_cast<const double2 *>(w);
+  double2 *o2 = reinterpret_cast<double2 *>(out);
+  const double c = scale ? scale[0] : 1.0;
   for (int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; p < n2; p += stride) {
     double ax = 0.0, ay = 0.0;
+#pragma unroll 8
     for (int i = 0; i < nv; ++i) {
       const double2 a = reinterpret_cast<const double2 *>(V + int64_t(i) * ld)[p];
       ax += h[i] * a.x;
       ay += h[i] * a.y;
     }
-    double2 t = w2[p];
-    t.x += sign * ax;
-    t.y += sign * ay;
-    w2[p] = t;
+    const double2 t = w ? w2[p] : make_double2(0.0, 0.0);
+    o2[p] = make_double2(c * (t.x + sign * ax), c * (t.y + sign * ay));
   }
 }
 
@@ -415,12 +514,30 @@ __global__ __launch_bounds__(256) void xpay_kernel(int64_t n, const double *__re
     z[p] = x[p] + a * y[p];
 }
 
-// columns per apply block: the block's columns (2 (L+1) doubles each) stay within 64 KB of LDS
-size_t col_bytes(int L) { return size_t(2) * (L + 1) * sizeof(double); }
-int apply_cols(int L) {
-  int cols = APPLY_MAX_COLS;
-  while (cols > 1 && cols * col_bytes(L) > 65536) cols /= 2;
-  return cols;
+// Shape of an apply launch.  Many columns: 64 a block, each thread reading its column's factors from
+// memory, bound by the bytes (125,000 columns of 11 levels 24 us; staged in LDS, in pieces of a
+// few columns' width, 46 us).  Too few for a block of 64 on each of 256 compute units: the
+// latency of the 2 (L+1) dependent steps counts, so the factors are staged with the columns
+// (2000 columns 11.5 -> 7.2 us) and the columns spread over up to 512 blocks of at least four.  Both
+// (64 bytes a column and level) have to fit 64 KB of LDS for four columns.
+struct ApplyShape {
+  int cols;
+  bool staged;
+  size_t lds;
+  unsigned blocks;
+};
+ApplyShape apply_shape(int V, int L) {
+  const size_t col = size_t(2) * (L + 1) * sizeof(double), fct = size_t(12) * (L + 1) * sizeof(float);
+  ApplyShape a{};
+  a.staged = V < 256 * APPLY_COLS && 4 * (col + fct) <= 65536;
+  const size_t per = col + (a.staged ? fct : 0);
+  a.cols = APPLY_COLS;
+  while (a.cols > 1 && a.cols * per > 65536) a.cols /= 2;
+  if (a.staged)
+    while (a.cols > 4 && (V + a.cols - 1) / a.cols < 512) a.cols /= 2;
+  a.lds = a.cols * per;
+  a.blocks = unsigned((V + a.cols - 1) / a.cols);
+  return a;
 }
 
 unsigned grid_for(int64_t n, int block) {
@@ -459,10 +576,9 @@ fo_status colblock_factor(const fo_mesh *mesh, const void *vals, int dtype, floa
 
 fo_status colblock_apply(const fo_mesh *mesh, const float *fac, const double *r, double *z, hipStream_t s) {
   const MeshView &m = mesh->view;
-  const int cols = apply_cols(m.L);
-  const unsigned blocks = unsigned((m.V + cols - 1) / cols);
-  hipLaunchKernelGGL(colblock_apply_kernel, dim3(blocks), dim3(APPLY_THREADS), cols * col_bytes(m.L), s, m.V, m.L,
-                     cols, fac, r, z);
+  const ApplyShape a = apply_shape(m.V, m.L);
+  hipLaunchKernelGGL(a.staged ? colblock_apply_kernel<true> : colblock_apply_kernel<false>, dim3(a.blocks),
+                     dim3(APPLY_THREADS), a.lds, s, m.V, m.L, a.cols, fac, r, z);
   FO_LAUNCH_CHECK("colblock_apply_kernel");
   return FO_OK;
 }
@@ -470,27 +586,29 @@ fo_status colblock_apply(const fo_mesh *mesh, const float *fac, const double *r,
 fo_status colblock_apply_correction(const fo_mesh *mesh, const float *fac, const float *W32, const float *JP,
                                     const double *y, const double *r, double *z, hipStream_t s) {
   const MeshView &m = mesh->view;
-  const int cols = apply_cols(m.L);
-  const unsigned blocks = unsigned((m.V + cols - 1) / cols);
-  hipLaunchKernelGGL(colblock_correction_kernel, dim3(blocks), dim3(APPLY_THREADS), cols * col_bytes(m.L), s, m.V,
-                     m.L, cols, mesh->nbr_ptr, mesh->nbr_idx, fac, W32, JP, y, r, z);
+  const ApplyShape a = apply_shape(m.V, m.L);
+  hipLaunchKernelGGL(a.staged ? colblock_correction_kernel<true> : colblock_correction_kernel<false>, dim3(a.blocks),
+                     dim3(APPLY_THREADS), a.lds, s, m.V, m.L, a.cols, mesh->nbr_ptr, mesh->nbr_idx, fac, W32, JP, y, r,
+                     z);
   FO_LAUNCH_CHECK("colblock_correction_kernel");
   return FO_OK;
 }
 
+// One pair of entries per thread until two blocks sit on every compute unit: a solve of 44,000
+// dofs took 27 us with a block per 4096 entries (11 blocks), 6 us with 86 (and 2.75M: 102 us before, 85 us with all loads of a pass in flight).
 int multidot_blocks(int64_t n) {
-  const int64_t g = (n + 16 * RED_BLOCK - 1) / (16 * RED_BLOCK);
+  const int64_t g = (n / 2 + RED_BLOCK - 1) / RED_BLOCK;
   return int(g < 512 ? (g > 0 ? g : 1) : 512);
 }
 
 fo_status multidot(int64_t n, const double *V, int64_t ld, int nv, const double *w, double *partial,
-                   double *out, hipStream_t s) {
+                   double *out, double drop, hipStream_t s) {
   if ((n | ld) & 1) return fail(FO_EINVAL, "multidot: vector length and stride must be even");
   const int nb = multidot_blocks(n);
   hipLaunchKernelGGL(multidot_kernel, dim3(nb), dim3(RED_BLOCK), 0, s, n / 2, V, ld, nv, w, partial);
   FO_LAUNCH_CHECK("multidot_kernel");
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3(nv + 1), dim3(256), 0, s, nb, nv + 1, partial, out);
-  FO_LAUNCH_CHECK("reduce_partials_kernel");
+  hipLaunchKernelGGL(reduce_dots_kernel, dim3(1), dim3(1024), 0, s, nb, nv, partial, drop, out);
+  FO_LAUNCH_CHECK("reduce_dots_kernel");
   return FO_OK;
 }
 
@@ -509,12 +627,12 @@ fo_status dot2(int64_t n, const double *a, const double *w, double *partial, dou
   return FO_OK;
 }
 
-fo_status multiaxpy(int64_t n, const double *V, int64_t ld, int nv, const double *h, double *w, double sign,
-                    hipStream_t s) {
+fo_status multiaxpy(int64_t n, const double *V, int64_t ld, int nv, const double *h, const double *scale,
+                    const double *w, double *out, double sign, hipStream_t s) {
   if ((n | ld) & 1) return fail(FO_EINVAL, "multiaxpy: vector length and stride must be even");
   const int64_t g = (n / 2 + 255) / 256;
   hipLaunchKernelGGL(multiaxpy_kernel, dim3(unsigned(g < 2048 ? (g > 0 ? g : 1) : 2048)), dim3(256), 0, s, n / 2, V,
-                     ld, nv, h, w, sign);
+                     ld, nv, h, scale, w, out, sign);
   FO_LAUNCH_CHECK("multiaxpy_kernel");
   return FO_OK;
 }

@@ -173,3 +173,28 @@ def test_newton_wedge_general_exponent(cap, n_glen, A, tol_ref):
     diff = np.abs(Ug - U_ref).max() / np.abs(U_ref).max()
     print(f"[newton n={n_glen}] max |U - U_oracle| / max |U_oracle| = {diff:.2e}")
     assert diff <= 1e-6
+
+
+@pytest.mark.parametrize("restart", [5, 6, 12, 18, 23, 24, 49])
+def test_gmres_restart_lengths(cap, restart):
+    """Krylov bases up to and across the dot products' group sizes (2, 6, 12, 18 and 24 vectors, a
+    second group): the bar of test_newton_matches_oracle_solution."""
+    m, U_ref, M = cap
+    U = to_dev(solve.sia_guess(m))
+    rep = M.newton_solve(U, tol=1e-8, gmres_restart=restart, max_lin=5000)
+    assert rep["status"] == 0 and rep["final_rel"] <= 1e-8
+    assert np.abs(U.cpu().numpy() - U_ref).max() <= 1e-6 * np.abs(U_ref).max()
+
+
+@pytest.mark.parametrize("n_points,L", [(12, 1), (30, 3), (60, 40), (14, 255)])
+def test_newton_on_few_columns(n_points, L):
+    """The preconditioner's apply with its factors in LDS (up to four columns of 255 levels fit) and,
+    beyond, in memory: the same bar."""
+    m = _cap(n_points=n_points, L=L)
+    U_ref, info = solve.newton_solve(m, solve.sia_guess(m), tol=1e-11)
+    assert info["status"] == "converged"
+    M = gpu_mesh(m)
+    U = to_dev(solve.sia_guess(m))
+    rep = M.newton_solve(U, tol=1e-8, max_lin=3000)
+    assert rep["status"] == 0 and rep["final_rel"] <= 1e-8
+    assert np.abs(U.cpu().numpy() - U_ref).max() <= 1e-6 * np.abs(U_ref).max()
