@@ -630,7 +630,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   if (fallback == 1) {
     if ((st = launch_assemble(m, Us, R, nullptr, FO_F64, FO_JAC_NEWTON, false, s)) != FO_OK) return st;
     if (n_residuals) ++*n_residuals;
-    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, s)) != FO_OK) return st;
+    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, nullptr, 0, s)) != FO_OK) return st;
     FO_HIP_TRY(hipMemcpyAsync(&hv[1], dots, sizeof(double), hipMemcpyDeviceToHost, s));
   }
   FO_HIP_TRY(hipStreamSynchronize(s));
@@ -638,7 +638,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   if (use_nn && fallback == 1) {
     if ((st = launch_assemble(m, U, R, nullptr, FO_F64, FO_JAC_NEWTON, false, s)) != FO_OK) return st;
     if (n_residuals) ++*n_residuals;
-    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, s)) != FO_OK) return st;
+    if ((st = multidot(n, nullptr, 0, 0, R, part, dots, 0.0, nullptr, 0, s)) != FO_OK) return st;
     FO_HIP_TRY(hipMemcpyAsync(&hv[0], dots, sizeof(double), hipMemcpyDeviceToHost, s));
     FO_HIP_TRY(hipStreamSynchronize(s));
     use_nn = std::isfinite(hv[0]) && hv[0] <= hv[1];

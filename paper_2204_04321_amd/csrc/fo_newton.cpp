@@ -13,6 +13,7 @@
 #include <chrono>
 #include <cmath>
 #include <cstring>
+#include <string>
 #include <vector>
 
 #include "fo_internal.h"
@@ -64,19 +65,44 @@ struct Ctx {
   hipStream_t s;
   char *ws;
   Layout L;
-  double *host;   // pinned scratch for reductions
+  double *host;   // pinned scratch: reductions land at 0 .. kDotsFlag, uploads start at kStage
+  uint64_t seq = 0;   // of the last reduction
   int64_t n;
   double *dptr(size_t off) { return reinterpret_cast<double *>(ws + off); }
 };
 
+constexpr int kStage = 512, kHostDoubles = 1024;
+
+// multidot whose results also go to c.host
+fo_status dots(Ctx &c, const double *V, int nv, const double *w, double drop) {
+  return multidot(c.n, V, c.n, nv, w, c.dptr(c.L.partial), c.dptr(c.L.dots), drop, c.host, ++c.seq, c.s);
+}
+
+// Waits for the results of the last dots(): they are in c.host once its number is at kDotsFlag,
+// while kernels launched after it may still run.  Ends when the stream has nothing left to do,
+// whether the number came or not, or reports an error.
+fo_status wait_dots(Ctx &c) {
+  const uint64_t *flag = reinterpret_cast<const uint64_t *>(c.host + kDotsFlag);
+  for (;;) {
+    for (int spin = 0; spin < 4096; ++spin)
+      if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) == c.seq) return FO_OK;
+    const hipError_t e = hipStreamQuery(c.s);
+    if (e == hipErrorNotReady) {
+      (void)hipGetLastError();      // no error of a launch: the launch checks must not find it
+      continue;
+    }
+    if (e != hipSuccess) return fail(FO_EDEVICE, std::string("reduction failed: ") + hipGetErrorString(e));
+    if (__atomic_load_n(flag, __ATOMIC_ACQUIRE) == c.seq) return FO_OK;
+    return fail(FO_EDEVICE, "reduction ended without its result");
+  }
+}
+
 // ||x||_2 with a deterministic device reduction
 fo_status norm2(Ctx &c, const double *x, double &out) {
-  fo_status st = multidot(c.n, nullptr, 0, 0, x, c.dptr(c.L.partial), c.dptr(c.L.dots), 0.0, c.s);
-  if (st != FO_OK) return st;
-  FO_HIP_TRY(hipMemcpyAsync(c.host, c.dptr(c.L.dots), sizeof(double), hipMemcpyDeviceToHost, c.s));
-  FO_HIP_TRY(hipStreamSynchronize(c.s));
-  out = std::sqrt(c.host[0]);
-  return FO_OK;
+  fo_status st = dots(c, nullptr, 0, x, 0.0);
+  if (st == FO_OK) st = wait_dots(c);
+  if (st == FO_OK) out = std::sqrt(c.host[0]);
+  return st;
 }
 
 // z = M^{-1} r with the preconditioner the options name
@@ -115,10 +141,17 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int jend = -1;
+    // w = J M^-1 V_j.  It is started as soon as V_j is on its way, so that the device has work while
+    // the host takes in the last projection's numbers, unless the residuals so far say that the
+    // iteration before it converges (its result would not be used).
+    auto product = [&](int j) -> fo_status {
+      fo_status s2 = precondition(c, o, V + int64_t(j) * n, z);
+      return s2 == FO_OK ? spmv(c.m, Jv, o->jac_dtype, z, w, c.s) : s2;
+    };
+    double rel_last = 1.0, rel_before = 1.0;      // |residual| / |b| after the last two iterations
+    if ((st = product(0)) != FO_OK) return st;
     for (int j = 0; j < mres; ++j) {
       double *vj = V + int64_t(j) * n;
-      if ((st = precondition(c, o, vj, z)) != FO_OK) return st;
-      if ((st = spmv(c.m, Jv, o->jac_dtype, z, w, c.s)) != FO_OK) return st;
       // classical Gram-Schmidt with one selective reorthogonalisation.  A pass that
       // shrinks w by kappa = ||w|| / ||w - V h|| leaves it orthogonal to V only to about
       // eps kappa, and the norm from ||w - V h||^2 = ||w||^2 - ||h||^2 is then good to
@@ -127,18 +160,19 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
       // The projected vector goes to V_(j+1), scaled to unit length by the norm formed on the
       // device (left unscaled where a second pass follows, which works on it in place).
       double *vn = vj + n;
+      double *h = c.dptr(c.L.dots);
+      bool ahead = j + 1 < mres && its + 1 < o->max_lin && rel_last * rel_last > o->lin_rtol * rel_before;
       for (int pass = 0; pass < 2; ++pass) {
         const double *src = pass == 0 ? w : vn;
-        double *dots = c.dptr(c.L.dots);
-        if ((st = multidot(n, V, n, j + 1, src, c.dptr(c.L.partial), dots, pass == 0 ? REORTH : 0.0, c.s)) != FO_OK)
-          return st;
-        if ((st = multiaxpy(n, V, n, j + 1, dots, dots + j + 2, src, vn, -1.0, c.s)) != FO_OK) return st;
-        FO_HIP_TRY(hipMemcpyAsync(c.host, dots, sizeof(double) * (j + 3), hipMemcpyDeviceToHost, c.s));
-        FO_HIP_TRY(hipStreamSynchronize(c.s));
+        if ((st = dots(c, V, j + 1, src, pass == 0 ? REORTH : 0.0)) != FO_OK) return st;
+        if ((st = multiaxpy(n, V, n, j + 1, h, h + j + 2, src, vn, -1.0, c.s)) != FO_OK) return st;
+        if (pass == 0 && ahead && (st = product(j + 1)) != FO_OK) return st;
+        if ((st = wait_dots(c)) != FO_OK) return st;
         for (int i = 0; i <= j; ++i) hsum[i] = (pass == 0 ? 0.0 : hsum[i]) + c.host[i];
         const double scale = c.host[j + 2];      // 1 / ||w|| after this projection, 0 for a zero vector
         H[size_t(j + 1) * mres + j] = scale > 0.0 ? 1.0 / scale : scale;
         if (scale != 1.0) break;                 // 1: left unscaled for the second pass
+        ahead = false;                           // V_(j+1) changes once more
       }
       for (int i = 0; i <= j; ++i) H[size_t(i) * mres + j] = hsum[i];
       const double hn = H[size_t(j + 1) * mres + j];
@@ -161,10 +195,13 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
       jend = j;
       const double rel = std::fabs(g[j + 1]) / bnorm;
       rel_out = rel;
+      rel_before = rel_last;
+      rel_last = rel;
       if (rel <= o->lin_rtol || its >= o->max_lin || hn == 0.0) {
         done = true;
         break;
       }
+      if (!ahead && j + 1 < mres && (st = product(j + 1)) != FO_OK) return st;
     }
     // y = H^{-1} g; x += M^{-1} V y
     const int k = jend + 1;
@@ -173,8 +210,8 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
       for (int q = i + 1; q < k; ++q) acc -= H[size_t(i) * mres + q] * y[q];
       y[i] = acc / H[size_t(i) * mres + i];
     }
-    std::memcpy(c.host, y.data(), sizeof(double) * k);
-    FO_HIP_TRY(hipMemcpyAsync(c.dptr(c.L.dots), c.host, sizeof(double) * k, hipMemcpyHostToDevice, c.s));
+    std::memcpy(c.host + kStage, y.data(), sizeof(double) * k);
+    FO_HIP_TRY(hipMemcpyAsync(c.dptr(c.L.dots), c.host + kStage, sizeof(double) * k, hipMemcpyHostToDevice, c.s));
     if ((st = multiaxpy(n, V, n, k, c.dptr(c.L.dots), nullptr, nullptr, t, 1.0, c.s)) != FO_OK) return st;
     if ((st = precondition(c, o, t, z)) != FO_OK) return st;
     if ((st = axpby(n, 1.0, z, 1.0, x, c.s)) != FO_OK) return st;
@@ -306,9 +343,19 @@ extern "C" fo_status fo_newton_solve(const fo_mesh *m, double *U, const fo_newto
   c.n = m->view.n_dofs;
   if (ws_bytes < c.L.total) return fail(FO_EINVAL, "fo_newton_solve: workspace too small");
   std::memset(rep, 0, sizeof(*rep));
-  if (hipHostMalloc(reinterpret_cast<void **>(&c.host), sizeof(double) * 1024) != hipSuccess)
+  if (hipHostMalloc(reinterpret_cast<void **>(&c.host), sizeof(double) * kHostDoubles, hipHostMallocCoherent) !=
+      hipSuccess)
     return fail(FO_ENOMEM, "fo_newton_solve: pinned host buffer");
-  struct HostFree { double *p; ~HostFree() { if (p) (void)hipHostFree(p); } } hf{c.host};
+  c.host[kDotsFlag] = 0.0;
+  struct HostFree {      // kernels of the stream may still write to it after an error
+    double *p;
+    hipStream_t s;
+    ~HostFree() {
+      if (!p) return;
+      (void)hipStreamSynchronize(s);
+      (void)hipHostFree(p);
+    }
+  } hf{c.host, c.s};
 
   const auto t_start = std::chrono::steady_clock::now();
   double *R = c.dptr(c.L.R), *Rt = c.dptr(c.L.Rt), *Ut = c.dptr(c.L.Ut), *dU = c.dptr(c.L.dU);

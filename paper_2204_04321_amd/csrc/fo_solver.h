@@ -14,9 +14,12 @@ fo_status colblock_apply_correction(const fo_mesh *mesh, const float *fac, const
 int multidot_blocks(int64_t n);
 // out[0..nv-1] = V_i . w, out[nv] = w . w, out[nv + 1] = 1 / ||w - V h|| from the first two (1 if
 // ||w - V h||^2 <= drop ||w||^2 with drop > 0; 0 if it is not positive with drop = 0).  partial:
-// multidot_blocks(n) * (nv + 1) doubles, out: nv + 2; n and ld even, FO_EINVAL otherwise.
+// multidot_blocks(n) * (nv + 1) doubles, out: nv + 2; n and ld even, FO_EINVAL otherwise.  host: NULL,
+// or pinned coherent memory of kDotsFlag + 1 doubles that receives out, then seq (an integer) at
+// kDotsFlag.
+constexpr int kDotsMax = 504, kDotsFlag = kDotsMax;
 fo_status multidot(int64_t n, const double *V, int64_t ld, int nv, const double *w, double *partial,
-                   double *out, double drop, hipStream_t s);
+                   double *out, double drop, double *host, uint64_t seq, hipStream_t s);
 int dot2_blocks(int64_t n);
 // out[0] = a . w, out[1] = w . w (partial: 2 dot2_blocks(n) doubles; n even, FO_EINVAL otherwise)
 fo_status dot2(int64_t n, const double *a, const double *w, double *partial, double *out, hipStream_t s);

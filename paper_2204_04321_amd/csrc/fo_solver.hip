@@ -383,10 +383,13 @@ __global__ __launch_bounds__(RED_BLOCK) void multidot_kernel(int64_t n2, const d
 // One block: out[i] = sum_b partial[i nb + b] (i <= nv) in a fixed order, one wave per i, and
 // out[nv + 1], the factor that brings w - V h to unit length: 1 / sqrt(w . w - |h|^2), or 1 where
 // that difference has lost too much to cancellation (not above drop w . w; the caller then
-// projects once more) and 0 where it is not positive.
+// projects once more) and 0 where it is not positive.  With `host` (pinned, coherent) the same
+// values go there as well, and after them `seq` to host[kDotsFlag]: the host reads them as soon as they
+// are there, while later kernels of the stream run.
 __global__ __launch_bounds__(1024) void reduce_dots_kernel(int nb, int nv, const double *__restrict__ partial,
-                                                           double drop, double *__restrict__ out) {
-  __shared__ double h2[16], ww;
+                                                           double drop, double *__restrict__ out, double *host,
+                                                           uint64_t seq) {
+  __shared__ double sum[kDotsMax], h2[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double mine = 0.0;
   for (int i = wave; i <= nv; i += 16) {
@@ -396,18 +399,30 @@ __global__ __launch_bounds__(1024) void reduce_dots_kernel(int nb, int nv, const
     for (int b = lane; b < nb; b += 64) s += row[b];
     for (int bit = 32; bit > 0; bit >>= 1) s += __shfl_xor(s, bit);
     if (lane == 0) {
-      out[i] = s;
+      sum[i] = s;
       if (i < nv) mine += s * s;
-      else ww = s;
     }
   }
   if (lane == 0) h2[wave] = mine;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double sum = 0.0;
-    for (int q = 0; q < 16; ++q) sum += h2[q];
-    const double left = ww - sum;
-    out[nv + 1] = left > drop * ww ? 1.0 / sqrt(left) : drop > 0.0 ? 1.0 : 0.0;
+    double t = 0.0;
+    for (int q = 0; q < 16; ++q) t += h2[q];
+    const double left = sum[nv] - t;
+    sum[nv + 1] = left > drop * sum[nv] ? 1.0 / sqrt(left) : drop > 0.0 ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  if (wave == 0) {      // one wave writes everything, so its release orders all of it before the flag
+    for (int i = lane; i <= nv + 1; i += 64) {
+      out[i] = sum[i];
+      if (host) host[i] = sum[i];
+    }
+    if (host) {
+      __threadfence_system();
+      if (lane == 0)
+        __hip_atomic_store(reinterpret_cast<uint64_t *>(host + kDotsFlag), seq, __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
 
@@ -602,12 +617,13 @@ int multidot_blocks(int64_t n) {
 }
 
 fo_status multidot(int64_t n, const double *V, int64_t ld, int nv, const double *w, double *partial,
-                   double *out, double drop, hipStream_t s) {
+                   double *out, double drop, double *host, uint64_t seq, hipStream_t s) {
   if ((n | ld) & 1) return fail(FO_EINVAL, "multidot: vector length and stride must be even");
+  if (nv + 2 > kDotsMax) return fail(FO_EINVAL, "multidot: too many vectors");
   const int nb = multidot_blocks(n);
   hipLaunchKernelGGL(multidot_kernel, dim3(nb), dim3(RED_BLOCK), 0, s, n / 2, V, ld, nv, w, partial);
   FO_LAUNCH_CHECK("multidot_kernel");
-  hipLaunchKernelGGL(reduce_dots_kernel, dim3(1), dim3(1024), 0, s, nb, nv, partial, drop, out);
+  hipLaunchKernelGGL(reduce_dots_kernel, dim3(1), dim3(1024), 0, s, nb, nv, partial, drop, out, host, seq);
   FO_LAUNCH_CHECK("reduce_dots_kernel");
   return FO_OK;
 }
