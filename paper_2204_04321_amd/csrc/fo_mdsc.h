@@ -33,8 +33,7 @@ struct PlaneLevel {
   int32_t *diag = nullptr;      // [n] index of each vertex's diagonal block
   double *A = nullptr;          // [4 nnzb]
   double *Dinv = nullptr;       // [4 n]
-  double *bound = nullptr;      // [n] Gershgorin row bounds
-  double *g = nullptr;          // [1] their maximum
+  double *g = nullptr;          // [1] largest Gershgorin row bound (behind the object's flags)
   int32_t *agg = nullptr;       // [n] aggregate of each vertex (smoothed levels)
   int32_t *mptr = nullptr, *midx = nullptr;   // members of the next level's vertices
   int32_t *gptr = nullptr, *gidx = nullptr;   // Galerkin gather lists for the next level
@@ -65,7 +64,7 @@ struct fo_mdsc {
                                     // of column v at (2 e + d) 2 (L+1) + q
   size_t jp_count = 0;
   double *Ainv = nullptr;           // coarsest inverse, row-major [nc][nc]
-  int32_t *flag = nullptr;          // device status of the last setup
+  int32_t *flag = nullptr;          // device status of the last setup, then the levels' g
   int32_t *flag_host = nullptr;     // pinned
   bool ready = false;
 };

@@ -3,11 +3,11 @@
 // AMG on the plane; Sec. 4.4: the prolongator built line by line by LU without pivoting of each
 // vertical line's block-tridiagonal system, Chebyshev smoothing on GPUs).
 //
-// Setup (per Jacobian): column factors (the column preconditioner's own kernel), the collapse
+// Setup (per Jacobian): the column preconditioner's factors and, in the same kernel, the collapse
 // weights W of every column by an FP64 block-tridiagonal solve with two right-hand sides, then
 // one pass over J that forms J P0 and the plane operator P0^T J P0 block by block, the plane
 // levels' diagonal inverses and Gershgorin bounds, Galerkin sums through precomputed gather
-// lists (fixed order, no atomics) and the coarsest inverse in one workgroup's LDS.
+// lists (fixed order, no atomics) and the coarsest inverse in one workgroup's registers.
 // Application: restrict with W, a V-cycle over the plane levels (Chebyshev before and after
 // each coarse correction, degree 2 on the first plane level and 1 below it, each step one
 // kernel that forms the residual it needs), then the column smoother on r - J P0 y fused with
@@ -28,6 +28,8 @@ namespace {
 constexpr int NC_MAX = 2 * kMdscCoarsestMax;   // coarsest dofs held in LDS
 constexpr double CHEB_RATIO = 30.0;
 enum { FLAG_DIAG = 0, FLAG_COARSE = 1, N_FLAGS = 4 };
+// the flags, then the levels' bounds g: zeroed together before a setup
+constexpr size_t STATUS_BYTES = sizeof(int32_t) * N_FLAGS + sizeof(double) * kMdscMaxLevels;
 
 __device__ __forceinline__ int nlev(int k, int L) { return (k == 0 || k == L) ? 2 : 3; }
 __device__ __forceinline__ int cumlev(int k) { return k == 0 ? 0 : 3 * k - 1; }
@@ -40,94 +42,17 @@ __device__ __forceinline__ void mul22(const double *a, const double *b, double *
   o[3] = a[2] * b[1] + a[3] * b[3];
 }
 
-// Collapse weights of one vertex column per thread.  Forward: S_k = D_k - Lo_k G_{k-1},
-// G_k = S_k^-1 Up_k, Y_k = S_k^-1 (I - Lo_k Y_{k-1}) for the two right-hand sides e_u, e_v at
-// once (Y_k is 2x2: rows the level's components, columns the right-hand sides); backward
-// Z_k = Y_k - G_k Z_{k+1}; then each right-hand side's solution is divided by the mean of its
-// own component over the levels (e_c itself where that is not usable).  The block's columns
-// (4 (L+1) values each, G and Y/Z) live in LDS and leave with coalesced stores, in FP64 and
-// rounded to FP32.
-template <class JT>
-__global__ __launch_bounds__(64) void weights_kernel(MeshView m, const int32_t *__restrict__ self_rank,
-                                                     const JT *__restrict__ J, double *__restrict__ W,
-                                                     float *__restrict__ W32) {
-  extern __shared__ double wsh[];   // [2][blockDim.x][4 (L + 1)]: Z then G
-  const int L = m.L, nw = 4 * (L + 1);
-  const int64_t v0 = int64_t(blockIdx.x) * blockDim.x;
-  const int nv = int(m.V - v0 < int64_t(blockDim.x) ? m.V - v0 : int64_t(blockDim.x));
-  if (int(threadIdx.x) < nv) {
-    const int64_t v = v0 + threadIdx.x;
-    const int D = m.deg[v], sr = self_rank[v];
-    const int64_t base = m.colptr[v];
-    double *Wv = wsh + threadIdx.x * nw;
-    double *Gv = wsh + (blockDim.x + threadIdx.x) * nw;
-    double Gp[4] = {0, 0, 0, 0}, Yp[4] = {0, 0, 0, 0};
-    for (int k = 0; k <= L; ++k) {
-      const int nl = nlev(k, L), kmin = k > 0 ? k - 1 : 0;
-      double Dk[4], Lo[4] = {0, 0, 0, 0}, Up[4] = {0, 0, 0, 0};
-      for (int c = 0; c < 2; ++c) {
-        const int64_t row = base + int64_t(4) * D * cumlev(k) + int64_t(c) * 2 * nl * D + int64_t(sr) * 2 * nl;
-        for (int d = 0; d < 2; ++d) {
-          Dk[2 * c + d] = double(J[row + 2 * (k - kmin) + d]);
-          if (k > 0) Lo[2 * c + d] = double(J[row + 2 * (k - 1 - kmin) + d]);
-          if (k < L) Up[2 * c + d] = double(J[row + 2 * (k + 1 - kmin) + d]);
-        }
-      }
-      double T[4] = {1, 0, 0, 1};
-      if (k > 0) {
-        double t[4];
-        mul22(Lo, Gp, t);
-        for (int i = 0; i < 4; ++i) Dk[i] -= t[i];
-        mul22(Lo, Yp, t);
-        for (int i = 0; i < 4; ++i) T[i] -= t[i];
-      }
-      const double det = Dk[0] * Dk[3] - Dk[1] * Dk[2];
-      const double Si[4] = {Dk[3] / det, -Dk[1] / det, -Dk[2] / det, Dk[0] / det};
-      mul22(Si, Up, Gp);
-      mul22(Si, T, Yp);
-      for (int i = 0; i < 4; ++i) {
-        Gv[4 * k + i] = Gp[i];
-        Wv[4 * k + i] = Yp[i];
-      }
-    }
-    double Z[4] = {Wv[4 * L], Wv[4 * L + 1], Wv[4 * L + 2], Wv[4 * L + 3]};
-    for (int k = L - 1; k >= 0; --k) {
-      const double G[4] = {Gv[4 * k], Gv[4 * k + 1], Gv[4 * k + 2], Gv[4 * k + 3]};
-      double t[4];
-      mul22(G, Z, t);
-      for (int i = 0; i < 4; ++i) {
-        Z[i] = Wv[4 * k + i] - t[i];
-        Wv[4 * k + i] = Z[i];
-      }
-    }
-    for (int c = 0; c < 2; ++c) {
-      double sum = 0.0;
-      bool finite = true;
-      for (int k = 0; k <= L; ++k) {
-        sum += Wv[4 * k + 2 * c + c];
-        finite = finite && isfinite(Wv[4 * k + c]) && isfinite(Wv[4 * k + 2 + c]);
-      }
-      const double mean = sum / double(L + 1);
-      const bool ok = finite && isfinite(mean) && mean > 0.0;
-      for (int k = 0; k <= L; ++k)
-        for (int cp = 0; cp < 2; ++cp)
-          Wv[4 * k + 2 * cp + c] = ok ? Wv[4 * k + 2 * cp + c] / mean : (cp == c ? 1.0 : 0.0);
-    }
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < nv * nw; e += blockDim.x) {
-    const double w = wsh[e];
-    W[v0 * nw + e] = w;
-    W32[v0 * nw + e] = float(w);
-  }
-}
-
 // One thread per plane block e = (v, neighbour r = w): the rows of J P0 of column v against
 // column w, T[(k, c')][d] = sum over the levels l of J_{(v,k,c'),(w,l,d')} W_w[l][d'][d], and
 // the block A_0[v][w][c][d] = sum_k sum_c' W_v[k][c'][c] T[(k, c')][d] from the FP64 values.
 // J P0 is stored in FP32 by block: entry d of row q of block e at (2 e + d) 2 (L+1) + q (for a
 // column, entry (r, d) of row q at (2 (nbr_ptr[v] + r) + d) 2 (L+1) + q), so a workgroup's
 // blocks own one contiguous range, staged in LDS and written with coalesced stores.
+//
+// Its floor is one pass over J.  A thread's rows lie apart, so the next level's values and weights
+// are loaded while this level's are used, and the three levels of weights a row meets are kept from
+// level to level (875,000 blocks of 10 layers, FP64: 454 -> 244 us; the 0.87 GB of J and 0.2 GB
+// written take 213 at the rate of a large copy).
 template <class JT>
 __global__ __launch_bounds__(256) void plane_kernel(MeshView m, const int32_t *__restrict__ nbr_ptr,
                                                     const int32_t *__restrict__ nbr_idx,
@@ -135,34 +60,64 @@ __global__ __launch_bounds__(256) void plane_kernel(MeshView m, const int32_t *_
                                                     const JT *__restrict__ J, const double *__restrict__ W,
                                                     float *__restrict__ JP, double *__restrict__ A0) {
   extern __shared__ float jsh[];   // [blockDim.x][2][2 (L + 1)]
+  typedef JT V2 __attribute__((ext_vector_type(2), aligned(alignof(JT))));   // rows start on any value
   const int L = m.L, nb = 2 * (L + 1);
   const int e0 = int(blockIdx.x) * blockDim.x, e = e0 + threadIdx.x;
   const int ne = nnzb - e0 < int(blockDim.x) ? nnzb - e0 : int(blockDim.x);
   if (e < nnzb) {
     const int v = blk_row[e], nb0 = nbr_ptr[v], r = e - nb0, D = nbr_ptr[v + 1] - nb0, w = nbr_idx[e];
-    const int64_t base = m.colptr[v];
-    const double *Wv = W + int64_t(v) * (L + 1) * 4, *Ww = W + int64_t(w) * (L + 1) * 4;
-    float *J0 = jsh + threadIdx.x * 2 * nb, *J1 = J0 + nb;
+    const JT *Jv = J + m.colptr[v];
+    const double4 *Wv = reinterpret_cast<const double4 *>(W) + int64_t(v) * (L + 1);
+    const double4 *Ww = reinterpret_cast<const double4 *>(W) + int64_t(w) * (L + 1);
+    float2 *J0 = reinterpret_cast<float2 *>(jsh + threadIdx.x * 2 * nb), *J1 = J0 + L + 1;
+    // a level's two rows against levels k - 1, k, k + 1 of w (zero where there is none)
+    auto rows = [&](int k, V2 (&j)[2][3]) {
+      const int nl = nlev(k, L);
+#pragma unroll
+      for (int cp = 0; cp < 2; ++cp) {
+        const V2 *p = reinterpret_cast<const V2 *>(Jv + int64_t(4) * D * cumlev(k) + cp * 2 * nl * D + r * 2 * nl);
+        j[cp][0] = V2{0, 0};
+        j[cp][2] = V2{0, 0};
+        if (k > 0) j[cp][0] = *p++;
+        j[cp][1] = p[0];
+        if (k < L) j[cp][2] = p[1];
+      }
+    };
+    V2 jn[2][3];
+    rows(0, jn);
+    double4 wl[3] = {make_double4(0, 0, 0, 0), Ww[0], Ww[1]}, wvn = Wv[0];
     double a[4] = {0, 0, 0, 0};
     for (int k = 0; k <= L; ++k) {
-      const int nl = nlev(k, L), klo = k > 0 ? k - 1 : 0;
-      double T[4] = {0, 0, 0, 0};
-      for (int cp = 0; cp < 2; ++cp) {
-        const int64_t row = base + int64_t(4) * D * cumlev(k) + int64_t(cp) * 2 * nl * D + int64_t(r) * 2 * nl;
-        for (int lev = 0; lev < nl; ++lev) {
-          const double j0 = double(J[row + 2 * lev]), j1 = double(J[row + 2 * lev + 1]);
-          const double *wl = Ww + 4 * (klo + lev);
-          T[2 * cp] += j0 * wl[0] + j1 * wl[2];
-          T[2 * cp + 1] += j0 * wl[1] + j1 * wl[3];
-        }
-        J0[2 * k + cp] = float(T[2 * cp]);
-        J1[2 * k + cp] = float(T[2 * cp + 1]);
+      V2 j[2][3];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) j[i / 3][i % 3] = jn[i / 3][i % 3];
+      const double4 wv = wvn;
+      double4 wn = wl[2];
+      if (k < L) {
+        rows(k + 1, jn);
+        wvn = Wv[k + 1];
+        if (k + 2 <= L) wn = Ww[k + 2];
       }
-      const double *wv = Wv + 4 * k;
-      for (int c = 0; c < 2; ++c)
-        for (int d = 0; d < 2; ++d) a[2 * c + d] += wv[c] * T[d] + wv[2 + c] * T[2 + d];
+      double T[4] = {0, 0, 0, 0};
+#pragma unroll
+      for (int cp = 0; cp < 2; ++cp)
+#pragma unroll
+        for (int lev = 0; lev < 3; ++lev) {
+          const double j0 = double(j[cp][lev].x), j1 = double(j[cp][lev].y);
+          T[2 * cp] += j0 * wl[lev].x + j1 * wl[lev].z;
+          T[2 * cp + 1] += j0 * wl[lev].y + j1 * wl[lev].w;
+        }
+      J0[k] = make_float2(float(T[0]), float(T[2]));
+      J1[k] = make_float2(float(T[1]), float(T[3]));
+      a[0] += wv.x * T[0] + wv.z * T[2];
+      a[1] += wv.x * T[1] + wv.z * T[3];
+      a[2] += wv.y * T[0] + wv.w * T[2];
+      a[3] += wv.y * T[1] + wv.w * T[3];
+      wl[0] = wl[1];
+      wl[1] = wl[2];
+      wl[2] = wn;
     }
-    for (int i = 0; i < 4; ++i) A0[4 * int64_t(e) + i] = a[i];
+    reinterpret_cast<double4 *>(A0)[e] = make_double4(a[0], a[1], a[2], a[3]);
   }
   __syncthreads();
   float *out = JP + int64_t(2) * nb * e0;
@@ -170,154 +125,206 @@ __global__ __launch_bounds__(256) void plane_kernel(MeshView m, const int32_t *_
 }
 
 // Diagonal-block inverse of every plane vertex and its Gershgorin row bound
-// max over its two rows of sum_w |(D_v^-1 A_vw)| (entries of both columns).
+// max over its two rows of sum_w |(D_v^-1 A_vw)| (entries of both columns); g, zero before, becomes
+// the largest bound of the level (non-negative doubles order as their bits do, so each workgroup
+// adds its own with one integer maximum).  A singular or non-finite block or bound marks the
+// setup as failed.  A vertex's blocks are taken by GL lanes (with the maximum in a kernel of one
+// workgroup after it: 14 us a level more).
+constexpr int GL = 8;
 __global__ __launch_bounds__(256) void diag_kernel(int n, const int32_t *__restrict__ ptr,
                                                    const int32_t *__restrict__ diag, const double *__restrict__ A,
-                                                   double *__restrict__ Dinv, double *__restrict__ bound,
+                                                   double *__restrict__ Dinv, double *__restrict__ g,
                                                    int32_t *__restrict__ flag) {
-  const int v = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (v >= n) return;
-  const double *a = A + 4 * int64_t(diag[v]);
-  const double det = a[0] * a[3] - a[1] * a[2];
-  double di[4] = {a[3] / det, -a[1] / det, -a[2] / det, a[0] / det};
-  double s0 = 0.0, s1 = 0.0;
-  for (int e = ptr[v]; e < ptr[v + 1]; ++e) {
-    const double *b = A + 4 * int64_t(e);
-    double t[4];
-    mul22(di, b, t);
-    s0 += fabs(t[0]) + fabs(t[1]);
-    s1 += fabs(t[2]) + fabs(t[3]);
-  }
-  bool ok = det != 0.0 && isfinite(det);
-  for (int i = 0; i < 4; ++i) ok = ok && isfinite(di[i]);
-  if (!ok) {
-    flag[FLAG_DIAG] = 1;
-    for (int i = 0; i < 4; ++i) di[i] = 0.0;
-  }
-  for (int i = 0; i < 4; ++i) Dinv[4 * int64_t(v) + i] = di[i];
-  bound[v] = ok ? fmax(s0, s1) : 0.0;
-}
-
-// g = max of the row bounds (one workgroup); a bound that is not a positive finite number
-// marks the setup as failed.
-__global__ __launch_bounds__(1024) void max_kernel(int n, const double *__restrict__ x, double *__restrict__ out,
-                                                   int32_t *__restrict__ flag) {
-  __shared__ double sh[1024];
-  double mx = 0.0;
-  bool bad = false;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    const double t = x[i];
-    bad = bad || !isfinite(t);
-    mx = t > mx ? t : mx;
-  }
-  sh[threadIdx.x] = bad ? -1.0 : mx;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if (int(threadIdx.x) < s) {
-      const double a = sh[threadIdx.x], b = sh[threadIdx.x + s];
-      sh[threadIdx.x] = (a < 0.0 || b < 0.0) ? -1.0 : (a > b ? a : b);
+  __shared__ double sh[4];
+  const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int v = int(gid / GL), sub = int(gid % GL);
+  double s0 = 0.0, s1 = 0.0, bound = 0.0;
+  if (v < n) {
+    const double4 a = reinterpret_cast<const double4 *>(A)[diag[v]];
+    const double det = a.x * a.w - a.y * a.z;
+    const double di[4] = {a.w / det, -a.y / det, -a.z / det, a.x / det};
+    for (int e = ptr[v] + sub; e < ptr[v + 1]; e += GL) {
+      const double4 b = reinterpret_cast<const double4 *>(A)[e];
+      const double bb[4] = {b.x, b.y, b.z, b.w};
+      double t[4];
+      mul22(di, bb, t);
+      s0 += fabs(t[0]) + fabs(t[1]);
+      s1 += fabs(t[2]) + fabs(t[3]);
     }
-    __syncthreads();
+#pragma unroll
+    for (int off = GL / 2; off > 0; off >>= 1) {
+      s0 += __shfl_xor(s0, off, GL);
+      s1 += __shfl_xor(s1, off, GL);
+    }
+    bool ok = det != 0.0 && isfinite(det);
+    for (int i = 0; i < 4; ++i) ok = ok && isfinite(di[i]);
+    bound = fmax(s0, s1);
+    if (!ok || !isfinite(bound) || !(bound > 0.0)) {
+      if (sub == 0) flag[FLAG_DIAG] = 1;
+      bound = 0.0;
+    }
+    if (sub == 0) reinterpret_cast<double4 *>(Dinv)[v] = make_double4(di[0], di[1], di[2], di[3]);
   }
+#pragma unroll
+  for (int off = 32; off >= GL; off >>= 1) bound = fmax(bound, __shfl_xor(bound, off, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = bound;
+  __syncthreads();
   if (threadIdx.x == 0) {
-    out[0] = sh[0];
-    if (!(sh[0] > 0.0)) flag[FLAG_DIAG] = 1;
+    bound = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
+    // most workgroups find a larger bound there already and leave the one address alone
+    auto *gb = reinterpret_cast<unsigned long long *>(g);
+    const auto mine = static_cast<unsigned long long>(__double_as_longlong(bound));
+    if (mine > __hip_atomic_load(gb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(gb, mine);
   }
 }
 
 // Galerkin operator of unsmoothed aggregation: every coarse block is the sum of the fine
-// blocks listed for it (ascending fine index).
+// blocks listed for it.  GL lanes share a block, lane i taking every GL-th entry of the list, then
+// add their sums in a fixed order: the list's indices and the blocks they name are loads that wait
+// for each other, and one lane per block walked all of them (all levels of a 125,000-vertex plane:
+// 96 -> 31 us).
 __global__ __launch_bounds__(256) void galerkin_kernel(int nnz_c, const int32_t *__restrict__ gptr,
                                                        const int32_t *__restrict__ gidx, const double *__restrict__ Af,
                                                        double *__restrict__ Ac) {
-  const int c = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (c >= nnz_c) return;
+  const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int c = int(gid / GL), sub = int(gid % GL);
   double s[4] = {0, 0, 0, 0};
-  for (int i = gptr[c]; i < gptr[c + 1]; ++i) {
-    const double4 b = reinterpret_cast<const double4 *>(Af)[gidx[i]];
-    s[0] += b.x;
-    s[1] += b.y;
-    s[2] += b.z;
-    s[3] += b.w;
-  }
-  reinterpret_cast<double4 *>(Ac)[c] = make_double4(s[0], s[1], s[2], s[3]);
+  if (c < nnz_c)
+    for (int i = gptr[c] + sub; i < gptr[c + 1]; i += GL) {
+      const double4 b = reinterpret_cast<const double4 *>(Af)[gidx[i]];
+      s[0] += b.x;
+      s[1] += b.y;
+      s[2] += b.z;
+      s[3] += b.w;
+    }
+#pragma unroll
+  for (int off = GL / 2; off > 0; off >>= 1)
+    for (int i = 0; i < 4; ++i) s[i] += __shfl_xor(s[i], off, GL);
+  if (c < nnz_c && sub == 0) reinterpret_cast<double4 *>(Ac)[c] = make_double4(s[0], s[1], s[2], s[3]);
 }
 
-// Inverse of the coarsest operator (nc = 2 n <= NC_MAX dofs) by Gauss-Jordan elimination with
-// partial (row) pivoting in LDS, one workgroup: for each column k the pivot row is swapped
-// in, scaled, and eliminated from every other row; the column swaps that undo the row
-// pivoting are applied in reverse order at the end.  Written column-major.
-__global__ __launch_bounds__(1024) void coarse_inverse_kernel(int n, const int32_t *__restrict__ ptr,
-                                                             const int32_t *__restrict__ idx,
-                                                             const double *__restrict__ A, double *__restrict__ Ainv,
-                                                             int32_t *__restrict__ flag) {
+// largest of a key over the wave's 64 lanes, in every lane
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+  auto step = [&](uint32_t y) { x = y > x ? y : x; };
+  step(uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0xB1, 0xf, 0xf, true)));    // quad_perm [1,0,3,2]
+  step(uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x4E, 0xf, 0xf, true)));    // quad_perm [2,3,0,1]
+  step(uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x141, 0xf, 0xf, true)));   // row_half_mirror
+  step(uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x140, 0xf, 0xf, true)));   // row_mirror
+  const uint32_t r0 = __builtin_amdgcn_readlane(x, 0), r1 = __builtin_amdgcn_readlane(x, 16);
+  const uint32_t r2 = __builtin_amdgcn_readlane(x, 32), r3 = __builtin_amdgcn_readlane(x, 48);
+  const uint32_t a = r0 > r1 ? r0 : r1, b = r2 > r3 ? r2 : r3;
+  return a > b ? a : b;
+}
+
+// Inverse of the coarsest operator (nc = 2 n <= NC_MAX dofs) by Gauss-Jordan exchange steps in one
+// workgroup: step k takes as pivot the largest entry of column k among the rows not taken yet (by
+// its top 25 bits, so within 2^-13 of the largest; the lowest row on ties) and exchanges that row
+// with column k.  No row moves: row perm[k] ends as row k of the inverse and column j as its column
+// perm[j].  Written row-major.
+//
+// Bound by the chain of the steps.  Every thread keeps an 8 x 8 part of the matrix (rows and columns
+// 16 apart) in registers, so a step passes only the pivot's column and its scaled row through LDS,
+// with two barriers; each of the four waves finds the pivot by itself (~110 dofs: 101 us with the
+// matrix in LDS and five barriers a step, 90 us as 4 x 4 parts of 1024 threads, which find the
+// pivot sixteen times, 64 us now).
+constexpr int INV_G = 16, INV_R = NC_MAX / INV_G;   // thread grid, rows and columns per thread
+__global__ __launch_bounds__(INV_G *INV_G) void coarse_inverse_kernel(int n, const int32_t *__restrict__ ptr,
+                                                                      const int32_t *__restrict__ idx,
+                                                                      const double *__restrict__ A,
+                                                                      double *__restrict__ Ainv,
+                                                                      int32_t *__restrict__ flag) {
   __shared__ double a[NC_MAX * NC_MAX];
-  __shared__ double fcol[NC_MAX];
-  __shared__ int perm[NC_MAX];
-  __shared__ int piv_row;
-  const int nc = 2 * n, tid = threadIdx.x, bd = blockDim.x;
-  for (int t = tid; t < nc * nc; t += bd) a[t] = 0.0;
+  __shared__ double col[2][NC_MAX], row[NC_MAX];
+  __shared__ int perm[NC_MAX], rank[NC_MAX];
+  const int nc = 2 * n, tid = threadIdx.x, lane = tid & 63, ti = tid / INV_G, tj = tid % INV_G;
+  for (int t = tid; t < NC_MAX * NC_MAX; t += INV_G * INV_G) a[t] = 0.0;
   __syncthreads();
-  for (int v = tid; v < n; v += bd)
-    for (int e = ptr[v]; e < ptr[v + 1]; ++e) {
-      const int w = idx[e];
-      for (int c = 0; c < 2; ++c)
-        for (int d = 0; d < 2; ++d) a[(2 * v + c) * nc + 2 * w + d] = A[4 * int64_t(e) + 2 * c + d];
+  for (int v = tid >> 2; v < n; v += INV_G * INV_G / 4)
+    for (int e = ptr[v] + (tid & 3); e < ptr[v + 1]; e += 4) {
+      const double4 b = reinterpret_cast<const double4 *>(A)[e];
+      double *o = a + 2 * v * NC_MAX + 2 * idx[e];
+      o[0] = b.x;
+      o[1] = b.y;
+      o[NC_MAX] = b.z;
+      o[NC_MAX + 1] = b.w;
     }
   __syncthreads();
-  bool singular = false;
-  for (int k = 0; k < nc; ++k) {
-    if (tid < 64) {   // pivot search: largest |a[i][k]|, i >= k, lowest row on ties
-      double best = -1.0;
-      int bi = k;
-      for (int i = k + tid; i < nc; i += 64) {
-        const double t = fabs(a[i * nc + k]);
-        if (t > best) { best = t; bi = i; }
+  double x[INV_R][INV_R];
+#pragma unroll
+  for (int r = 0; r < INV_R; ++r)
+#pragma unroll
+    for (int c = 0; c < INV_R; ++c) x[r][c] = a[(ti + INV_G * r) * NC_MAX + tj + INV_G * c];
+  bool free0 = lane < nc, free1 = lane + 64 < nc;   // rows lane and lane + 64: not taken yet
+#pragma unroll
+  for (int kb = 0; kb < INV_R; ++kb)
+    for (int kk = 0; kk < INV_G; ++kk) {
+      const int k = INV_G * kb + kk;
+      if (k >= nc) break;
+      double *ck = col[kk & 1];   // in turn: the other waves may still read the last step's
+      if (tj == kk)
+#pragma unroll
+        for (int r = 0; r < INV_R; ++r) {
+          ck[ti + INV_G * r] = x[r][kb];
+          x[r][kb] = 0.0;
+        }
+      __syncthreads();
+      auto key = [&](int i, bool ok) {
+        const uint32_t hi = uint32_t(__double2hiint(ck[i])) & 0x7fffff80u;
+        return ok ? hi | 0x80000000u | uint32_t(127 - i) : 0u;
+      };
+      const uint32_t k0 = key(lane, free0), k1 = key(lane + 64, free1);
+      const int p = 127 - int(wave_max(k0 > k1 ? k0 : k1) & 127u);
+      free0 = free0 && p != lane;
+      free1 = free1 && p != lane + 64;
+      const double piv = ck[p];
+      if (!(piv != 0.0) || !isfinite(piv)) {   // the same for every thread
+        if (tid == 0) flag[FLAG_COARSE] = 1;
+        return;
       }
-      for (int off = 32; off > 0; off >>= 1) {
-        const double ob = __shfl_xor(best, off, 64);
-        const int oi = __shfl_xor(bi, off, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+      if (tid == 0) {
+        perm[k] = p;
+        rank[p] = k;
       }
-      if (tid == 0) { piv_row = bi; perm[k] = bi; }
+      const int pr = p / INV_G;
+      const bool mine = ti == p % INV_G;
+      if (mine) {
+        const double inv = 1.0 / piv;
+#pragma unroll
+        for (int r = 0; r < INV_R; ++r)
+          if (r == pr) {   // the same for the wave: a branch, where selects would take 128 instructions
+#pragma unroll
+            for (int c = 0; c < INV_R; ++c) {
+              const double t = c == kb && tj == kk ? 1.0 : x[r][c];
+              const double q = t * inv;
+              row[tj + INV_G * c] = fma(fma(-piv, q, t), inv, q);   // t / piv to rounding
+            }
+          }
+      }
+      __syncthreads();
+      double rj[INV_R];
+#pragma unroll
+      for (int c = 0; c < INV_R; ++c) rj[c] = row[tj + INV_G * c];
+#pragma unroll
+      for (int r = 0; r < INV_R; ++r) {
+        const double f = ck[ti + INV_G * r];
+#pragma unroll
+        for (int c = 0; c < INV_R; ++c) x[r][c] -= f * rj[c];
+      }
+      if (mine)
+#pragma unroll
+        for (int r = 0; r < INV_R; ++r)
+          if (r == pr)
+#pragma unroll
+            for (int c = 0; c < INV_R; ++c) x[r][c] = rj[c];
     }
-    __syncthreads();
-    const int p = piv_row;
-    if (p != k)
-      for (int j = tid; j < nc; j += bd) {
-        const double t = a[k * nc + j];
-        a[k * nc + j] = a[p * nc + j];
-        a[p * nc + j] = t;
-      }
-    __syncthreads();
-    const double piv = a[k * nc + k];
-    if (!(piv != 0.0) || !isfinite(piv)) { singular = true; break; }   // the same for every thread
-    __syncthreads();
-    for (int j = tid; j < nc; j += bd) a[k * nc + j] = (j == k ? 1.0 : a[k * nc + j]) / piv;
-    for (int i = tid; i < nc; i += bd) fcol[i] = i == k ? 0.0 : a[i * nc + k];
-    __syncthreads();
-    for (int i = tid >> 4; i < nc; i += bd >> 4) {   // 16 threads per row group, no divisions
-      if (i == k) continue;
-      const double f = fcol[i];
-      for (int j = tid & 15; j < nc; j += 16) a[i * nc + j] = (j == k ? 0.0 : a[i * nc + j]) - f * a[k * nc + j];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < INV_R; ++r)
+#pragma unroll
+    for (int c = 0; c < INV_R; ++c) {
+      const int i = ti + INV_G * r, j = tj + INV_G * c;
+      if (i < nc && j < nc) Ainv[rank[i] * nc + perm[j]] = x[r][c];
     }
-    __syncthreads();
-  }
-  if (singular) {
-    if (tid == 0) flag[FLAG_COARSE] = 1;
-    return;
-  }
-  for (int k = nc - 1; k >= 0; --k) {
-    const int p = perm[k];
-    if (p != k)
-      for (int i = tid; i < nc; i += bd) {
-        const double t = a[i * nc + k];
-        a[i * nc + k] = a[i * nc + p];
-        a[i * nc + p] = t;
-      }
-    __syncthreads();
-  }
-  for (int t = tid; t < nc * nc; t += bd) Ainv[t] = a[t];
 }
 
 // ---- application ------------------------------------------------------------------------
@@ -534,7 +541,7 @@ static void free_mdsc(fo_mdsc *p) {
   if (!p) return;
   auto F = [](void *q) { if (q) (void)hipFree(q); };
   for (PlaneLevel &l : p->lv) {
-    F(l.own_ptr); F(l.own_idx); F(l.diag); F(l.A); F(l.Dinv); F(l.bound); F(l.g); F(l.agg);
+    F(l.own_ptr); F(l.own_idx); F(l.diag); F(l.A); F(l.Dinv); F(l.agg);
     F(l.mptr); F(l.midx); F(l.gptr); F(l.gidx); F(l.b); F(l.x); F(l.x2); F(l.d);
   }
   F(p->blk_row); F(p->lv_dev); F(p->fac); F(p->W); F(p->W32); F(p->JP); F(p->Ainv); F(p->flag);
@@ -592,6 +599,8 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
   }
   const size_t last = p->lv.size() - 1;
   // device arrays
+  if (!dev_alloc(p->flag, STATUS_BYTES / sizeof(int32_t)))
+    return bail(FO_ENOMEM, "fo_mdsc_create: device allocation failed");
   for (size_t l = 0; l <= last; ++l) {
     PlaneLevel &q = p->lv[l];
     q.n = int32_t(q.ptr_h.size()) - 1;
@@ -614,7 +623,8 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
          dev_alloc(q.x, 2 * size_t(q.n));
     if (l < last) {
       const PlaneTables &t = tabs[l];
-      ok = ok && dev_alloc(q.Dinv, 4 * size_t(q.n)) && dev_alloc(q.bound, size_t(q.n)) && dev_alloc(q.g, 1) &&
+      q.g = reinterpret_cast<double *>(p->flag + N_FLAGS) + l;
+      ok = ok && dev_alloc(q.Dinv, 4 * size_t(q.n)) &&
            (l > 0 || (dev_alloc(q.x2, 2 * size_t(q.n)) && dev_alloc(q.d, 2 * size_t(q.n)))) &&
            upload(q.agg, q.agg_h, s) && upload(q.mptr, t.mptr, s) && upload(q.midx, t.midx, s) &&
            upload(q.gptr, t.gptr, s) && upload(q.gidx, t.gidx, s);
@@ -635,7 +645,7 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
   }
   if (!upload(p->blk_row, blk_row, s) || !upload(p->lv_dev, views, s) || !dev_alloc(p->fac, 12 * nodes) ||
       !dev_alloc(p->W, 4 * nodes) || !dev_alloc(p->W32, 4 * nodes) || !dev_alloc(p->JP, p->jp_count) ||
-      !dev_alloc(p->Ainv, size_t(nc) * nc) || !dev_alloc(p->flag, N_FLAGS))
+      !dev_alloc(p->Ainv, size_t(nc) * nc))
     return bail(FO_ENOMEM, "fo_mdsc_create: device allocation failed");
   if (hipHostMalloc(reinterpret_cast<void **>(&p->flag_host), sizeof(int32_t) * N_FLAGS) != hipSuccess)
     return bail(FO_ENOMEM, "fo_mdsc_create: pinned allocation failed");
@@ -670,13 +680,6 @@ fo_status setup_t(fo_mdsc *p, const JT *J, hipStream_t s) {
   const fo_mesh *m = p->mesh;
   const MeshView &mv = m->view;
   const PlaneLevel &l0 = p->lv[0];
-  // columns per block: the block's weights and factors (8 (L+1) doubles per column) within 64 KB of LDS
-  const size_t col_bytes = size_t(8) * (mv.L + 1) * sizeof(double);
-  int cols = 64;
-  while (cols > 1 && cols * col_bytes > 65536) cols /= 2;
-  hipLaunchKernelGGL(weights_kernel<JT>, dim3(blocks_for(mv.V, cols)), dim3(cols), cols * col_bytes, s, mv,
-                     m->self_rank, J, p->W, p->W32);
-  FO_LAUNCH_CHECK("mdsc weights");
   // blocks per workgroup: their J P0 rows (4 (L+1) floats each) within 64 KB of LDS
   const size_t blk_bytes = size_t(4) * (mv.L + 1) * sizeof(float);
   int tpb = 256;
@@ -694,27 +697,24 @@ extern "C" fo_status fo_mdsc_setup(fo_mdsc *p, const void *J, int32_t dtype, voi
   hipStream_t s = static_cast<hipStream_t>(stream);
   p->ready = false;
   fo_status st;
-  if ((st = launch_fill_zero(p->flag, sizeof(int32_t) * N_FLAGS, s)) != FO_OK) return st;
-  if ((st = colblock_factor(p->mesh, J, dtype, p->fac, s)) != FO_OK) return st;
+  if ((st = launch_fill_zero(p->flag, STATUS_BYTES, s)) != FO_OK) return st;
+  if ((st = colblock_factor_weights(p->mesh, J, dtype, p->fac, p->W, p->W32, s)) != FO_OK) return st;
   st = dtype == FO_F64 ? setup_t(p, static_cast<const double *>(J), s) : setup_t(p, static_cast<const float *>(J), s);
   if (st != FO_OK) return st;
   const size_t last = p->lv.size() - 1;
   for (size_t l = 0; l < last; ++l) {
     PlaneLevel &q = p->lv[l];
-    hipLaunchKernelGGL(diag_kernel, dim3(blocks_for(q.n, 256)), dim3(256), 0, s, q.n, q.ptr, q.diag, q.A, q.Dinv,
-                       q.bound, p->flag);
+    hipLaunchKernelGGL(diag_kernel, dim3(blocks_for(int64_t(q.n) * GL, 256)), dim3(256), 0, s, q.n, q.ptr, q.diag, q.A,
+                       q.Dinv, q.g, p->flag);
     FO_LAUNCH_CHECK("mdsc diag");
-    hipLaunchKernelGGL(max_kernel, dim3(1), dim3(1024), 0, s, q.n, q.bound, q.g, p->flag);
-    FO_LAUNCH_CHECK("mdsc bound");
     const PlaneLevel &c = p->lv[l + 1];
-    hipLaunchKernelGGL(galerkin_kernel, dim3(blocks_for(c.nnzb, 256)), dim3(256), 0, s, c.nnzb, q.gptr, q.gidx, q.A,
-                       c.A);
+    hipLaunchKernelGGL(galerkin_kernel, dim3(blocks_for(int64_t(c.nnzb) * GL, 256)), dim3(256), 0, s, c.nnzb,
+                       q.gptr, q.gidx, q.A, c.A);
     FO_LAUNCH_CHECK("mdsc galerkin");
   }
   const PlaneLevel &c = p->lv[last];
-  // 1024 threads: the elimination's LDS loads depend on the stores before them, so each
-  // thread's short chain of entries is latency-bound (64 threads: 350 us, 256: 149 us, 1024: 101 us)
-  hipLaunchKernelGGL(coarse_inverse_kernel, dim3(1), dim3(1024), 0, s, c.n, c.ptr, c.idx, c.A, p->Ainv, p->flag);
+  hipLaunchKernelGGL(coarse_inverse_kernel, dim3(1), dim3(INV_G * INV_G), 0, s, c.n, c.ptr, c.idx, c.A, p->Ainv,
+                     p->flag);
   FO_LAUNCH_CHECK("mdsc coarse inverse");
   FO_HIP_TRY(hipMemcpyAsync(p->flag_host, p->flag, sizeof(int32_t) * N_FLAGS, hipMemcpyDeviceToHost, s));
   FO_HIP_TRY(hipStreamSynchronize(s));

@@ -6,6 +6,10 @@
 namespace fo {
 fo_status spmv(const fo_mesh *mesh, const void *vals, int dtype, const double *x, double *y, hipStream_t s);
 fo_status colblock_factor(const fo_mesh *mesh, const void *vals, int dtype, float *fac, hipStream_t s);
+// The same factors and, from one pass over the column blocks, the collapse weights of the two-level
+// preconditioner: W [V][L+1][2][2] and its FP32 rounding.
+fo_status colblock_factor_weights(const fo_mesh *mesh, const void *vals, int dtype, float *fac, double *W, float *W32,
+                                  hipStream_t s);
 fo_status colblock_apply(const fo_mesh *mesh, const float *fac, const double *r, double *z, hipStream_t s);
 // z = P0 y + M^{-1} (r - JP y): the column smoother after the plane correction of the two-level
 // preconditioner (W32: FP32 collapse weights [V][L+1][2][2], JP: FP32 J P0 by column, y: [2 V])

@@ -102,53 +102,129 @@ __global__ __launch_bounds__(256) void spmv_kernel(int V, int L, const int64_t *
   }
 }
 
-// Block-tridiagonal factor of one vertical line (column v): per level k the inverse
-// of the Schur complement S_k (2x2), the coupling to level k-1 (Lo_k) and G_k =
-// S_k^{-1} Up_k (Up_k: the coupling to level k+1), which is all the backward sweep needs.
+// A level's three 2x2 blocks of a vertical line, by row: coupling to level k - 1, diagonal, coupling
+// to level k + 1 (zero where there is none).  The pairs may lie on any boundary of their type.
+template <class JT>
+struct LineRows {
+  typedef JT V2 __attribute__((ext_vector_type(2), aligned(alignof(JT))));
+  V2 lo[2], di[2], up[2];
+  __device__ __forceinline__ void load(const JT *__restrict__ vals, int D, int sr, int k, int L) {
+    const int nl = nlev(k, L);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const V2 *p = reinterpret_cast<const V2 *>(vals + int64_t(4) * D * cumlev(k) + c * 2 * nl * D + sr * 2 * nl);
+      lo[c] = V2{0, 0};
+      up[c] = V2{0, 0};
+      if (k > 0) lo[c] = *p++;
+      di[c] = p[0];
+      if (k < L) up[c] = p[1];
+    }
+  }
+};
+
+// 2x2 product, [2 r + c]
+__device__ __forceinline__ void mul22(const double *a, const double *b, double *o) {
+  o[0] = a[0] * b[0] + a[1] * b[2];
+  o[1] = a[0] * b[1] + a[1] * b[3];
+  o[2] = a[2] * b[0] + a[3] * b[2];
+  o[3] = a[2] * b[1] + a[3] * b[3];
+}
+
+// Block-tridiagonal factor of one vertical line (a column per thread): per level k the inverse
+// of the Schur complement S_k = D_k - Lo_k G_{k-1} (2x2), the coupling to level k-1 (Lo_k) and
+// G_k = S_k^{-1} Up_k (Up_k: the coupling to level k+1), which is all the backward sweep needs.
 // The recursion runs in FP64; the stored factors are FP32 (half the bytes for every
 // preconditioner apply), which defines a fixed linear M^{-1} as right preconditioning needs.
-template <class JT>
-__global__ __launch_bounds__(128) void colblock_factor_kernel(MeshView m, const int32_t *__restrict__ self_rank,
-                                                              const JT *__restrict__ vals,
-                                                              float *__restrict__ fac) {
-  const int v = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (v >= m.V) return;
-  const int L = m.L;
-  const int D = m.deg[v];
-  const int sr = self_rank[v];
-  const int64_t base = m.colptr[v];
-  const int64_t V = m.V;
-  double Gp[4] = {0, 0, 0, 0};      // G_{k-1} = S_{k-1}^{-1} Up_{k-1}
-  for (int k = 0; k <= L; ++k) {
-    const int nl = nlev(k, L), kmin = k > 0 ? k - 1 : 0;
-    double Dk[4], Lo[4] = {0, 0, 0, 0}, Up[4] = {0, 0, 0, 0};
-    for (int c = 0; c < 2; ++c) {
-      const int64_t row = base + int64_t(4) * D * cumlev(k) + int64_t(c) * 2 * nl * D + int64_t(sr) * 2 * nl;
-      for (int d = 0; d < 2; ++d) {
-        Dk[2 * c + d] = double(vals[row + 2 * (k - kmin) + d]);
-        if (k > 0) Lo[2 * c + d] = double(vals[row + 2 * (k - 1 - kmin) + d]);
-        if (k < L) Up[2 * c + d] = double(vals[row + 2 * (k + 1 - kmin) + d]);
+//
+// WEIGHTS also forms the collapse weights of the two-level preconditioner from the same values:
+// forward Y_k = S_k^-1 (I - Lo_k Y_{k-1}) for the two right-hand sides e_u, e_v at once (rows the
+// level's components, columns the right-hand sides), backward Z_k = Y_k - G_k Z_{k+1}, then each
+// right-hand side's solution is divided by the mean of its own component over the levels (e_c
+// itself where that is not usable).  The block's columns (4 (L+1) values each, Y/Z and G) live in
+// LDS and leave with coalesced stores, in FP64 and rounded to FP32.
+//
+// Bound by memory latency: a column's rows lie apart in J and its levels follow from each other, so
+// the rows are loaded two levels ahead (125,000 columns of 10 layers, FP64: 120 us without the
+// weights, and 123 us for a kernel of their own that read the same rows again; together 144 us, of
+// which the ~300 MB of 64-byte pieces the rows touch take 60; 2,000 columns, alone: 17 -> 12 us).
+template <class JT, bool WEIGHTS>
+__global__ __launch_bounds__(64) void colblock_factor_kernel(MeshView m, const int32_t *__restrict__ self_rank,
+                                                             const JT *__restrict__ vals, float *__restrict__ fac,
+                                                             double *__restrict__ W, float *__restrict__ W32) {
+  extern __shared__ double wsh[];   // [2][blockDim.x][4 (L + 1)]: Z then G
+  const int L = m.L, nw = 4 * (L + 1);
+  const int64_t V = m.V, v0 = int64_t(blockIdx.x) * blockDim.x;
+  const int nv = int(V - v0 < int64_t(blockDim.x) ? V - v0 : int64_t(blockDim.x));
+  if (int(threadIdx.x) < nv) {
+    const int64_t v = v0 + threadIdx.x;
+    const int D = m.deg[v], sr = self_rank[v];
+    const JT *line = vals + m.colptr[v];
+    double *Wv = wsh + threadIdx.x * nw, *Gv = wsh + (blockDim.x + threadIdx.x) * nw;
+    double G[4] = {0, 0, 0, 0}, Y[4] = {0, 0, 0, 0};
+    LineRows<JT> cur, n1, n2;
+    n1.load(line, D, sr, 0, L);
+    n2.load(line, D, sr, 1, L);
+    for (int k = 0; k <= L; ++k) {
+      cur = n1;
+      n1 = n2;
+      if (k + 2 <= L) n2.load(line, D, sr, k + 2, L);
+      const double Lo[4] = {double(cur.lo[0].x), double(cur.lo[0].y), double(cur.lo[1].x), double(cur.lo[1].y)};
+      const double Up[4] = {double(cur.up[0].x), double(cur.up[0].y), double(cur.up[1].x), double(cur.up[1].y)};
+      double S[4] = {double(cur.di[0].x), double(cur.di[0].y), double(cur.di[1].x), double(cur.di[1].y)};
+      double t[4];
+      mul22(Lo, G, t);
+      for (int i = 0; i < 4; ++i) S[i] -= t[i];
+      const double det = S[0] * S[3] - S[1] * S[2];
+      const double Si[4] = {S[3] / det, -S[1] / det, -S[2] / det, S[0] / det};
+      mul22(Si, Up, G);
+      float *Fk = fac + int64_t(k) * 12 * V + v;   // field f of level k at Fk[f V]
+      for (int i = 0; i < 4; ++i) {
+        Fk[i * V] = float(Si[i]);
+        Fk[(4 + i) * V] = float(Lo[i]);
+        Fk[(8 + i) * V] = float(G[i]);
+      }
+      if constexpr (WEIGHTS) {
+        double T[4] = {1, 0, 0, 1};
+        mul22(Lo, Y, t);
+        for (int i = 0; i < 4; ++i) T[i] -= t[i];
+        mul22(Si, T, Y);
+        for (int i = 0; i < 4; ++i) {
+          Gv[4 * k + i] = G[i];
+          Wv[4 * k + i] = Y[i];
+        }
       }
     }
-    if (k > 0) {
-      // S_k = D_k - Lo_k S_{k-1}^{-1} Up_{k-1}
-      Dk[0] -= Lo[0] * Gp[0] + Lo[1] * Gp[2];
-      Dk[1] -= Lo[0] * Gp[1] + Lo[1] * Gp[3];
-      Dk[2] -= Lo[2] * Gp[0] + Lo[3] * Gp[2];
-      Dk[3] -= Lo[2] * Gp[1] + Lo[3] * Gp[3];
+    if constexpr (WEIGHTS) {
+      double Z[4] = {Y[0], Y[1], Y[2], Y[3]};
+      double sum[2] = {Y[0], Y[3]};
+      bool finite[2] = {isfinite(Y[0]) && isfinite(Y[2]), isfinite(Y[1]) && isfinite(Y[3])};
+      for (int k = L - 1; k >= 0; --k) {
+        double t[4];
+        mul22(Gv + 4 * k, Z, t);
+        for (int i = 0; i < 4; ++i) {
+          Z[i] = Wv[4 * k + i] - t[i];
+          Wv[4 * k + i] = Z[i];
+        }
+        for (int c = 0; c < 2; ++c) {
+          sum[c] += Z[3 * c];
+          finite[c] = finite[c] && isfinite(Z[c]) && isfinite(Z[2 + c]);
+        }
+      }
+      for (int c = 0; c < 2; ++c) {
+        const double mean = sum[c] / double(L + 1);
+        const bool ok = finite[c] && isfinite(mean) && mean > 0.0;
+        for (int k = 0; k <= L; ++k)
+          for (int cp = 0; cp < 2; ++cp)
+            Wv[4 * k + 2 * cp + c] = ok ? Wv[4 * k + 2 * cp + c] / mean : (cp == c ? 1.0 : 0.0);
+      }
     }
-    const double det = Dk[0] * Dk[3] - Dk[1] * Dk[2];
-    const double id = 1.0 / det;
-    double Si[4] = {Dk[3] * id, -Dk[1] * id, -Dk[2] * id, Dk[0] * id};
-    Gp[0] = Si[0] * Up[0] + Si[1] * Up[2];
-    Gp[1] = Si[0] * Up[1] + Si[1] * Up[3];
-    Gp[2] = Si[2] * Up[0] + Si[3] * Up[2];
-    Gp[3] = Si[2] * Up[1] + Si[3] * Up[3];
-    float *Fk = fac + int64_t(k) * 12 * V + v;   // field f of level k at Fk[f V]
-    for (int i = 0; i < 4; ++i) {
-      Fk[i * V] = float(Si[i]);
-      Fk[(4 + i) * V] = float(Lo[i]);
-      Fk[(8 + i) * V] = float(Gp[i]);
+  }
+  if constexpr (WEIGHTS) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < nv * nw; e += blockDim.x) {
+      const double w = wsh[e];
+      W[v0 * nw + e] = w;
+      W32[v0 * nw + e] = float(w);
     }
   }
 }
@@ -578,13 +654,31 @@ fo_status spmv(const fo_mesh *mesh, const void *vals, int dtype, const double *x
 
 fo_status colblock_factor(const fo_mesh *mesh, const void *vals, int dtype, float *fac, hipStream_t s) {
   const MeshView &m = mesh->view;
-  const unsigned blocks = unsigned((m.V + 127) / 128);
+  const unsigned blocks = unsigned((m.V + 63) / 64);
   if (dtype == FO_F32)
-    hipLaunchKernelGGL(colblock_factor_kernel<float>, dim3(blocks), dim3(128), 0, s, m, mesh->self_rank,
-                       static_cast<const float *>(vals), fac);
+    hipLaunchKernelGGL((colblock_factor_kernel<float, false>), dim3(blocks), dim3(64), 0, s, m, mesh->self_rank,
+                       static_cast<const float *>(vals), fac, nullptr, nullptr);
   else
-    hipLaunchKernelGGL(colblock_factor_kernel<double>, dim3(blocks), dim3(128), 0, s, m, mesh->self_rank,
-                       static_cast<const double *>(vals), fac);
+    hipLaunchKernelGGL((colblock_factor_kernel<double, false>), dim3(blocks), dim3(64), 0, s, m, mesh->self_rank,
+                       static_cast<const double *>(vals), fac, nullptr, nullptr);
+  FO_LAUNCH_CHECK("colblock_factor_kernel");
+  return FO_OK;
+}
+
+fo_status colblock_factor_weights(const fo_mesh *mesh, const void *vals, int dtype, float *fac, double *W, float *W32,
+                                  hipStream_t s) {
+  const MeshView &m = mesh->view;
+  // columns per block: their weights and couplings (8 (L+1) doubles per column) within 64 KB of LDS
+  const size_t col_bytes = size_t(8) * (m.L + 1) * sizeof(double);
+  int cols = 64;
+  while (cols > 1 && cols * col_bytes > 65536) cols /= 2;
+  const unsigned blocks = unsigned((m.V + cols - 1) / cols);
+  if (dtype == FO_F32)
+    hipLaunchKernelGGL((colblock_factor_kernel<float, true>), dim3(blocks), dim3(cols), cols * col_bytes, s, m,
+                       mesh->self_rank, static_cast<const float *>(vals), fac, W, W32);
+  else
+    hipLaunchKernelGGL((colblock_factor_kernel<double, true>), dim3(blocks), dim3(cols), cols * col_bytes, s, m,
+                       mesh->self_rank, static_cast<const double *>(vals), fac, W, W32);
   FO_LAUNCH_CHECK("colblock_factor_kernel");
   return FO_OK;
 }
