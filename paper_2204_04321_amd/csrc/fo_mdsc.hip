@@ -28,8 +28,8 @@ namespace {
 constexpr int NC_MAX = 2 * kMdscCoarsestMax;   // coarsest dofs held in LDS
 constexpr double CHEB_RATIO = 30.0;
 enum { FLAG_DIAG = 0, FLAG_COARSE = 1, N_FLAGS = 4 };
-// the flags, then the levels' bounds g: zeroed together before a setup
-constexpr size_t STATUS_BYTES = sizeof(int32_t) * N_FLAGS + sizeof(double) * kMdscMaxLevels;
+// the flags, then the levels' bounds and smoothing coefficients: zeroed together before a setup
+constexpr size_t STATUS_BYTES = sizeof(int32_t) * N_FLAGS + sizeof(PlaneCheb) * kMdscMaxLevels;
 
 __device__ __forceinline__ int nlev(int k, int L) { return (k == 0 || k == L) ? 2 : 3; }
 __device__ __forceinline__ int cumlev(int k) { return k == 0 ? 0 : 3 * k - 1; }
@@ -178,16 +178,29 @@ __global__ __launch_bounds__(256) void diag_kernel(int n, const int32_t *__restr
   }
 }
 
+// Degree-2 Chebyshev coefficients over [g / ratio, g]: d_0 = D^-1 r_0 / theta and
+// d_1 = rho_1 rho_0 d_0 + 2 rho_1 / delta D^-1 r_1.
+__device__ __forceinline__ void cheb_coeffs(PlaneCheb &c) {
+  const double g = c.g;
+  const double lo = g / CHEB_RATIO;
+  const double theta = 0.5 * (g + lo), delta = 0.5 * (g - lo);
+  const double sigma = theta / delta, rho0 = 1.0 / sigma, rho1 = 1.0 / (2.0 * sigma - rho0);
+  c.inv_theta = 1.0 / theta;
+  c.c1 = rho1 * rho0;
+  c.c2 = 2.0 * rho1 / delta;
+}
+
 // Galerkin operator of unsmoothed aggregation: every coarse block is the sum of the fine
 // blocks listed for it.  GL lanes share a block, lane i taking every GL-th entry of the list, then
-// add their sums in a fixed order: the list's indices and the blocks they name are loads that wait
+// add their sums in a fixed order (and one forms the fine level's smoothing coefficients): the list's indices and the blocks they name are loads that wait
 // for each other, and one lane per block walked all of them (all levels of a 125,000-vertex plane:
 // 96 -> 31 us).
 __global__ __launch_bounds__(256) void galerkin_kernel(int nnz_c, const int32_t *__restrict__ gptr,
                                                        const int32_t *__restrict__ gidx, const double *__restrict__ Af,
-                                                       double *__restrict__ Ac) {
+                                                       double *__restrict__ Ac, PlaneCheb *__restrict__ ch) {
   const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int c = int(gid / GL), sub = int(gid % GL);
+  if (gid == 0) cheb_coeffs(*ch);
   double s[4] = {0, 0, 0, 0};
   if (c < nnz_c)
     for (int i = gptr[c] + sub; i < gptr[c + 1]; i += GL) {
@@ -220,7 +233,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t x) {
 // workgroup: step k takes as pivot the largest entry of column k among the rows not taken yet (by
 // its top 25 bits, so within 2^-13 of the largest; the lowest row on ties) and exchanges that row
 // with column k.  No row moves: row perm[k] ends as row k of the inverse and column j as its column
-// perm[j].  Written row-major.
+// perm[j].  Written column-major.
 //
 // Bound by the chain of the steps.  Every thread keeps an 8 x 8 part of the matrix (rows and columns
 // 16 apart) in registers, so a step passes only the pivot's column and its scaled row through LDS,
@@ -323,78 +336,92 @@ __global__ __launch_bounds__(INV_G *INV_G) void coarse_inverse_kernel(int n, con
 #pragma unroll
     for (int c = 0; c < INV_R; ++c) {
       const int i = ti + INV_G * r, j = tj + INV_G * c;
-      if (i < nc && j < nc) Ainv[rank[i] * nc + perm[j]] = x[r][c];
+      if (i < nc && j < nc) Ainv[perm[j] * nc + rank[i]] = x[r][c];
     }
 }
 
 // ---- application ------------------------------------------------------------------------
 
-struct Cheb {
-  double inv_theta, c1, c2;
-};
-
-// Degree-2 Chebyshev coefficients over [g / ratio, g]: d_0 = D^-1 r_0 / theta and
-// d_1 = rho_1 rho_0 d_0 + 2 rho_1 / delta D^-1 r_1.
-__device__ __forceinline__ Cheb cheb_coeffs(double g) {
-  const double lo = g / CHEB_RATIO;
-  const double theta = 0.5 * (g + lo), delta = 0.5 * (g - lo);
-  const double sigma = theta / delta, rho0 = 1.0 / sigma, rho1 = 1.0 / (2.0 * sigma - rho0);
-  return {1.0 / theta, rho1 * rho0, 2.0 * rho1 / delta};
+__device__ __forceinline__ double2 apply22(double4 d, double2 x) {
+  return make_double2(d.x * x.x + d.y * x.y, d.z * x.x + d.w * x.y);
 }
 
-__device__ __forceinline__ double2 apply22(const double *Dv, double2 x) {
-  return make_double2(Dv[0] * x.x + Dv[1] * x.y, Dv[2] * x.x + Dv[3] * x.y);
+__device__ __forceinline__ double4 diag_inv(const LevelDev &P, int v) {
+  return reinterpret_cast<const double4 *>(P.Dinv)[v];
 }
 
-// b_0[(v, c)] = sum over the column's levels and components of W[v][k][c'][c] r[(v, k, c')].
-// The products of a block of columns are staged in LDS (coalesced loads of r and of the FP32
-// weights, whose two columns c sit next to each other for every row), then one thread per
-// (column, c) sums its column's rows in level order.
-__global__ __launch_bounds__(128) void restrict_fine_kernel(int V, int L, int cols, const float *__restrict__ W32,
-                                                            const double *__restrict__ r, double *__restrict__ b0) {
-  extern __shared__ double rsh[];   // [2][cols][2 (L + 1)]
-  const int nb = 2 * (L + 1);
-  const int64_t v0 = int64_t(blockIdx.x) * cols;
-  const int nv = int(V - v0 < int64_t(cols) ? V - v0 : int64_t(cols));
-  const float2 *W2 = reinterpret_cast<const float2 *>(W32);
-  for (int e = threadIdx.x; e < nv * nb; e += blockDim.x) {
-    const float2 w = W2[v0 * nb + e];
-    const double rv = r[v0 * nb + e];
-    rsh[e] = double(w.x) * rv;
-    rsh[cols * nb + e] = double(w.y) * rv;
+// x1 = D^-1 b / theta of vertex v: a smoothed level's first iterate, from zero
+__device__ __forceinline__ void store_x1(const LevelDev &P, int v, double2 b) {
+  const double it = P.ch->inv_theta;
+  const double2 t = apply22(diag_inv(P, v), b);
+  reinterpret_cast<double2 *>(P.x1)[v] = make_double2(t.x * it, t.y * it);
+}
+
+// b_0[(v, c)] = sum over the column's levels and components of W[v][k][c'][c] r[(v, k, c')], and x1
+// of the first level if it is smoothed.  RL lanes share a column, a lane taking every RL-th level:
+// 16 bytes of r and of the FP32 weights, whose two columns c sit next to each other for every row
+// (125,000 columns of 10 layers: 12.6 us, of which the 46 MB take 9; staged in LDS and summed by a
+// thread per (column, c) 15).
+constexpr int RL = 4;
+__global__ __launch_bounds__(256) void restrict_fine_kernel(LevelDev P, int L, const float *__restrict__ W32,
+                                                            const double *__restrict__ r) {
+  const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const int v = int(gid / RL), sub = int(gid % RL);
+  double2 s = make_double2(0.0, 0.0);
+  if (v < P.n) {
+    const float4 *w = reinterpret_cast<const float4 *>(W32) + int64_t(v) * (L + 1);
+    const double2 *rv = reinterpret_cast<const double2 *>(r) + int64_t(v) * (L + 1);
+#pragma unroll 3
+    for (int k = sub; k <= L; k += RL) {
+      const float4 wk = w[k];
+      const double2 rk = rv[k];
+      s.x += double(wk.x) * rk.x + double(wk.z) * rk.y;
+      s.y += double(wk.y) * rk.x + double(wk.w) * rk.y;
+    }
   }
-  __syncthreads();
-  for (int t = threadIdx.x; t < 2 * nv; t += blockDim.x) {
-    const int v = t >> 1, c = t & 1;
-    const double *p = rsh + c * cols * nb + v * nb;
-    double sum = 0.0;
-    for (int q = 0; q < nb; ++q) sum += p[q];
-    b0[2 * (v0 + v) + c] = sum;
+#pragma unroll
+  for (int off = RL / 2; off > 0; off >>= 1) {
+    s.x += __shfl_xor(s.x, off, RL);
+    s.y += __shfl_xor(s.y, off, RL);
+  }
+  if (v < P.n && sub == 0) {
+    reinterpret_cast<double2 *>(P.b)[v] = s;
+    if (P.x1) store_x1(P, v, s);
   }
 }
 
 // The V-cycle's kernels.  The first plane level smooths with Chebyshev of degree 2 (x kept
-// between the steps), the coarser ones with degree 1, whose pre-smoothed value from zero,
-// x1 = D^-1 b / theta, is formed wherever it is needed instead of stored.  A vertex's row
-// blocks are taken by G = 8 lanes (consecutive blocks, coalesced 32-byte loads) and summed
+// between the steps), the coarser ones with degree 1.  The pre-smoothed value from zero,
+// x1 = D^-1 b / theta, is stored by the kernel that forms b: a neighbour's then costs 16 bytes
+// instead of the 48 of its D^-1 and b.  A vertex's row
+// blocks are taken by G lanes (consecutive blocks, coalesced 32-byte loads) and summed
 // with shuffles; the restriction takes one wave per aggregate.
-constexpr int G = 8;
+//
+// Bound by the chain of loads (row bounds, neighbours, their values): the operator of a 125,000-vertex
+// plane is 28 MB, 6 us at the rate of a large copy.  So the levels' addresses come as kernel
+// arguments and the smoothing coefficients from the setup, the vertex's own values are loaded
+// before the row, and G = 4 lanes take two blocks each at once, which holds a row of the usual 7 in
+// one pass and all rows of that plane on the chip at a time.  With the addresses in memory, the
+// coefficients worked out by every thread, 8 lanes and the vertex's values loaded last:
+// pre-smoothing 14 -> 9 us, restriction 15 -> 13.6, post-smoothing 14 and 12.4 -> 10.6 and 9.
+constexpr int G = 4;
 
-// x1 of vertex w: D_w^-1 b_w / theta
-__device__ __forceinline__ double2 x1_of(const LevelDev &P, int w, double inv_theta) {
-  const double2 t = apply22(P.Dinv + 4 * int64_t(w), reinterpret_cast<const double2 *>(P.b)[w]);
-  return make_double2(t.x * inv_theta, t.y * inv_theta);
-}
-
-// partial sums of A_vw u_w over this lane's blocks of row v
+// partial sums of A_vw u_w over this lane's blocks of row v, two blocks' loads in flight
 template <class U>
 __device__ __forceinline__ double2 row_partial(const LevelDev &P, int v, int sub, U u) {
   double2 s = make_double2(0.0, 0.0);
-  for (int e = P.ptr[v] + sub; e < P.ptr[v + 1]; e += G) {
-    const double2 xw = u(P.idx[e]);
-    const double4 a = reinterpret_cast<const double4 *>(P.A)[e];
-    s.x += a.x * xw.x + a.y * xw.y;
-    s.y += a.z * xw.x + a.w * xw.y;
+  const int end = P.ptr[v + 1];
+  const double4 *A = reinterpret_cast<const double4 *>(P.A);
+  for (int e = P.ptr[v] + sub; e < end; e += 2 * G) {
+    const bool two = e + G < end;
+    const int f = two ? e + G : e;
+    const int w0 = P.idx[e], w1 = P.idx[f];
+    const double4 a = A[e], b = A[f];
+    const double2 x0 = u(w0), x1 = u(w1);
+    s.x += a.x * x0.x + a.y * x0.y;
+    s.y += a.z * x0.x + a.w * x0.y;
+    s.x += two ? b.x * x1.x + b.y * x1.y : 0.0;
+    s.y += two ? b.z * x1.x + b.w * x1.y : 0.0;
   }
   return s;
 }
@@ -410,48 +437,39 @@ __device__ __forceinline__ double2 group_sum(double2 s) {
 
 // Degree-2 pre-smoothing from x = 0 on the first level: x1 = D^-1 b / theta,
 // x = x1 + c1 x1 + c2 D^-1 (b - A x1).
-__global__ __launch_bounds__(256) void pre2_kernel(const LevelDev *__restrict__ lv, int l) {
-  const LevelDev P = lv[l];
+__global__ __launch_bounds__(256) void pre2_kernel(LevelDev P) {
   const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int v = int(gid / G), sub = int(gid % G);
-  const Cheb ch = cheb_coeffs(P.g[0]);
-  double2 s = make_double2(0.0, 0.0);
-  if (v < P.n) s = row_partial(P, v, sub, [&](int w) { return x1_of(P, w, ch.inv_theta); });
-  s = group_sum(s);
-  if (v < P.n && sub == 0) {
-    const double2 b = reinterpret_cast<const double2 *>(P.b)[v];
-    const double2 ds = apply22(P.Dinv + 4 * int64_t(v), make_double2(b.x - s.x, b.y - s.y));
-    const double2 x1 = x1_of(P, v, ch.inv_theta);
+  if (v >= P.n) return;   // a whole group
+  const PlaneCheb ch = *P.ch;
+  const double2 *x1v = reinterpret_cast<const double2 *>(P.x1);
+  const double2 b = reinterpret_cast<const double2 *>(P.b)[v], x1 = x1v[v];
+  const double4 Dv = diag_inv(P, v);
+  const double2 s = group_sum(row_partial(P, v, sub, [&](int w) { return x1v[w]; }));
+  if (sub == 0) {
+    const double2 ds = apply22(Dv, make_double2(b.x - s.x, b.y - s.y));
     reinterpret_cast<double2 *>(P.x)[v] =
         make_double2(x1.x + (ch.c1 * x1.x + ch.c2 * ds.x), x1.y + (ch.c1 * x1.y + ch.c2 * ds.y));
   }
 }
 
 // Residual and restriction in one pass, one wave per aggregate a of the next level:
-// b_C[a] = sum over the members v of (b_v - A_v x), x the pre-smoothed vector (stored for
-// degree 2, x1 formed on the fly for degree 1).  Lanes take (member, block) pairs, 8 members
-// and 8 blocks per pass.
+// b_C[a] = sum over the members v of (b_v - A_v x), x the pre-smoothed vector (x1 for degree 1),
+// and x1 of the next level if it is smoothed.  Lanes take (member, block) pairs, 16
+// members (most aggregates have 7 to 10) and 8 blocks per pass.
 template <int DEG>
-__global__ __launch_bounds__(256) void resid_restrict_kernel(const LevelDev *__restrict__ lv, int l) {
-  const LevelDev P = lv[l], C = lv[l + 1];
+__global__ __launch_bounds__(256) void resid_restrict_kernel(LevelDev P, LevelDev C) {
   const int a = int((int64_t(blockIdx.x) * blockDim.x + threadIdx.x) >> 6);
   const int lane = threadIdx.x & 63, mi = lane / G, sub = lane % G;
   double2 s = make_double2(0.0, 0.0);
   if (a < C.n) {
-    const double inv_theta = DEG == 2 ? 0.0 : cheb_coeffs(P.g[0]).inv_theta;
-    const double2 *x2 = reinterpret_cast<const double2 *>(P.x);
+    const double2 *x = reinterpret_cast<const double2 *>(DEG == 2 ? P.x : P.x1);
     for (int i = P.mptr[a] + mi; i < P.mptr[a + 1]; i += 64 / G) {
       const int v = P.midx[i];
-      double2 t;
-      if constexpr (DEG == 2) t = row_partial(P, v, sub, [&](int w) { return x2[w]; });
-      else t = row_partial(P, v, sub, [&](int w) { return x1_of(P, w, inv_theta); });
-      if (sub == 0) {
-        const double2 b = reinterpret_cast<const double2 *>(P.b)[v];
-        t.x -= b.x;
-        t.y -= b.y;
-      }
-      s.x -= t.x;
-      s.y -= t.y;
+      const double2 b = reinterpret_cast<const double2 *>(P.b)[v];
+      const double2 t = row_partial(P, v, sub, [&](int w) { return x[w]; });
+      s.x += (sub == 0 ? b.x : 0.0) - t.x;
+      s.y += (sub == 0 ? b.y : 0.0) - t.y;
     }
   }
 #pragma unroll
@@ -459,33 +477,33 @@ __global__ __launch_bounds__(256) void resid_restrict_kernel(const LevelDev *__r
     s.x += __shfl_xor(s.x, off, 64);
     s.y += __shfl_xor(s.y, off, 64);
   }
-  if (a < C.n && lane == 0) reinterpret_cast<double2 *>(C.b)[a] = s;
+  if (a < C.n && lane == 0) {
+    reinterpret_cast<double2 *>(C.b)[a] = s;
+    if (C.x1) store_x1(C, a, s);
+  }
 }
 
 // Prolongation and the first post-smoothing step: x' = x + x_C[agg], d = D^-1 (b - A x') / theta,
 // x_out = x' + d (x' of the neighbours formed on the fly; x is x1 for degree 1).  Degree 2
 // writes x2 and d for the second step; degree 1 writes the level's final x.
 template <int DEG>
-__global__ __launch_bounds__(256) void post0_kernel(const LevelDev *__restrict__ lv, int l) {
-  const LevelDev P = lv[l], C = lv[l + 1];
+__global__ __launch_bounds__(256) void post0_kernel(LevelDev P, LevelDev C) {
   const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int v = int(gid / G), sub = int(gid % G);
-  const Cheb ch = cheb_coeffs(P.g[0]);
-  const double2 *xv2 = reinterpret_cast<const double2 *>(P.x);
+  if (v >= P.n) return;   // a whole group
+  const PlaneCheb ch = *P.ch;
+  const double2 *xv2 = reinterpret_cast<const double2 *>(DEG == 2 ? P.x : P.x1);
   const double2 *xc2 = reinterpret_cast<const double2 *>(C.x);
   auto xp = [&](int w) {
-    const double2 xw = DEG == 2 ? xv2[w] : x1_of(P, w, ch.inv_theta);
-    const double2 cw = xc2[P.agg[w]];
+    const double2 xw = xv2[w], cw = xc2[P.agg[w]];
     return make_double2(xw.x + cw.x, xw.y + cw.y);
   };
-  double2 s = make_double2(0.0, 0.0);
-  if (v < P.n) s = row_partial(P, v, sub, xp);
-  s = group_sum(s);
-  if (v < P.n && sub == 0) {
-    const double2 b = reinterpret_cast<const double2 *>(P.b)[v];
-    const double2 dv = apply22(P.Dinv + 4 * int64_t(v), make_double2(b.x - s.x, b.y - s.y));
+  const double2 b = reinterpret_cast<const double2 *>(P.b)[v], xo = xp(v);
+  const double4 Dv = diag_inv(P, v);
+  const double2 s = group_sum(row_partial(P, v, sub, xp));
+  if (sub == 0) {
+    const double2 dv = apply22(Dv, make_double2(b.x - s.x, b.y - s.y));
     const double dx = dv.x * ch.inv_theta, dy = dv.y * ch.inv_theta;
-    const double2 xo = xp(v);
     const double2 out = make_double2(xo.x + dx, xo.y + dy);
     if constexpr (DEG == 2) {
       reinterpret_cast<double2 *>(P.x2)[v] = out;
@@ -497,36 +515,104 @@ __global__ __launch_bounds__(256) void post0_kernel(const LevelDev *__restrict__
 }
 
 // Second degree-2 post-smoothing step: x = x2 + c1 d + c2 D^-1 (b - A x2).
-__global__ __launch_bounds__(256) void post1_kernel(const LevelDev *__restrict__ lv, int l) {
-  const LevelDev P = lv[l];
+__global__ __launch_bounds__(256) void post1_kernel(LevelDev P) {
   const int64_t gid = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   const int v = int(gid / G), sub = int(gid % G);
-  const Cheb ch = cheb_coeffs(P.g[0]);
+  if (v >= P.n) return;   // a whole group
+  const PlaneCheb ch = *P.ch;
   const double2 *xv2 = reinterpret_cast<const double2 *>(P.x2);
-  double2 s = make_double2(0.0, 0.0);
-  if (v < P.n) s = row_partial(P, v, sub, [&](int w) { return xv2[w]; });
-  s = group_sum(s);
-  if (v < P.n && sub == 0) {
-    const double2 b = reinterpret_cast<const double2 *>(P.b)[v];
-    const double2 ds = apply22(P.Dinv + 4 * int64_t(v), make_double2(b.x - s.x, b.y - s.y));
-    const double2 dv = reinterpret_cast<const double2 *>(P.d)[v];
-    const double2 xo = xv2[v];
+  const double2 b = reinterpret_cast<const double2 *>(P.b)[v], dv = reinterpret_cast<const double2 *>(P.d)[v];
+  const double2 xo = xv2[v];
+  const double4 Dv = diag_inv(P, v);
+  const double2 s = group_sum(row_partial(P, v, sub, [&](int w) { return xv2[w]; }));
+  if (sub == 0) {
+    const double2 ds = apply22(Dv, make_double2(b.x - s.x, b.y - s.y));
     reinterpret_cast<double2 *>(P.x)[v] =
         make_double2(xo.x + (ch.c1 * dv.x + ch.c2 * ds.x), xo.y + (ch.c1 * dv.y + ch.c2 * ds.y));
   }
 }
 
-// x = Ainv b on the coarsest level: one wave per row of the row-major inverse, lanes over its
-// columns, a shuffle sum per row.
-__global__ __launch_bounds__(1024) void coarse_solve_kernel(const LevelDev *__restrict__ lv, int last,
-                                                            const double *__restrict__ Ainv) {
-  const LevelDev C = lv[last];
-  const int nc = 2 * C.n, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwave = blockDim.x >> 6;
-  for (int i = wave; i < nc; i += nwave) {
-    double sum = 0.0;
-    for (int j = lane; j < nc; j += 64) sum += Ainv[int64_t(i) * nc + j] * C.b[j];
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (lane == 0) C.x[i] = sum;
+// The V-cycle from level P down as one matrix, two columns (of vertex blockIdx.x) per workgroup, from
+// the next level's matrix C^T: with b a unit vector, x1 = D^-1 b / theta, x_C = C R (b - A x1),
+// x' = x1 + P x_C and x' + D^-1 (b - A x') / theta.  x1 has one vertex and b - A x1 its neighbours
+// (the plane graphs are symmetric).  Column-major, dofs n = 2 P.n.
+__global__ __launch_bounds__(256) void dense_level_kernel(LevelDev P, int nC, const double *__restrict__ CT,
+                                                          double *__restrict__ MT) {
+  __shared__ double2 res[2][kMdscDenseMax];   // b - A x1 at the neighbours, per column
+  __shared__ double2 xc[2][kMdscDenseMax];    // x_C per column
+  const int j = blockIdx.x, tid = threadIdx.x, p0 = P.ptr[j], D = P.ptr[j + 1] - p0;
+  const double it = P.ch->inv_theta;
+  const double4 Dj = diag_inv(P, j);
+  const double2 x1[2] = {make_double2(Dj.x * it, Dj.z * it), make_double2(Dj.y * it, Dj.w * it)};
+  const double4 *A = reinterpret_cast<const double4 *>(P.A);
+  for (int i = tid; i < D; i += 256) {
+    const int w = P.idx[p0 + i];
+    double4 a = make_double4(0, 0, 0, 0);
+    for (int e = P.ptr[w]; e < P.ptr[w + 1]; ++e)
+      if (P.idx[e] == j) a = A[e];
+    for (int c = 0; c < 2; ++c)
+      res[c][i] = make_double2((w == j && c == 0 ? 1.0 : 0.0) - (a.x * x1[c].x + a.y * x1[c].y),
+                               (w == j && c == 1 ? 1.0 : 0.0) - (a.z * x1[c].x + a.w * x1[c].y));
+  }
+  __syncthreads();
+  for (int q = tid; q < nC; q += 256) {
+    double2 s[2] = {make_double2(0, 0), make_double2(0, 0)};
+    for (int i = 0; i < D; ++i) {
+      const int64_t a = 2 * P.agg[P.idx[p0 + i]];
+      const double2 m0 = reinterpret_cast<const double2 *>(CT + a * 2 * nC)[q];
+      const double2 m1 = reinterpret_cast<const double2 *>(CT + (a + 1) * 2 * nC)[q];
+      for (int c = 0; c < 2; ++c) {
+        s[c].x += m0.x * res[c][i].x + m1.x * res[c][i].y;
+        s[c].y += m0.y * res[c][i].x + m1.y * res[c][i].y;
+      }
+    }
+    xc[0][q] = s[0];
+    xc[1][q] = s[1];
+  }
+  __syncthreads();
+  for (int v = tid; v < P.n; v += 256) {
+    double2 s[2] = {make_double2(0, 0), make_double2(0, 0)}, xv[2];
+    for (int e = P.ptr[v]; e < P.ptr[v + 1]; ++e) {
+      const int w = P.idx[e], aw = P.agg[w];
+      const double4 a = A[e];
+      for (int c = 0; c < 2; ++c) {
+        double2 x = xc[c][aw];
+        if (w == j) x = make_double2(x.x + x1[c].x, x.y + x1[c].y);
+        s[c].x += a.x * x.x + a.y * x.y;
+        s[c].y += a.z * x.x + a.w * x.y;
+      }
+    }
+    for (int c = 0; c < 2; ++c) {
+      xv[c] = xc[c][P.agg[v]];
+      if (v == j) xv[c] = make_double2(xv[c].x + x1[c].x, xv[c].y + x1[c].y);
+      const double2 d = apply22(diag_inv(P, v), make_double2((v == j && c == 0 ? 1.0 : 0.0) - s[c].x,
+                                                            (v == j && c == 1 ? 1.0 : 0.0) - s[c].y));
+      reinterpret_cast<double2 *>(MT)[int64_t(2 * j + c) * P.n + v] =
+          make_double2(xv[c].x + d.x * it, xv[c].y + d.y * it);
+    }
+  }
+}
+
+// x = M b for the matrix of a level and all below it, column-major: 16 rows per workgroup, 64 groups of
+// lanes over the columns, sums over a wave by shuffles and over the waves in LDS (430 dofs: 4.7 us, in
+// place of 14 for that level's two kernels and the coarsest solve).
+constexpr int DENSE_ROWS = 16, DENSE_THREADS = 1024;
+__global__ __launch_bounds__(DENSE_THREADS) void dense_apply_kernel(LevelDev C, const double *__restrict__ MT) {
+  __shared__ double sh[DENSE_THREADS / 64][DENSE_ROWS];
+  const int nc = 2 * C.n, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * DENSE_ROWS + lane % DENSE_ROWS, ic = i < nc ? i : nc - 1;
+  double sum = 0.0;
+#pragma unroll 4
+  for (int j = threadIdx.x / DENSE_ROWS; j < nc; j += DENSE_THREADS / DENSE_ROWS)
+    sum += MT[int64_t(j) * nc + ic] * C.b[j];
+#pragma unroll
+  for (int off = 32; off >= DENSE_ROWS; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  if (lane < DENSE_ROWS) sh[wave][lane] = sum;
+  __syncthreads();
+  if (threadIdx.x < DENSE_ROWS && i < nc) {
+    double t = 0.0;
+    for (int w = 0; w < DENSE_THREADS / 64; ++w) t += sh[w][threadIdx.x];
+    C.x[i] = t;
   }
 }
 
@@ -542,9 +628,9 @@ static void free_mdsc(fo_mdsc *p) {
   auto F = [](void *q) { if (q) (void)hipFree(q); };
   for (PlaneLevel &l : p->lv) {
     F(l.own_ptr); F(l.own_idx); F(l.diag); F(l.A); F(l.Dinv); F(l.agg);
-    F(l.mptr); F(l.midx); F(l.gptr); F(l.gidx); F(l.b); F(l.x); F(l.x2); F(l.d);
+    F(l.mptr); F(l.midx); F(l.gptr); F(l.gidx); F(l.b); F(l.x); F(l.x2); F(l.d); F(l.MT);
   }
-  F(p->blk_row); F(p->lv_dev); F(p->fac); F(p->W); F(p->W32); F(p->JP); F(p->Ainv); F(p->flag);
+  F(p->blk_row); F(p->fac); F(p->W); F(p->W32); F(p->JP); F(p->flag);
   if (p->flag_host) (void)hipHostFree(p->flag_host);
   delete p;
 }
@@ -598,6 +684,9 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
     p->lv.push_back(std::move(c));
   }
   const size_t last = p->lv.size() - 1;
+  // the first level that a matrix of its own stands for, with all below it
+  p->dense = int(last);
+  while (p->dense > 1 && p->lv[p->dense - 1].ptr_h.size() - 1 <= size_t(kMdscDenseMax)) --p->dense;
   // device arrays
   if (!dev_alloc(p->flag, STATUS_BYTES / sizeof(int32_t)))
     return bail(FO_ENOMEM, "fo_mdsc_create: device allocation failed");
@@ -623,9 +712,10 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
          dev_alloc(q.x, 2 * size_t(q.n));
     if (l < last) {
       const PlaneTables &t = tabs[l];
-      q.g = reinterpret_cast<double *>(p->flag + N_FLAGS) + l;
+      q.ch = reinterpret_cast<PlaneCheb *>(p->flag + N_FLAGS) + l;
       ok = ok && dev_alloc(q.Dinv, 4 * size_t(q.n)) &&
-           (l > 0 || (dev_alloc(q.x2, 2 * size_t(q.n)) && dev_alloc(q.d, 2 * size_t(q.n)))) &&
+           (int(l) >= p->dense || dev_alloc(q.x2, 2 * size_t(q.n))) && (l > 0 || dev_alloc(q.d, 2 * size_t(q.n))) &&
+           (int(l) < p->dense || dev_alloc(q.MT, 4 * size_t(q.n) * size_t(q.n))) &&
            upload(q.agg, q.agg_h, s) && upload(q.mptr, t.mptr, s) && upload(q.midx, t.midx, s) &&
            upload(q.gptr, t.gptr, s) && upload(q.gidx, t.gidx, s);
     }
@@ -637,15 +727,8 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
   const size_t nodes = size_t(V) * size_t(L + 1);
   const int nc = 2 * p->lv[last].n;
   p->jp_count = size_t(2 * (L + 1)) * 2 * size_t(ptr[V]);
-  // device views of the levels
-  std::vector<LevelDev> views(p->lv.size());
-  for (size_t l = 0; l <= last; ++l) {
-    const PlaneLevel &q = p->lv[l];
-    views[l] = LevelDev{q.n, q.ptr, q.idx, q.agg, q.mptr, q.midx, q.A, q.Dinv, q.g, q.b, q.x, q.x2, q.d};
-  }
-  if (!upload(p->blk_row, blk_row, s) || !upload(p->lv_dev, views, s) || !dev_alloc(p->fac, 12 * nodes) ||
-      !dev_alloc(p->W, 4 * nodes) || !dev_alloc(p->W32, 4 * nodes) || !dev_alloc(p->JP, p->jp_count) ||
-      !dev_alloc(p->Ainv, size_t(nc) * nc))
+  if (!upload(p->blk_row, blk_row, s) || !dev_alloc(p->fac, 12 * nodes) || !dev_alloc(p->W, 4 * nodes) || !dev_alloc(p->W32, 4 * nodes) || !dev_alloc(p->JP, p->jp_count) ||
+      !dev_alloc(p->lv[last].MT, size_t(nc) * nc))
     return bail(FO_ENOMEM, "fo_mdsc_create: device allocation failed");
   if (hipHostMalloc(reinterpret_cast<void **>(&p->flag_host), sizeof(int32_t) * N_FLAGS) != hipSuccess)
     return bail(FO_ENOMEM, "fo_mdsc_create: pinned allocation failed");
@@ -675,6 +758,11 @@ extern "C" fo_status fo_mdsc_graph(const fo_mdsc *p, int32_t level, int32_t *ptr
 }
 
 namespace {
+// What the kernels read of a level.  x1 shares x2, which the first level writes only after its last use.
+LevelDev view(const PlaneLevel &q) {
+  return LevelDev{q.n, q.ptr, q.idx, q.agg, q.mptr, q.midx, q.A, q.Dinv, q.ch, q.b, q.x, q.x2, q.x2, q.d};
+}
+
 template <class JT>
 fo_status setup_t(fo_mdsc *p, const JT *J, hipStream_t s) {
   const fo_mesh *m = p->mesh;
@@ -705,17 +793,22 @@ extern "C" fo_status fo_mdsc_setup(fo_mdsc *p, const void *J, int32_t dtype, voi
   for (size_t l = 0; l < last; ++l) {
     PlaneLevel &q = p->lv[l];
     hipLaunchKernelGGL(diag_kernel, dim3(blocks_for(int64_t(q.n) * GL, 256)), dim3(256), 0, s, q.n, q.ptr, q.diag, q.A,
-                       q.Dinv, q.g, p->flag);
+                       q.Dinv, &q.ch->g, p->flag);
     FO_LAUNCH_CHECK("mdsc diag");
     const PlaneLevel &c = p->lv[l + 1];
     hipLaunchKernelGGL(galerkin_kernel, dim3(blocks_for(int64_t(c.nnzb) * GL, 256)), dim3(256), 0, s, c.nnzb,
-                       q.gptr, q.gidx, q.A, c.A);
+                       q.gptr, q.gidx, q.A, c.A, q.ch);
     FO_LAUNCH_CHECK("mdsc galerkin");
   }
   const PlaneLevel &c = p->lv[last];
-  hipLaunchKernelGGL(coarse_inverse_kernel, dim3(1), dim3(INV_G * INV_G), 0, s, c.n, c.ptr, c.idx, c.A, p->Ainv,
+  hipLaunchKernelGGL(coarse_inverse_kernel, dim3(1), dim3(INV_G * INV_G), 0, s, c.n, c.ptr, c.idx, c.A, c.MT,
                      p->flag);
   FO_LAUNCH_CHECK("mdsc coarse inverse");
+  for (int l = int(last) - 1; l >= p->dense; --l) {
+    hipLaunchKernelGGL(dense_level_kernel, dim3(p->lv[l].n), dim3(256), 0, s, view(p->lv[l]), p->lv[l + 1].n,
+                       p->lv[l + 1].MT, p->lv[l].MT);
+    FO_LAUNCH_CHECK("mdsc dense level");
+  }
   FO_HIP_TRY(hipMemcpyAsync(p->flag_host, p->flag, sizeof(int32_t) * N_FLAGS, hipMemcpyDeviceToHost, s));
   FO_HIP_TRY(hipStreamSynchronize(s));
   if (p->flag_host[FLAG_DIAG])
@@ -733,37 +826,34 @@ extern "C" fo_status fo_mdsc_apply(const fo_mdsc *p, const double *r, double *z,
   if (!p->ready) return fail(FO_EINVAL, "fo_mdsc_apply: no successful fo_mdsc_setup");
   hipStream_t s = static_cast<hipStream_t>(stream);
   const MeshView &mv = p->mesh->view;
-  const size_t last = p->lv.size() - 1;
   const PlaneLevel &l0 = p->lv[0];
-  {
-    const size_t col_bytes = size_t(4) * (mv.L + 1) * sizeof(double);
-    int cols = 64;
-    while (cols > 1 && cols * col_bytes > 65536) cols /= 2;
-    hipLaunchKernelGGL(restrict_fine_kernel, dim3(blocks_for(mv.V, cols)), dim3(128), cols * col_bytes, s, mv.V,
-                       mv.L, cols, p->W32, r, l0.b);
-    FO_LAUNCH_CHECK("mdsc restrict");
-  }
+  const int nd = p->dense;
+  hipLaunchKernelGGL(restrict_fine_kernel, dim3(blocks_for(int64_t(mv.V) * RL, 256)), dim3(256), 0, s, view(l0), mv.L,
+                     p->W32, r);
+  FO_LAUNCH_CHECK("mdsc restrict");
   // level 0 smooths with degree 2, the coarser levels with degree 1
-  const int nl = int(last);
-  for (int l = 0; l < nl; ++l) {
-    const unsigned gv = blocks_for(int64_t(p->lv[l].n) * G, 256), ga = blocks_for(int64_t(p->lv[l + 1].n) * 64, 256);
+  for (int l = 0; l < nd; ++l) {
+    const LevelDev P = view(p->lv[l]), C = view(p->lv[l + 1]);
+    const unsigned gv = blocks_for(int64_t(P.n) * G, 256), ga = blocks_for(int64_t(C.n) * 64, 256);
     if (l == 0) {
-      hipLaunchKernelGGL(pre2_kernel, dim3(gv), dim3(256), 0, s, p->lv_dev, l);
-      hipLaunchKernelGGL(resid_restrict_kernel<2>, dim3(ga), dim3(256), 0, s, p->lv_dev, l);
+      hipLaunchKernelGGL(pre2_kernel, dim3(gv), dim3(256), 0, s, P);
+      hipLaunchKernelGGL(resid_restrict_kernel<2>, dim3(ga), dim3(256), 0, s, P, C);
     } else {
-      hipLaunchKernelGGL(resid_restrict_kernel<1>, dim3(ga), dim3(256), 0, s, p->lv_dev, l);
+      hipLaunchKernelGGL(resid_restrict_kernel<1>, dim3(ga), dim3(256), 0, s, P, C);
     }
     FO_LAUNCH_CHECK("mdsc pre-smoothing");
   }
-  hipLaunchKernelGGL(coarse_solve_kernel, dim3(1), dim3(1024), 0, s, p->lv_dev, nl, p->Ainv);
-  FO_LAUNCH_CHECK("mdsc coarse solve");
-  for (int l = nl - 1; l >= 0; --l) {
-    const unsigned gv = blocks_for(int64_t(p->lv[l].n) * G, 256);
+  hipLaunchKernelGGL(dense_apply_kernel, dim3(blocks_for(2 * p->lv[nd].n, DENSE_ROWS)), dim3(DENSE_THREADS), 0, s,
+                     view(p->lv[nd]), p->lv[nd].MT);
+  FO_LAUNCH_CHECK("mdsc dense solve");
+  for (int l = nd - 1; l >= 0; --l) {
+    const LevelDev P = view(p->lv[l]), C = view(p->lv[l + 1]);
+    const unsigned gv = blocks_for(int64_t(P.n) * G, 256);
     if (l == 0) {
-      hipLaunchKernelGGL(post0_kernel<2>, dim3(gv), dim3(256), 0, s, p->lv_dev, l);
-      hipLaunchKernelGGL(post1_kernel, dim3(gv), dim3(256), 0, s, p->lv_dev, l);
+      hipLaunchKernelGGL(post0_kernel<2>, dim3(gv), dim3(256), 0, s, P, C);
+      hipLaunchKernelGGL(post1_kernel, dim3(gv), dim3(256), 0, s, P);
     } else {
-      hipLaunchKernelGGL(post0_kernel<1>, dim3(gv), dim3(256), 0, s, p->lv_dev, l);
+      hipLaunchKernelGGL(post0_kernel<1>, dim3(gv), dim3(256), 0, s, P, C);
     }
     FO_LAUNCH_CHECK("mdsc post-smoothing");
   }
@@ -785,7 +875,7 @@ extern "C" fo_status fo_mdsc_export(const fo_mdsc *p, int32_t what, int32_t leve
     src = p->lv[level].A;
     n = 4 * size_t(p->lv[level].nnzb);
   } else if (what == FO_MDSC_BOUND && level >= 0 && level < nl - 1) {
-    src = p->lv[level].g;
+    src = &p->lv[level].ch->g;
     n = 1;
   } else {
     return fail(FO_EINVAL, "fo_mdsc_export: bad field or level");

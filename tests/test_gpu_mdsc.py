@@ -445,3 +445,37 @@ def test_weights_fallback_columns_match_oracle():
     err_a = np.abs(P.export("plane", 0).reshape(-1, 4) - A_o).max() / np.abs(A_o).max()
     print(f"\n[mdsc fallback] {len(fell)} columns on e_c; weights {err_w:.1e}, plane {err_a:.1e}")
     assert err_w <= 1e-11 and err_a <= 1e-10
+
+
+@pytest.mark.parametrize("name,sizes", [("islands_512", [1536, 512, 64]), ("islands_513", [1539, 513, 65, 9]),
+                                        ("strip", [2000, 334, 112, 38])])
+def test_apply_where_levels_are_one_matrix(name, sizes):
+    """Planes whose coarser levels lie at the largest size that is applied as one matrix, just above it,
+    and below it twice over (a strip, which coarsens three- to sixfold): one application against the
+    oracle's V-cycle.  The FP32 column factors bound the difference as in
+    test_apply_matches_oracle (the matrix itself is FP64): the same 1e-6."""
+    from paper_2204_04321_amd.api import Mdsc
+    if name == "strip":
+        xy, cells, sig = structured_box(999, 1, 2, 999 * 2e3, 2e3, elem="wedge")
+        m = _slab_fields(xy, cells, sig, seed=9)
+    else:
+        n = int(name.split("_")[1])
+        base = np.array([[0.0, 0.0], [3e3, 0.0], [1e3, 2.5e3]])
+        xy = np.concatenate([base + np.array([10e3 * (i % 32), 10e3 * (i // 32)]) for i in range(n)])
+        m = _slab_fields(xy, np.arange(3 * n, dtype=np.int32).reshape(n, 3), np.linspace(0, 1, 3), seed=10)
+    M = gpu_mesh(m)
+    P = Mdsc(M)
+    got = [len(P.graph(lvl)[0]) - 1 for lvl in range(P.n_levels + 1)]
+    print(f"\n[mdsc matrix] {name}: levels {got}", flush=True)
+    assert got == sizes
+    U = solve.sia_guess(m) + smooth_velocity(m, np.random.default_rng(1), u_scale=5.0)
+    _, Jo = fo.assemble(m, U)
+    Jo = sp.csr_matrix(Jo)
+    P.setup(torch.from_numpy(Jo.data.copy()).cuda())
+    H = mdsc.Hierarchy(m, Jo)
+    r = np.random.default_rng(4).normal(size=m.n_dofs)
+    z = P.apply(to_dev(r)).cpu().numpy()
+    want = H.apply(r)
+    err = np.abs(z - want).max() / np.abs(want).max()
+    print(f"[mdsc matrix] {name}: apply {err:.1e}")
+    assert err <= 1e-6
