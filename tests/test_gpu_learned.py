@@ -262,3 +262,27 @@ def test_committed_network_on_heldout_caps():
         assert 0 <= rep["fallbacks"] <= 6
         if fb == 0:
             assert rep["fallbacks"] == 0
+
+
+@pytest.mark.parametrize("n_cells,L", [(3, 1), (7, 7), (8, 8), (9, 6), (16, 15), (17, 3), (64, 10)])
+def test_features_and_shallow_ice_around_many_cells(n_cells, L):
+    """Fans of triangles around one vertex: fewer, exactly and more cells and neighbours than the
+    lanes that share a vertex (8), rim vertices with fewer than 6 neighbours, and as many layers.
+    Gradients and the shallow-ice profile differ from the reference by the rounding of sums of up to 64
+    terms and of powers: 1e-12 of the largest value; copied thicknesses agree exactly."""
+    from fo_inputs.meshgen import ExtrudedMesh
+    rng = np.random.default_rng(n_cells)
+    phi = 2 * np.pi * (np.arange(n_cells) + rng.uniform(0.3, 0.7, n_cells)) / n_cells
+    rad = rng.uniform(2e3, 5e3, n_cells)
+    xy = np.concatenate([[[0.0, 0.0]], np.stack([rad * np.cos(phi), rad * np.sin(phi)], 1)])
+    i = np.arange(n_cells)
+    tri = np.stack([0 * i, 1 + i, 1 + (i + 1) % n_cells], 1).astype(np.int32)
+    H = rng.uniform(500.0, 900.0, n_cells + 1)
+    s = 1000.0 - 0.02 * xy[:, 0] + rng.uniform(0.0, 30.0, n_cells + 1)
+    m = ExtrudedMesh("wedge", xy, tri, s, H, rng.uniform(200.0, 2000.0, n_cells + 1), np.linspace(0, 1, L + 1), A=1e-16)
+    M = gpu_mesh(m)
+    F, Fo = M.features().cpu().numpy(), ol.column_features(m)
+    np.testing.assert_allclose(F[:, :4], Fo[:, :4], rtol=1e-6, atol=1e-9)
+    np.testing.assert_array_equal(F[:, 4:], Fo[:, 4:].astype(np.float32))
+    U, Uo = M.sia().cpu().numpy(), solve.sia_guess(m)
+    assert np.abs(U - Uo).max() <= 1e-12 * np.abs(Uo).max()
