@@ -221,19 +221,24 @@ __device__ __forceinline__ int tile_row(int q, int j) { return j < 4 ? 4 * q + j
 
 // Gradients of all layers over tiles of 32 rows: the errors dZ_2, dZ_1, dZ_0 pass from layer to
 // layer through LDS in BF16, and each tile adds its 32-row products to the block's weight
-// gradients, held in accumulators (76 registers a lane) until the block's last tile.  Block b
-// writes its sums to part + b NPARAM (the gradients themselves when it is the only one); the
+// gradients, held in accumulators (up to 76 registers a lane) until the block's last tile.  HI: the
+// sums of layers 2 and 3, LO: of layers 0 and 1; a block forms one half or both (backward_plan) and
+// writes its sums to its part of the scratch, or to the gradients when it is the only one; the
 // blocks' sums are added by mlp_reduce_kernel in block order.  Bound by the latency of a tile
 // (three dependent layers, two barriers), so a tile's loads are issued ahead of the chain.
 // Measured, with the sum over the blocks, against one wave per 16x16 tile of each weight gradient
-// walking the whole batch: 230 -> 37 us (512 rows), 2333 -> 36 us (4096), 36.7 ms -> 75 us (65536).
-__global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const float *__restrict__ P,
-                                                                      const float *__restrict__ X, int B,
-                                                                      const float *__restrict__ acts,
-                                                                      const float *__restrict__ dY,
-                                                                      float *__restrict__ part) {
-  __shared__ __align__(16) __bf16 err[2][BWD_ROWS * LDA];       // dZ_2, dZ_1 by row
-  __shared__ __align__(16) __bf16 actT[2][2][NH * LDT];         // [tile parity][layer 0, 1]: activations by column
+// walking the whole batch: 230 -> 30 us (512 rows), 2333 -> 27 us (4096), 36.7 ms -> 73 us (65536).
+constexpr int64_t SPLIT_BELOW = 192;   // blocks of all layers that the scratch holds (backward_plan)
+
+struct BackwardLds {
+  __align__(16) __bf16 err[2][BWD_ROWS * LDA];       // dZ_2, dZ_1 by row
+  __align__(16) __bf16 actT[2][2][NH * LDT];         // [tile parity][layer 0, 1]: activations by column
+};
+
+template <bool HI, bool LO>
+__device__ __forceinline__ void backward_tiles(const float *__restrict__ P, const float *__restrict__ X, int B,
+                                               const float *__restrict__ acts, const float *__restrict__ dY,
+                                               float *__restrict__ G, BackwardLds &S, int block, int blocks) {
   const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
   const int n = 16 * wave + r;
   // W_l as the right operand of dZ_l W_l: k over the layer's outputs, column n of its inputs
@@ -243,7 +248,7 @@ __global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const floa
     const int k = 8 * q + e;
     w3[e] = k < NOUT ? __bf16(P[woff(3) + k * NH + n]) : __bf16(0.f);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; LO && j < 4; ++j) {
       w2[j][e] = __bf16(P[woff(2) + (32 * j + k) * NH + n]);
       w1[j][e] = __bf16(P[woff(1) + (32 * j + k) * NH + n]);
     }
@@ -255,7 +260,7 @@ __global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const floa
   float s3[2] = {0.f, 0.f}, s2 = 0.f, s1 = 0.f, s0 = 0.f;       // bias gradients: this lane's rows
   const int tiles = (B + BWD_ROWS - 1) / BWD_ROWS;
   int par = 0;
-  for (int t = blockIdx.x; t < tiles; t += gridDim.x, par ^= 1) {
+  for (int t = block; t < tiles; t += blocks, par ^= 1) {
     const int64_t m0 = int64_t(t) * BWD_ROWS;
     const int rows = B - m0 < BWD_ROWS ? int(B - m0) : BWD_ROWS;
     float a2[8], a1[8], a0[8];
@@ -268,8 +273,11 @@ __global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const floa
       const float *am = acts + mm * NH + n;
       a2[j] = in ? am[2 * int64_t(B) * NH] : 0.f;
       a1[j] = in ? am[int64_t(B) * NH] : 0.f;
-      a0[j] = in ? am[0] : 0.f;
-      x[j] = in && r < NIN ? __bf16(X[mm * NIN + (r < NIN ? r : 0)]) : __bf16(0.f);
+      if constexpr (LO) {
+        a0[j] = in ? am[0] : 0.f;
+        x[j] = in && r < NIN ? __bf16(X[mm * NIN + (r < NIN ? r : 0)]) : __bf16(0.f);
+      }
+      if constexpr (!HI) continue;
       const float y0 = in ? dY[mm * NOUT + r] : 0.f;
       const float y1 = in && 16 + r < NOUT ? dY[mm * NOUT + (16 + r < NOUT ? 16 + r : 0)] : 0.f;
       s3[0] += y0;
@@ -277,17 +285,19 @@ __global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const floa
       y[0][j] = __bf16(y0);
       y[1][j] = __bf16(y1);
     }
-    bf16x8 h2, h1, h0;
+    auto bf16_of = [](const float *v) {
+      bf16x8 h;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      h2[j] = __bf16(a2[j]);
-      h1[j] = __bf16(a1[j]);
-      h0[j] = __bf16(a0[j]);
+      for (int j = 0; j < 8; ++j) h[j] = __bf16(v[j]);
+      return h;
+    };
+    if constexpr (LO) *reinterpret_cast<bf16x8 *>(&S.actT[par][0][n * LDT + 8 * q]) = bf16_of(a0);
+    if constexpr (HI) {
+      *reinterpret_cast<bf16x8 *>(&S.actT[par][1][n * LDT + 8 * q]) = bf16_of(a1);
+      const bf16x8 h2 = bf16_of(a2);
+      g3[0] = mfma(y[0], h2, g3[0]);
+      g3[1] = mfma(y[1], h2, g3[1]);
     }
-    *reinterpret_cast<bf16x8 *>(&actT[par][1][n * LDT + 8 * q]) = h1;
-    *reinterpret_cast<bf16x8 *>(&actT[par][0][n * LDT + 8 * q]) = h0;
-    g3[0] = mfma(y[0], h2, g3[0]);
-    g3[1] = mfma(y[1], h2, g3[1]);
     // dZ = (product) (1 - a^2) of the lane's eight entries, zero past the batch
     auto through_tanh = [&](const f32x4 *c, const float *a, float &sum, float *d) {
       bf16x8 f;
@@ -313,77 +323,119 @@ __global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const floa
       c[h] = mfma(row_frag(dY + (m0 + (m < rows ? m : 0)) * NOUT, 8 * q, m < rows ? NOUT : 0), w3, zero);
     }
     const bf16x8 d2 = through_tanh(c, a2, s2, d);
-    put(err[0], d2);
+    if constexpr (LO) put(S.err[0], d2);
     __syncthreads();
+    if constexpr (LO) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const __bf16 *src = err[0] + (16 * h + r) * LDA + 8 * q;
-      c[h] = zero;
+      for (int h = 0; h < 2; ++h) {
+        const __bf16 *src = S.err[0] + (16 * h + r) * LDA + 8 * q;
+        c[h] = zero;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) c[h] = mfma(*reinterpret_cast<const bf16x8 *>(src + 32 * j), w2[j], c[h]);
+        for (int j = 0; j < 4; ++j) c[h] = mfma(*reinterpret_cast<const bf16x8 *>(src + 32 * j), w2[j], c[h]);
+      }
     }
+    if constexpr (HI) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      g2[i] = mfma(d2, *reinterpret_cast<const bf16x8 *>(&actT[par][1][(16 * i + r) * LDT + 8 * q]), g2[i]);
-    const bf16x8 d1 = through_tanh(c, a1, s1, d);
-    put(err[1], d1);
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const __bf16 *src = err[1] + (16 * h + r) * LDA + 8 * q;
-      c[h] = zero;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) c[h] = mfma(*reinterpret_cast<const bf16x8 *>(src + 32 * j), w1[j], c[h]);
+      for (int i = 0; i < 8; ++i)
+        g2[i] = mfma(d2, *reinterpret_cast<const bf16x8 *>(&S.actT[par][1][(16 * i + r) * LDT + 8 * q]), g2[i]);
     }
+    if constexpr (LO) {
+      const bf16x8 d1 = through_tanh(c, a1, s1, d);
+      put(S.err[1], d1);
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      g1[i] = mfma(d1, *reinterpret_cast<const bf16x8 *>(&actT[par][0][(16 * i + r) * LDT + 8 * q]), g1[i]);
-    const bf16x8 d0 = through_tanh(c, a0, s0, d);
-    g0 = mfma(d0, x, g0);
+      for (int h = 0; h < 2; ++h) {
+        const __bf16 *src = S.err[1] + (16 * h + r) * LDA + 8 * q;
+        c[h] = zero;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[h] = mfma(*reinterpret_cast<const bf16x8 *>(src + 32 * j), w1[j], c[h]);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        g1[i] = mfma(d1, *reinterpret_cast<const bf16x8 *>(&S.actT[par][0][(16 * i + r) * LDT + 8 * q]), g1[i]);
+      const bf16x8 d0 = through_tanh(c, a0, s0, d);
+      g0 = mfma(d0, x, g0);
+    }
   }
-  float *G = part + int64_t(blockIdx.x) * NPARAM;
   auto over_q = [](float v) {
     v += __shfl_xor(v, 16);
     return v + __shfl_xor(v, 32);
   };
-  s3[0] = over_q(s3[0]);
-  s3[1] = over_q(s3[1]);
-  s2 = over_q(s2);
-  s1 = over_q(s1);
-  s0 = over_q(s0);
-  if (q == 0) {
-    if (wave == 0) {
-      G[boff(3) + r] = s3[0];
-      if (16 + r < NOUT) G[boff(3) + 16 + r] = s3[1];
+  if constexpr (HI) {
+    s3[0] = over_q(s3[0]);
+    s3[1] = over_q(s3[1]);
+    s2 = over_q(s2);
+    if (q == 0) {
+      if (wave == 0) {
+        G[boff(3) + r] = s3[0];
+        if (16 + r < NOUT) G[boff(3) + 16 + r] = s3[1];
+      }
+      G[boff(2) + n] = s2;
     }
-    G[boff(2) + n] = s2;
-    G[boff(1) + n] = s1;
-    G[boff(0) + n] = s0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = 4 * q + i;              // row of a 16-row tile of outputs
+      G[woff(3) + m * NH + n] = g3[0][i];
+      if (16 + m < NOUT) G[woff(3) + (16 + m) * NH + n] = g3[1][i];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) G[woff(2) + (16 * wave + m) * NH + 16 * j + r] = g2[j][i];
+    }
   }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = 4 * q + i;              // row of a 16-row tile of outputs
-    G[woff(3) + m * NH + n] = g3[0][i];
-    if (16 + m < NOUT) G[woff(3) + (16 + m) * NH + n] = g3[1][i];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      G[woff(2) + (16 * wave + m) * NH + 16 * j + r] = g2[j][i];
-      G[woff(1) + (16 * wave + m) * NH + 16 * j + r] = g1[j][i];
+  if constexpr (LO) {
+    s1 = over_q(s1);
+    s0 = over_q(s0);
+    if (q == 0) {
+      G[boff(1) + n] = s1;
+      G[boff(0) + n] = s0;
     }
-    if (r < NIN) G[woff(0) + (16 * wave + m) * NIN + r] = g0[i];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int m = 4 * q + i;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) G[woff(1) + (16 * wave + m) * NH + 16 * j + r] = g1[j][i];
+      if (r < NIN) G[woff(0) + (16 * wave + m) * NIN + r] = g0[i];
+    }
   }
 }
 
-// G = sum of the nb blocks' gradients in a fixed order: 64 parameters a block, four waves over
+// Which block forms what (backward_plan), and where block b of a kind leaves its sums: parameter p at
+// base + b stride + p.
+struct BackwardPlan {
+  int split;                        // blocks of layers 2 and 3, then blocks of layers 0 and 1; or all layers
+  int hi_blocks, lo_blocks;         // blocks with sums of layers 2 and 3, of layers 0 and 1
+  int64_t hi_base, hi_stride, lo_base, lo_stride;
+};
+
+__global__ __launch_bounds__(MLP_THREADS, 2) void mlp_backward_kernel(const float *__restrict__ P,
+                                                                      const float *__restrict__ X, int B,
+                                                                      const float *__restrict__ acts,
+                                                                      const float *__restrict__ dY,
+                                                                      float *__restrict__ part, BackwardPlan L) {
+  __shared__ BackwardLds S;
+  const int b = blockIdx.x;
+  if (!L.split) {
+    backward_tiles<true, true>(P, X, B, acts, dY, part + b * L.hi_stride, S, b, L.hi_blocks);
+  } else if (b < L.hi_blocks) {
+    backward_tiles<true, false>(P, X, B, acts, dY, part + L.hi_base + b * L.hi_stride, S, b, L.hi_blocks);
+  } else {
+    const int c = b - L.hi_blocks;
+    backward_tiles<false, true>(P, X, B, acts, dY, part + L.lo_base + c * L.lo_stride, S, c, L.lo_blocks);
+  }
+}
+
+// G = sum of the blocks' gradients in a fixed order: 64 parameters a block, four waves over
 // the blocks
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(int nb, const float *__restrict__ part,
+__global__ __launch_bounds__(256) void mlp_reduce_kernel(BackwardPlan L, const float *__restrict__ part,
                                                          float *__restrict__ G) {
   __shared__ float sh[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, p = int(blockIdx.x) * 64 + lane;
+  const bool hi = p >= woff(2);
+  const int nb = hi ? L.hi_blocks : L.lo_blocks;
+  const int64_t base = hi ? L.hi_base : L.lo_base, stride = hi ? L.hi_stride : L.lo_stride;
   float s = 0.f;
   if (p < NPARAM) {
 #pragma unroll 8
-    for (int b = w; b < nb; b += 4) s += part[int64_t(b) * NPARAM + p];
+    for (int b = w; b < nb; b += 4) s += part[base + b * stride + p];
   }
   sh[w][lane] = s;
   __syncthreads();
@@ -541,22 +593,38 @@ extern "C" fo_status fo_mlp_forward(const float *P, const float *X, int32_t B, f
   return mlp_forward_impl(P, X, B, acts, Y, static_cast<hipStream_t>(stream));
 }
 
+// The scratch (2 B NH floats) bounds the blocks, each of which leaves its sums there.  A block of layers 0
+// and 1 only, or of 2 and 3 only, leaves half as much, so twice as many work on the tiles; the former
+// take longer for a tile (they pass the errors through all layers), so there are half as many more of
+// them.  Where the scratch holds most of a block per compute unit anyway, blocks of all layers do not
+// load the tiles and form the first errors twice.  Both, with the sum over the blocks, by rows: 512
+// 29.6 us in halves, 37.4 not; 4096 27.2, 36.2; 16384 36.9, 46.3; 24000 43.7, 48.7; 27952 49.4, 50.7.
+// Less scratch than three such blocks: one of each kind, straight into the gradients (200 rows: 32 us,
+// 39 in one block).
+static BackwardPlan backward_plan(int32_t B) {
+  constexpr int64_t LO = woff(2), HI = NPARAM - LO, MOST = 256;
+  const int64_t scratch = 2 * int64_t(B) * NH, tiles = (int64_t(B) + BWD_ROWS - 1) / BWD_ROWS;
+  if (scratch < HI + 2 * LO) return {1, 1, 1, 0, 0, 0, 0};
+  if (scratch / NPARAM >= SPLIT_BELOW) {
+    const int nb = int(std::min({scratch / NPARAM, tiles, MOST}));
+    return {0, nb, nb, 0, NPARAM, 0, NPARAM};
+  }
+  const int64_t nhi = std::min({2 * scratch / (2 * HI + 3 * LO), tiles, 2 * MOST / 5});
+  const int64_t nlo = std::min({(scratch - nhi * HI) / LO, tiles, MOST - nhi});
+  return {1, int(nhi), int(nlo), -LO, HI, nhi * HI, LO};
+}
+
 extern "C" fo_status fo_mlp_backward(const float *P, const float *X, int32_t B, const float *acts, const float *dY,
                                      float *dacts, float *G, void *stream) {
   if (!P || !X || !acts || !dY || !dacts || !G || B < 0) return fail(FO_EINVAL, "fo_mlp_backward: bad argument");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // as many blocks as the scratch holds gradients (2 B NH floats), at most one per row tile and
-  // per compute unit
-  const int tiles = int((int64_t(B) + BWD_ROWS - 1) / BWD_ROWS);
-  int64_t nb = 2 * int64_t(B) * NH / NPARAM;
-  if (nb > tiles) nb = tiles;
-  if (nb > 256) nb = 256;
-  if (nb < 1) nb = 1;
-  hipLaunchKernelGGL(mlp_backward_kernel, dim3(unsigned(nb)), dim3(MLP_THREADS), 0, s, P, X, B, acts, dY,
-                     nb > 1 ? dacts : G);
+  const BackwardPlan L = backward_plan(B);
+  const bool direct = L.hi_blocks == 1 && L.lo_blocks == 1;   // no sums to add: the gradients themselves
+  hipLaunchKernelGGL(mlp_backward_kernel, dim3(unsigned(L.split ? L.hi_blocks + L.lo_blocks : L.hi_blocks)),
+                     dim3(MLP_THREADS), 0, s, P, X, B, acts, dY, direct ? G : dacts, L);
   FO_LAUNCH_CHECK("mlp_backward_kernel");
-  if (nb > 1) {
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 63) / 64), dim3(256), 0, s, int(nb), dacts, G);
+  if (!direct) {
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((NPARAM + 63) / 64), dim3(256), 0, s, L, dacts, G);
     FO_LAUNCH_CHECK("mlp_reduce_kernel");
   }
   return FO_OK;

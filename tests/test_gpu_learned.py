@@ -286,3 +286,10 @@ def test_features_and_shallow_ice_around_many_cells(n_cells, L):
     np.testing.assert_array_equal(F[:, 4:], Fo[:, 4:].astype(np.float32))
     U, Uo = M.sia().cpu().numpy(), solve.sia_guess(m)
     assert np.abs(U - Uo).max() <= 1e-12 * np.abs(Uo).max()
+
+
+@pytest.mark.parametrize("B", [215, 216, 1024, 27952, 27953])
+def test_backward_plans_match_reference(B):
+    """Row counts where the gradients' blocks change: one block for each half of the layers straight
+    into the gradients (to 215 rows), several for each half (to 27952), blocks of all layers."""
+    test_batch_sizes_at_tile_edges_match_reference(B)
