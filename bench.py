@@ -41,7 +41,7 @@ FP64_VALU_PEAK_TFLOPS = 78.6   # MI355X FP64 vector, vendor figure (256 CUs x 12
 FLOPS_PER_WEDGE = 4600.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "assemble_icesheet_traffic.json")
 KERNEL_SRC = os.path.join(ROOT, "paper_2204_04321_amd", "csrc", "fo_assemble.hip")
-KERNEL_NAME = "owner_kernel<wedge, Jacobian, JT, n=3>"
+KERNEL_NAME = "prism_owner_kernel<Jacobian, JT, n=3>"
 
 
 def algorithmic_bytes(m, nnz: int, jac_bytes: int = 8) -> int:
@@ -200,7 +200,7 @@ def ensemble_bench(args):
                    "members_cells_max": max(M.n_cells for M in meshes)},
         "roofline": {"bound": "hbm", "achieved": alg / (ms / 1e3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": alg / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "ensemble_kernel (whole step)", "algorithmic_bytes": alg},
+                     "kernel": "prism_ensemble_kernel (whole step)", "algorithmic_bytes": alg},
     }
     print(json.dumps(out))
 
