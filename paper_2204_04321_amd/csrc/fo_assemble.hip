@@ -310,8 +310,8 @@ __device__ __forceinline__ float quad_xor(float v) {
 //
 // With a Jacobian it is bound by FP64 issue and the LDS adds alike (ice sheet of 125,000 columns of
 // 10 layers: vector units 76% busy while two waves share a SIMD, the LDS 66% of the kernel's
-// time); the residual alone, four waves per SIMD, by vector issue.  R+J 705 -> 574 us in FP64 and
-// 670 -> 528 us with FP32 values, residual 180 -> 173 us, against one lane per item.  The parts:
+// time); the residual alone, four waves per SIMD, by vector issue.  R+J 705 -> 551-575 us in FP64 and
+// 670 -> 519 us with FP32 values, residual 175-180 -> 152 us, against one lane per item.  The parts:
 // the split itself, with the constants in LDS, -7%; items of one vertex spread over the wave
 // (below) -5%; sigma through scalar loads and the wait before the copy-out -2%; the copy-out of a
 // level in one piece -6%.  Carrying the shared entries in FP64 too spills (+5%).
@@ -513,7 +513,11 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
       f0 = f1;
       const double gx = ds * c_[GRAV], gy = ds * c_[GRAV + 1], lx0 = c_[LX], ly0 = c_[LY];
       AT S[2][4][2], B[2][4][3];     // sums of L (x, y) and, per triangle point, of L . p (signed by the lane)
-      double Rl[2][2] = {{l0 * gx, l0 * gy}, {l1 * gx, l1 * gy}};
+      // The gradient of level a's basis function is l_a (lx, ly, 0) -+ lam (px, py, iz): the residual's
+      // sums are those of the two parts (h, p), not of the two levels.  Both kernels sum alike, so
+      // their residuals are the same bits (residual alone 166 -> 152 us; with the Jacobian, whose rows
+      // need both levels, as long as before: 552 and 551, in an ensemble 455 and 458).
+      double RH[2] = {gx, gy}, RP[2] = {0.0, 0.0};
 #pragma unroll
       for (int tp = 0; tp < 3; ++tp) {
         const double iz = c_[INVH + tp] * ids, W = c_[WH + tp] * ds, lam_a = tp == 0 ? 2.0 / 3.0 : 1.0 / 6.0;
@@ -521,30 +525,41 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
         const double px = -zxs * iz, py = -zys * iz;        // d zeta / dx, d zeta / dy
         const double ux = fma(px, dum, ucx), uy = fma(py, dum, ucy);
         const double vx = fma(px, dvm, vcx), vy = fma(py, dvm, vcy);
-        const double exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = 0.5 * (iz * dum), eyz = 0.5 * (iz * dvm);
+        const double hz = 0.5 * iz, exx = ux, eyy = vy, exy = 0.5 * (uy + vx), exz = hz * dum, eyz = hz * dvm;
         const double qe = fma(exx, exx, fma(eyy, exx + eyy, fma(exy, exy, fma(exz, exz, fma(eyz, eyz, m.eps0_sq)))));
-        // 2 mu W, and 2 mu' W = 2 visc_exp mu W / q; for n = 3, mu is q^(-1/3) and 1/q its cube
+        // s2 = 2 mu W and t2 = mu' / mu = visc_exp / q; for n = 3, mu is q^(-1/3) and 1/q its cube
         double s2, t2;
         if constexpr (N3) {
           const double y = rcbrt64(qe);
           s2 = y * W;
-          t2 = (s2 * tfac) * (y * y * y);
+          t2 = tfac * (y * y * y);
         } else {
           s2 = powq(qe, m.visc_exp) * W;
-          t2 = (s2 * tfac) * rcp64(qe);
+          t2 = tfac * rcp64(qe);
         }
         const double E1x = 2.0 * exx + eyy, E2y = exx + 2.0 * eyy;
-        const AT spx = AT(flip(px, minus)), spy = AT(flip(py, minus)), spz = AT(flip(iz, minus));
+        const double mx = flip(px, minus), my = flip(py, minus), mz = flip(iz, minus);
+        const AT spx = AT(mx), spy = AT(my), spz = AT(mz);
         const AT e1x = AT(E1x), e1y = AT(exy), e2y = AT(E2y), e1z = AT(exz), e2z = AT(eyz), half = AT(0.5);
+        const double hX = s2 * lx0, hY = s2 * ly0, s2l = s2 * lam_a;
+        const double h0 = fma(E1x, hX, exy * hY), h1 = fma(exy, hX, E2y * hY);
+        const double p0 = s2l * fma(E1x, px, fma(exy, py, exz * iz)), p1 = s2l * fma(exy, px, fma(E2y, py, eyz * iz));
+        RH[0] += h0;
+        RH[1] += h1;
+        RP[0] += p0;
+        RP[1] += p1;
+        if constexpr (JAC) {
+          // the part of A along p for either level: formed once where registers allow (the sums of
+          // FP32 values take half of theirs), else from the lane-signed p that B reads
+          constexpr bool KEPT = sizeof(AT) == 4;
+          const double qX = s2l * px, qY = s2l * py, qZ = s2l * iz, s2m = flip(s2l, minus);
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
-          const double l = a ? l1 : l0, la = a ? lam_a : -lam_a;
-          const double ax = fma(l, lx0, la * px), ay = fma(l, ly0, la * py), az = la * iz;
-          const double g0 = E1x * ax + exy * ay + exz * az, g1 = exy * ax + E2y * ay + eyz * az;
-          Rl[a][0] = fma(s2, g0, Rl[a][0]);
-          Rl[a][1] = fma(s2, g1, Rl[a][1]);
-          if constexpr (JAC) {
-            const AT Ax = AT(s2 * ax), Ay = AT(s2 * ay), Az = AT(s2 * az), T0 = AT(t2 * g0), T1 = AT(t2 * g1);
+          for (int a = 0; a < 2; ++a) {
+            const double l = a ? l1 : l0, sm = a ? s2m : -s2m;
+            const AT Ax = AT(KEPT ? fma(l, hX, a ? qX : -qX) : fma(sm, mx, l * hX));
+            const AT Ay = AT(KEPT ? fma(l, hY, a ? qY : -qY) : fma(sm, my, l * hY));
+            const AT Az = AT(KEPT ? (a ? qZ : -qZ) : sm * mz);
+            const AT T0 = AT(t2 * fma(l, h0, a ? p0 : -p0)), T1 = AT(t2 * fma(l, h1, a ? p1 : -p1));
             const AT hAx = half * Ax, hAy = half * Ay, hAz = half * Az;
             // L for uu, uv, vu, vv: coefficients of (bx, by, bz) in d R_(a,c) / d U_(b,d)
             const AT Lx[4] = {fma(T0, e1x, Ax + Ax), fma(T0, e1y, hAy), fma(T1, e1x, Ay), fma(T1, e1y, hAx)};
@@ -562,8 +577,9 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
       __builtin_amdgcn_s_setprio(1);
       // residual: lane z ends with row node z
       {
-        const double k0_ = z ? Rl[1][0] : Rl[0][0], k1_ = z ? Rl[1][1] : Rl[0][1];
-        const double s0_ = z ? Rl[0][0] : Rl[1][0], s1_ = z ? Rl[0][1] : Rl[1][1];
+        const double p0 = flip(RP[0], minus), p1 = flip(RP[1], minus);
+        const double k0_ = fma(G2, RH[0], p0), k1_ = fma(G2, RH[1], p1);
+        const double s0_ = fma(G1, RH[0], -p0), s1_ = fma(G1, RH[1], -p1);
         const double r0 = k0_ + quad_xor<1>(s0_), r1 = k1_ + quad_xor<1>(s1_);
         if (act) {
           double *r = Rw + (z ? nxt : cur) * 2 * max_tv + rloc;
