@@ -613,12 +613,12 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
               const AT h = fma(hx[j], S[a][cd][0], hy[j] * S[a][cd][1]);
               const AT lb = fma(half, B[a][cd][j], bm);
               e[j] = fma(lkept, h, a ? -lb : lb) + quad_xor<1>(fma(lsent, h, a ? lb : -lb));
-              if (CARRY && a == 0) e[j] += carry[cd][j];
             }
             const int off = (cd >> 1) * 2 * nl * Dv + (cd & 1);
             if (add) {
 #pragma unroll
-              for (int j = 0; j < 3; ++j) lds_add(wj[j] + off, double(e[j]));
+              for (int j = 0; j < 3; ++j)     // cells are summed in FP64
+                lds_add(wj[j] + off, CARRY && a == 0 ? double(e[j]) + double(carry[cd][j]) : double(e[j]));
             }
             if (CARRY && a == 1) {
 #pragma unroll

@@ -488,3 +488,30 @@ def test_single_mesh_beyond_int32_offsets():
     assert rep["status"] == 0 and rep["final_rel"] <= 1e-8
     P.close()
     M.close()
+
+
+@pytest.mark.parametrize("L", [2, 3])
+def test_fp32_entries_are_summed_in_fp64(L):
+    """FP32 values are sums over cells formed in FP64 and rounded once.  Two triangles mirrored about
+    their common edge, ice at rest in the bottom layer (viscosity at its cap) and sheared above it
+    (viscosity 5e6 times lower): the bottom layer's entries (u, v) of the edge's nodes at the level
+    between cancel exactly (all lengths are powers of two, so both triangles' are the same FP32
+    numbers of opposite sign), and what is left are the sheared layer's, 1e-7 of them.  A sum of two layers
+    in FP32 would keep none of their digits.  Bar: the rounding of the two sheared cells' own FP32
+    derivatives, some 20 operations of 2^-24 each, on terms ten times what is left: 2^-15 holds 512."""
+    xy = np.array([[0.0, 0.0], [0.0, 1024.0], [1024.0, 512.0], [-1024.0, 512.0]])
+    cells = np.array([[0, 2, 1], [0, 1, 3]], dtype=np.int32)
+    H = np.full(4, 1024.0 * L)
+    m = ExtrudedMesh("wedge", xy, cells, H.copy(), H, np.zeros(4), np.arange(L + 1) / L, A=1e-16)
+    U = np.zeros((4, L + 1, 2))
+    U[:, 2:, 0], U[:, 2:, 1] = 1024.0, 512.0
+    M = gpu_mesh(m)
+    J64, J32 = (gpu_jacobian(M, U.reshape(-1), dtype)[1].toarray() for dtype in ("f64", "f32"))
+    for v in (0, 1):
+        at = 2 * (v * (L + 1) + 1)
+        for w in (0, 1):
+            col = 2 * (w * (L + 1) + 1)
+            for r, c in ((at, col + 1), (at + 1, col)):
+                want, got = J64[r, c], J32[r, c]
+                print(f"[fp32 sums] L={L} ({v},{w}) J64 {want:.9e} J32 {got:.9e}", flush=True)
+                assert want != 0.0 and abs(got - want) <= 2.0 ** -15 * abs(want)
