@@ -421,17 +421,23 @@ __device__ __forceinline__ void dot_pass(int64_t n2, const double *__restrict__ 
                                          const double *__restrict__ w, int i0, double (&s)[MD_GROUP]) {
   const int64_t stride = int64_t(gridDim.x) * RED_BLOCK;
   const double2 *w2 = reinterpret_cast<const double2 *>(w);
-  for (int64_t p = int64_t(blockIdx.x) * RED_BLOCK + threadIdx.x; p < n2; p += 2 * stride) {
-    const bool two = p + stride < n2;
-    const int64_t p1 = two ? p + stride : p;
-    const double2 wp = w2[p];
-    double2 wq = w2[p1];
-    if (!two) wq = make_double2(0.0, 0.0);
+  auto vec = [&](int q) { return reinterpret_cast<const double2 *>(i0 + q < nv ? V + int64_t(i0 + q) * ld : w); };
+  int64_t p = int64_t(blockIdx.x) * RED_BLOCK + threadIdx.x;
+  for (; p + stride < n2; p += 2 * stride) {
+    const double2 wp = w2[p], wq = w2[p + stride];
 #pragma unroll
     for (int q = 0; q < G; ++q) {
-      const double2 *Vi = reinterpret_cast<const double2 *>(i0 + q < nv ? V + int64_t(i0 + q) * ld : w);
-      const double2 a = Vi[p], b = Vi[p1];
+      const double2 *Vi = vec(q);
+      const double2 a = Vi[p], b = Vi[p + stride];
       s[q] = fma(a.x, wp.x, fma(a.y, wp.y, fma(b.x, wq.x, fma(b.y, wq.y, s[q]))));
+    }
+  }
+  if (p < n2) {     // no second place: its products are left out, not multiplied by zero (infinite entries)
+    const double2 wp = w2[p];
+#pragma unroll
+    for (int q = 0; q < G; ++q) {
+      const double2 a = vec(q)[p];
+      s[q] = fma(a.x, wp.x, fma(a.y, wp.y, s[q]));
     }
   }
 }

@@ -198,3 +198,18 @@ def test_newton_on_few_columns(n_points, L):
     rep = M.newton_solve(U, tol=1e-8, max_lin=3000)
     assert rep["status"] == 0 and rep["final_rel"] <= 1e-8
     assert np.abs(U.cpu().numpy() - U_ref).max() <= 1e-6 * np.abs(U_ref).max()
+
+
+def test_infinite_residual_norm_is_reported():
+    """A finite velocity whose residual overflows at some dofs: the norm is infinite, not undefined, and
+    the solve stops with FO_ENONFINITE, wherever among the dofs the overflow lies."""
+    from paper_2204_04321_amd import _lib
+    m = _cap(n_points=40, L=2)
+    m = m.with_fields(beta=np.full(m.xy.shape[0], 1e300))
+    M = gpu_mesh(m)
+    for v in (0, m.xy.shape[0] // 2, m.xy.shape[0] - 1):
+        U = np.zeros((m.xy.shape[0], 3, 2))
+        U[v, 0, 0] = 1e10
+        rep = M.newton_solve(to_dev(U.reshape(-1)), tol=1e-8)
+        assert rep["status"] == _lib.FO_ENONFINITE
+        assert np.isfinite(rep["f0_norm"]) and np.isposinf(rep["final_norm"]) and np.isposinf(rep["final_rel"]), (v, rep)
