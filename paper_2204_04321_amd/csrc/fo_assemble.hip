@@ -320,7 +320,7 @@ constexpr int PRISM_CONST = 18;         // FP64 constants of an item (144 bytes:
 constexpr int PRISM_ITEMS = WAVE / 2;   // items per pass of a wave
 
 // The levels kb <= k < ke of a task's columns (and level L if ke = L).  kb > 0 starts with layer
-// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: a task may hold
+// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: the task holds
 // more items than one pass of a wave takes (a vertex in more cells than that is a task of its
 // own), so the item constants are reloaded for every layer and pass.
 template <bool JAC, class JT, bool N3, bool PASSES>
@@ -665,7 +665,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
 constexpr int HEX_ITEMS = WAVE / 4;   // items per pass of a wave
 
 // The levels kb <= k < ke of a task's columns (and level L if ke = L).  kb > 0 starts with layer
-// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: a task may hold
+// kb - 1, whose lower rows belong to the range below and are dropped.  PASSES: the task holds
 // more items than one pass of a wave takes (a vertex in more cells than that is a task of its
 // own), so the item constants are reloaded for every layer and pass.
 template <bool JAC, class JT, bool N3, bool PASSES>
@@ -1231,6 +1231,31 @@ __device__ __forceinline__ void tet_task(const MeshView &m, const int4 task, con
   }
 }
 
+// A task by its kind: only one that holds more items than a pass takes walks them in passes, so a vertex
+// in many cells costs its own task alone, and a task's bits do not depend on the others in the launch.
+// PASSES: the launch has such tasks (kernels without them do not carry their code).  Ice sheet of
+// 125,000 columns and one vertex in 40 triangles: R+J 742 us in FP64, 722 with FP32 values, residual
+// 277 with all tasks in passes; 606, 559 and 172 so (without that vertex 591, 522 and 164).
+template <bool JAC, class JT, bool N3, bool PASSES>
+__device__ __forceinline__ void any_prism_task(const MeshView &m, const int4 task, const double *__restrict__ U,
+                                               double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
+                                               int max_tv, int kb, int ke, unsigned char *smem) {
+  if (PASSES && __builtin_amdgcn_readfirstlane(m.vc_ptr[task.z] - task.w) > PRISM_ITEMS)
+    prism_task<JAC, JT, N3, true>(m, task, U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+  else
+    prism_task<JAC, JT, N3, false>(m, task, U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+}
+
+template <bool JAC, class JT, bool N3, bool PASSES>
+__device__ __forceinline__ void any_hex_task(const MeshView &m, const int4 task, const double *__restrict__ U,
+                                             double *__restrict__ R, JT *__restrict__ J, int picard, int max_slot,
+                                             int max_tv, int kb, int ke, unsigned char *smem) {
+  if (PASSES && __builtin_amdgcn_readfirstlane(m.vc_ptr[task.z] - task.w) > HEX_ITEMS)
+    hex_task<JAC, JT, N3, true>(m, task, U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+  else
+    hex_task<JAC, JT, N3, false>(m, task, U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+}
+
 // Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
 template <bool JAC, class JT, bool N3, bool PASSES>
 __global__ __launch_bounds__(WAVE, PRISM_WAVES) void prism_owner_kernel(MeshView m, const int4 *__restrict__ tasks, int lpc,
@@ -1239,7 +1264,7 @@ __global__ __launch_bounds__(WAVE, PRISM_WAVES) void prism_owner_kernel(MeshView
                                                               int max_tv) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
-  prism_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+  any_prism_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
 }
 
 // Block (x, y): task x, levels y lpc .. (y + 1) lpc - 1 of its columns
@@ -1250,7 +1275,7 @@ __global__ __launch_bounds__(WAVE, 2) void hex_owner_kernel(MeshView m, const in
                                                             int max_tv) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int kb = int(blockIdx.y) * lpc, ke = kb + lpc < m.L ? kb + lpc : m.L;
-  hex_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
+  any_hex_task<JAC, JT, N3, PASSES>(m, tasks[blockIdx.x], U, R, J, picard, max_slot, max_tv, kb, ke, smem);
 }
 
 template <bool JAC, class JT, bool N3>
@@ -1297,8 +1322,8 @@ __global__ __launch_bounds__(WAVE, PRISM_WAVES) void prism_ensemble_kernel(const
                                                                  int *__restrict__ counter, int picard) {
   extern __shared__ __align__(16) unsigned char smem[];
   ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
-    prism_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0,
-                            e.view.L, smem);
+    any_prism_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv,
+                                        0, e.view.L, smem);
   });
 }
 
@@ -1308,8 +1333,8 @@ __global__ __launch_bounds__(WAVE, 2) void hex_ensemble_kernel(const EnsembleMem
                                                                int *__restrict__ counter, int picard) {
   extern __shared__ __align__(16) unsigned char smem[];
   ensemble_loop(mem, tasks, n_tasks, counter, [&](const EnsembleMember &e, const int4 task) {
-    hex_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0, e.view.L,
-                          smem);
+    any_hex_task<JAC, JT, N3, PASSES>(e.view, task, e.U, e.R, static_cast<JT *>(e.J), picard, e.max_slot, e.max_tv, 0,
+                                      e.view.L, smem);
   });
 }
 
@@ -1410,7 +1435,7 @@ fo_status launch_ens_t(const EnsembleLaunch &E, int kind, hipStream_t s) {
   return FO_OK;
 }
 
-// Calls f<cell, jac, value type, n = 3, several passes> for the run-time choices
+// Calls f<cell, jac, value type, n = 3, tasks of several passes> for the run-time choices
 template <class F>
 fo_status by_kernel(int nv, bool tet, bool want_jac, int dtype, bool n3, bool passes, F f) {
   auto by_pass = [&](auto c, auto jac, auto val, auto n) {

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from fo_inputs import ensemble_member
+from fo_inputs.meshgen import ExtrudedMesh
 from oracle import fo_oracle as fo
 
 from gpu_util import gpu_jacobian, gpu_mesh, parity_errors, to_dev
@@ -204,3 +205,47 @@ def test_full_size_64_member_ensemble():
     torch.cuda.empty_cache()
     for i in (small, large):
         _full_mesh_parity(functools.partial(ensemble_member, i), f"member{i}")
+
+
+def _mirrored_pair():
+    """Two triangles mirrored about their common edge, ice at rest below a layer sheared a thousand
+    million times faster than ice flows: entries of the lower layer cancel and leave the upper one's, so
+    sums taken in another order differ in all digits of a value."""
+    xy = np.array([[0.0, 0.0], [0.0, 1024.0], [1024.0, 512.0], [-1024.0, 512.0]])
+    m = ExtrudedMesh("wedge", xy, np.array([[0, 2, 1], [0, 1, 3]], dtype=np.int32), np.full(4, 2048.0),
+                     np.full(4, 2048.0), np.zeros(4), np.array([0.0, 0.5, 1.0]), A=1e-16)
+    U = np.zeros((4, 3, 2))
+    U[:, 2] = 1e12, 5e11
+    return m, U.reshape(-1)
+
+
+MANY_CELLS = {
+    "wedge": lambda a: [a._fan(64, 4, 8), a._box(9, 7, 4, "wedge", 21), _mirrored_pair(), a._fan(33, 3, 9),
+                        a._box(6, 5, 13, "wedge", 22)],
+    "hex": lambda a: [a._quad_fan(44, 2, 32), a._box(7, 5, 3, "hex", 23), a._quad_fan(16, 5, 33)],
+}
+
+
+@pytest.mark.parametrize("n", [3.0, 2.5])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("elem", sorted(MANY_CELLS))
+def test_members_with_a_vertex_in_many_cells(elem, dtype, n):
+    """Members around a vertex whose cells take several passes of a wave (more than 32 triangles, 16
+    quadrilaterals) beside members that take one: each equals its own single-mesh calls bit for bit."""
+    import test_gpu_assembly as a
+    from paper_2204_04321_amd.api import Ensemble
+    descs = [(m if n == 3.0 else m.with_fields(n=n, A=1e-14), U) for m, U in MANY_CELLS[elem](a)]
+    Ms = [gpu_mesh(m) for m, _ in descs]
+    E = Ensemble(Ms)
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    Us = [to_dev(U) for _, U in descs]
+    Rs = [torch.full((M.n_dofs,), float("nan"), dtype=torch.float64, device="cuda") for M in Ms]
+    Js = [torch.full((M.nnz,), float("nan"), dtype=tdt, device="cuda") for M in Ms]
+    for kind in ("newton", "picard"):
+        E.assemble(Us, Rs, Js, dtype=dtype, kind=kind)
+        torch.cuda.synchronize()
+        for i, (M, Ud, R, J) in enumerate(zip(Ms, Us, Rs, Js)):
+            R1, J1 = M.jacobian(Ud, dtype=dtype, kind=kind)
+            torch.cuda.synchronize()
+            assert torch.equal(R, R1) and torch.equal(R, M.residual(Ud)), (kind, i)
+            assert torch.equal(J, J1), (kind, i, int((J != J1).sum()))
