@@ -169,9 +169,8 @@ fo_status gmres(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b
         if (pass == 0 && ahead && (st = product(j + 1)) != FO_OK) return st;
         if ((st = wait_dots(c)) != FO_OK) return st;
         for (int i = 0; i <= j; ++i) hsum[i] = (pass == 0 ? 0.0 : hsum[i]) + c.host[i];
-        const double scale = c.host[j + 2];      // 1 / ||w|| after this projection, 0 for a zero vector
-        H[size_t(j + 1) * mres + j] = scale > 0.0 ? 1.0 / scale : scale;
-        if (scale != 1.0) break;                 // 1: left unscaled for the second pass
+        H[size_t(j + 1) * mres + j] = projected_norm(c.host, j + 1);
+        if (c.host[j + 2] != 1.0) break;         // 1: left unscaled for the second pass
         ahead = false;                           // V_(j+1) changes once more
       }
       for (int i = 0; i <= j; ++i) H[size_t(i) * mres + j] = hsum[i];
@@ -288,6 +287,15 @@ fo_status pcg(Ctx &c, const fo_newton_opts *o, const void *Jv, const double *b, 
 }
 
 }  // namespace
+
+double projected_norm(const double *out, int nv) {
+  double h2 = 0.0;
+  for (int i = 0; i < nv; ++i) h2 += out[i] * out[i];
+  const double left = out[nv] - h2, scale = out[nv + 1];
+  if (std::isinf(left) && left > 0.0) return left;
+  return scale > 0.0 ? 1.0 / scale : 0.0;
+}
+
 }  // namespace fo
 
 using namespace fo;

@@ -24,6 +24,9 @@ int multidot_blocks(int64_t n);
 constexpr int kDotsMax = 504, kDotsFlag = kDotsMax;
 fo_status multidot(int64_t n, const double *V, int64_t ld, int nv, const double *w, double *partial,
                    double *out, double drop, double *host, uint64_t seq, hipStream_t s);
+// ||w - V h|| from what multidot wrote for nv vectors: 0 where its square is not positive, infinite where
+// the square overflowed (the device's scale is 0 there too)
+double projected_norm(const double *out, int nv);
 int dot2_blocks(int64_t n);
 // out[0] = a . w, out[1] = w . w (partial: 2 dot2_blocks(n) doubles; n even, FO_EINVAL otherwise)
 fo_status dot2(int64_t n, const double *a, const double *w, double *partial, double *out, hipStream_t s);

@@ -153,3 +153,19 @@ def test_plain_c_caller(tmp_path):
     assert f"linear solver 0, opts size {ctypes.sizeof(_lib.NewtonOpts)}" in p.stdout
     assert f"report size {ctypes.sizeof(_lib.NewtonReport)}" in p.stdout
     assert o.learned_fallback == 1 and o.learned_smooth == 0 and not o.mlp_params
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="library not built")
+def test_norm_of_a_projected_vector_reports_overflow():
+    """What the Krylov solver takes as the norm after a projection, from the dot products h, w . w and
+    the device's scale 1 / ||w - V h|| (0 where w . w - |h|^2 is not a positive number, infinite or not).
+    An overflowed square gives an infinite norm, on which the solve stops with FO_ENONFINITE; it is not
+    the norm 0 of an exhausted Krylov space."""
+    norm = ctypes.CDLL(LIB)._ZN2fo14projected_normEPKdi
+    norm.restype, norm.argtypes = ctypes.c_double, [ctypes.POINTER(ctypes.c_double), ctypes.c_int]
+    inf, nan = float("inf"), float("nan")
+    for h, ww, scale, want in (([3.0, 0.0], 25.0, 0.25, 4.0), ([3.0, 4.0], 25.0, 0.0, 0.0), ([], 16.0, 0.25, 4.0),
+                               ([1e150, -2e140], inf, 0.0, inf), ([], inf, 0.0, inf), ([1.0], nan, 0.0, 0.0),
+                               ([1e200], inf, 0.0, 0.0), ([1e200], 1.0, 0.0, 0.0)):
+        out = (ctypes.c_double * (len(h) + 2))(*h, ww, scale)
+        assert norm(out, len(h)) == want, (h, ww, scale)
