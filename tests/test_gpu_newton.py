@@ -213,3 +213,36 @@ def test_infinite_residual_norm_is_reported():
         rep = M.newton_solve(to_dev(U.reshape(-1)), tol=1e-8)
         assert rep["status"] == _lib.FO_ENONFINITE
         assert np.isfinite(rep["f0_norm"]) and np.isposinf(rep["final_norm"]) and np.isposinf(rep["final_rel"]), (v, rep)
+
+
+@pytest.mark.parametrize("max_lin", [16, 20])
+def test_gmres_on_an_exhausted_krylov_space(max_lin):
+    """As many Krylov vectors as there are unknowns, and more: the projections leave rounding only, so
+    they are repeated (each on a vector that the next product had been started from), and the last
+    vectors add nothing to the solution.  The bar of test_newton_matches_oracle_solution."""
+    xy = np.array([[0.0, 0.0], [4e3, 0.0], [4.2e3, 3.9e3], [-0.2e3, 4.1e3]])
+    H = np.array([900.0, 800.0, 850.0, 950.0])
+    m = ExtrudedMesh("wedge", xy, np.array([[0, 1, 2], [0, 2, 3]], dtype=np.int32), H + 0.02 * (xy[:, 1] - xy[:, 0]), H,
+                     np.array([500.0, 600.0, 700.0, 800.0]), np.array([0.0, 1.0]), A=1e-16)
+    U_ref, info = solve.newton_solve(m, solve.sia_guess(m), tol=1e-11)
+    assert info["status"] == "converged"
+    U = to_dev(solve.sia_guess(m))
+    rep = gpu_mesh(m).newton_solve(U, tol=1e-10, lin_rtol=1e-16, max_lin=max_lin, gmres_restart=50)
+    print(f"\n[exhausted] {rep['newton_its']} Newton, {rep['lin_its']} linear its, {rep['final_rel']:.1e}")
+    assert rep["status"] == 0 and rep["lin_its"] >= 14 * rep["newton_its"]
+    assert np.abs(U.cpu().numpy() - U_ref).max() <= 1e-6 * np.abs(U_ref).max()
+
+
+@pytest.mark.parametrize("n_points,L", [(60, 256), (60, 300)])
+def test_newton_on_few_tall_columns(n_points, L):
+    """Columns of more than 256 levels, whose factors do not fit LDS four columns at a time: the
+    preconditioner's apply reads them from memory on a small mesh too, with the columns of a block bounded by
+    LDS (15 and 13 by their bytes, so 8).  The bar of test_newton_matches_oracle_solution.  (On fewer
+    points the oracle's own residual stops at rounding above the 1e-11 asked of it.)"""
+    m = _cap(n_points=n_points, L=L)
+    U_ref, info = solve.newton_solve(m, solve.sia_guess(m), tol=1e-11)
+    assert info["status"] == "converged"
+    U = to_dev(solve.sia_guess(m))
+    rep = gpu_mesh(m).newton_solve(U, tol=1e-8, max_lin=3000)
+    assert rep["status"] == 0 and rep["final_rel"] <= 1e-8
+    assert np.abs(U.cpu().numpy() - U_ref).max() <= 1e-6 * np.abs(U_ref).max()
