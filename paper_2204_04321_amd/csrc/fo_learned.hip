@@ -654,19 +654,21 @@ extern "C" fo_status fo_adam_step(float *P, const float *G, float *Mom, float *V
 namespace {
 constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
-struct LLayout { size_t F, acts, Y, Us, R, D, partial, dots, flag, total; };
+struct LLayout { size_t F, partial, Y, Us, R, D, dots, flag, total; };
 LLayout llayout(const fo_mesh *m) {
   const size_t V = size_t(m->view.V), n = size_t(m->view.n_dofs);
   LLayout L{};
   size_t off = 0;
   auto take = [&](size_t b) { size_t a = off; off += up(b); return a; };
   L.F = take(4 * V * NIN);
-  L.acts = take(4 * 3 * V * NH);
+  // The dot products' partial sums: 8 multidot_blocks(n) bytes, at most 4 KB, where 4.5 KB lie here from
+  // three vertices on.  The rest of the region is not used (inference stores no activations); its size is
+  // part of the total that callers were told, and of the limit of the variant without a workspace.
+  L.partial = take(up(4 * 3 * V * NH) + 8 * std::min<size_t>(std::max<size_t>((n + 4095) / 4096, 1), 512));
   L.Y = take(4 * V * NOUT);
   L.Us = take(8 * n);
   L.R = take(8 * n);
   L.D = take(8 * 2 * n);
-  L.partial = take(8 * size_t(std::min<int64_t>(std::max<int64_t>((int64_t(n) + 4095) / 4096, 1), 512)));
   L.dots = take(16);
   L.flag = take(16);
   L.total = off;
@@ -693,9 +695,7 @@ fo_status learned_guess(const fo_mesh *m, const float *P, const float *norm, dou
   float *Y = reinterpret_cast<float *>(w + L.Y);
   double *Us = reinterpret_cast<double *>(w + L.Us), *R = reinterpret_cast<double *>(w + L.R);
   double *D0 = reinterpret_cast<double *>(w + L.D);
-  // The dot products' partial sums (up to 512) lie where a training pass keeps its activations, which
-  // inference does not store; the layout's sizes are part of what callers were told and stay.
-  double *part = reinterpret_cast<double *>(w + L.acts), *dots = reinterpret_cast<double *>(w + L.dots);
+  double *part = reinterpret_cast<double *>(w + L.partial), *dots = reinterpret_cast<double *>(w + L.dots);
   int *flag = reinterpret_cast<int *>(w + L.flag);
   const int V = m->view.V;
   const int64_t n = m->view.n_dofs;

@@ -293,3 +293,23 @@ def test_backward_plans_match_reference(B):
     """Row counts where the gradients' blocks change: one block for each half of the layers straight
     into the gradients (to 215 rows), several for each half (to 27952), blocks of all layers."""
     test_batch_sizes_at_tile_edges_match_reference(B)
+
+
+def test_guess_in_the_smallest_workspace():
+    """One triangle's three columns, where the workspace is as small as it gets: with exactly the bytes
+    asked for, everything after them stays as it was and the guess is the one of a larger workspace."""
+    from fo_inputs.meshgen import ExtrudedMesh
+    from paper_2204_04321_amd import _lib
+    m = ExtrudedMesh("wedge", np.array([[0.0, 0.0], [3e3, 0.0], [1e3, 2.5e3]]), np.array([[0, 1, 2]], dtype=np.int32),
+                     np.array([900.0, 850.0, 880.0]), np.array([700.0, 720.0, 690.0]), np.array([500.0, 600.0, 550.0]),
+                     np.linspace(0, 1, 11), A=1e-16)
+    M = gpu_mesh(m)
+    need = int(_lib.lib().fo_learned_workspace_bytes(M.handle))
+    params = to_dev(_flat(ol.init_params(np.random.default_rng(2))), torch.float32)
+    norm = to_dev(np.concatenate([M.features().cpu().numpy().mean(0), np.ones(10)]), torch.float32)
+    ws = torch.full((need + 65536,), 165, dtype=torch.uint8, device="cuda")
+    U, used = M.learned_guess(params, norm, workspace=ws[:need], fallback=1)
+    U2, used2 = M.learned_guess(params, norm, fallback=1)
+    torch.cuda.synchronize()
+    assert used == used2 and torch.equal(U, U2) and bool(torch.isfinite(U).all())
+    assert bool((ws[need:] == 165).all())
