@@ -235,8 +235,9 @@ fo_status fo_newton_solve(const fo_mesh *mesh, double *U_dev, const fo_newton_op
  *                 transfers, Galerkin operators, Chebyshev over [g/30, g] on D^-1 A (D: 2x2
  *                 diagonal blocks, g: the Gershgorin bound max row sum of |D^-1 A|) before
  *                 and after the coarse correction, degree 2 on the first plane level and 1
- *                 below it, the coarsest level solved by its inverse (Gauss-Jordan with
- *                 partial pivoting);
+ *                 below it, the coarsest level solved by its inverse (Gauss-Jordan, the pivot
+ *                 within 2^-13 of the column's largest); levels of at most 512 vertices below
+ *                 the first are applied, with all below them, as one matrix formed at setup;
  *   application:  y = V-cycle(P0^T r), z = P0 y + B^-1 (r - J P0 y), with J P0 and the weights
  *                 of P0 and P0^T stored in FP32 (the plane operators are formed from the FP64
  *                 values; any stored precision leaves M a fixed linear operator).
@@ -251,7 +252,8 @@ fo_status fo_mdsc_aggregate_graph(int32_t n, const int32_t *ptr, const int32_t *
 
 /* Build the hierarchy's graphs, aggregates and transfer tables for a mesh (host work plus
  * device allocations: about (L+1)(2 nnz_plane + 15 V) doubles, nnz_plane the number of
- * ordered base-vertex pairs that share a cell, self pairs included).  The mesh's device must
+ * ordered base-vertex pairs that share a cell, self pairs included, and 4 n^2 doubles for a level
+ * of n <= 512 vertices that is applied as a matrix).  The mesh's device must
  * be current.  Synchronises `stream`. */
 fo_status fo_mdsc_create(const fo_mesh *mesh, void *stream, fo_mdsc **out);
 void fo_mdsc_destroy(fo_mdsc *p);

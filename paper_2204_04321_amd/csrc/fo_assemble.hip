@@ -654,9 +654,11 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
 // accumulators and ran one wave per SIMD with 40 of its 64 lanes busy, the window budget being
 // ten columns), and the horizontal map, gradients and the slopes of bed and thickness at a lane's
 // point are constants of the whole column.  Bound by FP64 issue: about 1000 vector instructions
-// a layer.  30,000 columns of 7 layers (210,000 hexahedra), FP64 R+J: 293 -> 132 us; 2000
-// hexahedra (with the levels split over blocks): 68 -> 12 us.  Compiled for three or four waves
-// per SIMD the column constants spill: 333 and 572 us.
+// a layer.  30,000 columns of 7 layers (210,000 hexahedra), FP64 R+J: 294 -> 121 us; 2000
+// hexahedra (with the levels split over blocks): 68 -> 10.6 us.  Compiled for three or four waves
+// per SIMD the column constants spill: 333 and 572 us.  For n != 3 the general power's constants
+// beside the velocities loaded ahead spill 47 registers (27 with FP32 values); with n = 2.5 the
+// 30,000 columns take 182 us (152), 340 (331) with one lane per item.
 //
 // Exchanges without selections: lane bits b0 = lane & 1, b1 = lane >> 1 & 1.  A lane forms the
 // entries at level b0 as "kept" and at the other level as "sent" (lane-constant weights l_b0 and
@@ -1376,7 +1378,9 @@ size_t window_bytes(bool jac, int max_slot, int max_tv) {
 // idle while each wave walks its columns layer by layer, so the levels are split over blocks; a
 // block that does not start at the bed repeats the layer below its first level.  The cost taken
 // here is the layers of a block (the repeated one included) times the rounds of `resident`
-// waves; results do not depend on the split (every level's sums keep their order).
+// waves; results do not depend on the split (every level's sums keep their order).  The residual-only
+// kernels hold more waves than `resident` says (prisms four on a SIMD, tetrahedra three), so
+// mid-sized meshes are split less for them than the chip would take.
 int layers_per_block(int64_t n_tasks, int L, int64_t resident) {
   int best = L;
   double best_cost = 0.0;
@@ -1392,7 +1396,7 @@ int layers_per_block(int64_t n_tasks, int L, int64_t resident) {
   return best;
 }
 
-constexpr int64_t RESIDENT = 2048;   // two waves on each of 1024 SIMDs
+constexpr int64_t RESIDENT = 2048;   // with a Jacobian, two waves on each of 1024 SIMDs
 
 template <Cell C, bool JAC, class JT, bool N3, bool PASSES>
 fo_status launch_t(const fo_mesh *mesh, const double *U, double *R, JT *J, int kind, hipStream_t s) {

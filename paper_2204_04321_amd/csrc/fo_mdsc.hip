@@ -25,7 +25,7 @@
 namespace fo {
 namespace {
 
-constexpr int NC_MAX = 2 * kMdscCoarsestMax;   // coarsest dofs held in LDS
+constexpr int NC_MAX = 2 * kMdscCoarsestMax;   // most coarsest dofs
 constexpr double CHEB_RATIO = 30.0;
 enum { FLAG_DIAG = 0, FLAG_COARSE = 1, N_FLAGS = 4 };
 // the flags, then the levels' bounds and smoothing coefficients: zeroed together before a setup
@@ -192,9 +192,9 @@ __device__ __forceinline__ void cheb_coeffs(PlaneCheb &c) {
 
 // Galerkin operator of unsmoothed aggregation: every coarse block is the sum of the fine
 // blocks listed for it.  GL lanes share a block, lane i taking every GL-th entry of the list, then
-// add their sums in a fixed order (and one forms the fine level's smoothing coefficients): the list's indices and the blocks they name are loads that wait
-// for each other, and one lane per block walked all of them (all levels of a 125,000-vertex plane:
-// 96 -> 31 us).
+// add their sums in a fixed order (and one forms the fine level's smoothing coefficients): the list's
+// indices and the blocks they name are loads that wait for each other, and one lane per block walked
+// all of them (all levels of a 125,000-vertex plane: 96 -> 31 us).
 __global__ __launch_bounds__(256) void galerkin_kernel(int nnz_c, const int32_t *__restrict__ gptr,
                                                        const int32_t *__restrict__ gidx, const double *__restrict__ Af,
                                                        double *__restrict__ Ac, PlaneCheb *__restrict__ ch) {
@@ -727,8 +727,8 @@ extern "C" fo_status fo_mdsc_create(const fo_mesh *m, void *stream, fo_mdsc **ou
   const size_t nodes = size_t(V) * size_t(L + 1);
   const int nc = 2 * p->lv[last].n;
   p->jp_count = size_t(2 * (L + 1)) * 2 * size_t(ptr[V]);
-  if (!upload(p->blk_row, blk_row, s) || !dev_alloc(p->fac, 12 * nodes) || !dev_alloc(p->W, 4 * nodes) || !dev_alloc(p->W32, 4 * nodes) || !dev_alloc(p->JP, p->jp_count) ||
-      !dev_alloc(p->lv[last].MT, size_t(nc) * nc))
+  if (!upload(p->blk_row, blk_row, s) || !dev_alloc(p->fac, 12 * nodes) || !dev_alloc(p->W, 4 * nodes) ||
+      !dev_alloc(p->W32, 4 * nodes) || !dev_alloc(p->JP, p->jp_count) || !dev_alloc(p->lv[last].MT, size_t(nc) * nc))
     return bail(FO_ENOMEM, "fo_mdsc_create: device allocation failed");
   if (hipHostMalloc(reinterpret_cast<void **>(&p->flag_host), sizeof(int32_t) * N_FLAGS) != hipSuccess)
     return bail(FO_ENOMEM, "fo_mdsc_create: pinned allocation failed");

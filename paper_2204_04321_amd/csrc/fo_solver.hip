@@ -725,8 +725,10 @@ fo_status colblock_apply_correction(const fo_mesh *mesh, const float *fac, const
   return FO_OK;
 }
 
-// One pair of entries per thread until two blocks sit on every compute unit: a solve of 44,000
-// dofs took 27 us with a block per 4096 entries (11 blocks), 6 us with 86 (and 2.75M: 102 us before, 85 us with all loads of a pass in flight).
+// One pair of entries per thread up to 512 blocks (registers leave one wave per SIMD, so those are two
+// rounds of the 256 compute units): a solve of 44,000 dofs took 27 us with a block per 4096 entries
+// (11 blocks), 6 us with 86.  2.75M dofs: 102 us before, 85 us with all loads of a pass in flight, which
+// is 5.7 TB/s.
 int multidot_blocks(int64_t n) {
   const int64_t g = (n / 2 + RED_BLOCK - 1) / RED_BLOCK;
   return int(g < 512 ? (g > 0 ? g : 1) : 512);
