@@ -535,7 +535,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
           t2 = tfac * (y * y * y);
         } else {
           s2 = powq(qe, m.visc_exp) * W;
-          t2 = tfac * rcp64(qe);
+          t2 = tfac == 0.0 ? 0.0 : tfac * rcp64(qe);     // n = 1 is defined at q = 0
         }
         const double E1x = 2.0 * exx + eyy, E2y = exx + 2.0 * eyy;
         const double mx = flip(px, minus), my = flip(py, minus), mz = flip(iz, minus);
@@ -863,7 +863,7 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
         if constexpr (N3) mu = m.visc_pref * rcbrt64(qe);
         else mu = m.visc_pref * powq(qe, m.visc_exp);
         s2[zi] = 2.0 * mu * Wz;
-        t2[zi] = (mu * rcp64(qe)) * (tfac * Wz);
+        t2[zi] = !N3 && tfac == 0.0 ? 0.0 : (mu * rcp64(qe)) * (tfac * Wz);     // n = 1 is defined at q = 0
         E1x[zi] = 2.0 * exx + eyy;
         Exy[zi] = exy;
         E2y[zi] = exx + 2.0 * eyy;
@@ -1138,7 +1138,7 @@ __device__ __forceinline__ void tet_task(const MeshView &m, const int4 task, con
         t2[q] = (s2[q] * tfac) * (y * y * y);
       } else {
         s2[q] = powq(qe, m.visc_exp) * W;
-        t2[q] = (s2[q] * tfac) * rcp64(qe);
+        t2[q] = tfac == 0.0 ? 0.0 : (s2[q] * tfac) * rcp64(qe);     // n = 1 is defined at q = 0
       }
       E1x[q] = 2.0 * exx + eyy; Exy[q] = exy; E2y[q] = exx + 2.0 * eyy; Exz[q] = exz; Eyz[q] = eyz;
       if (q < 2) {      // on to the next plane: column q's node moves up

@@ -515,3 +515,26 @@ def test_fp32_entries_are_summed_in_fp64(L):
                 want, got = J64[r, c], J32[r, c]
                 print(f"[fp32 sums] L={L} ({v},{w}) J64 {want:.9e} J32 {got:.9e}", flush=True)
                 assert want != 0.0 and abs(got - want) <= 2.0 ** -15 * abs(want)
+
+
+@pytest.mark.parametrize("elem", ["wedge", "tet", "hex"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_constant_viscosity_needs_no_strain(elem, dtype):
+    """n = 1: the viscosity is a constant, so at zero strain rate without regularisation (where a power
+    of the strain rate has no derivative) the Jacobian is the one of any other velocity, bit for bit, with and
+    without the viscosity-derivative term, which is zero; single meshes and ensembles alike."""
+    from paper_2204_04321_amd.api import Ensemble
+    m, U = _box(4, 3, 3, elem, 41)
+    m = m.with_fields(n=1.0, A=1e-6)
+    M, M0 = gpu_mesh(m), gpu_mesh(m.with_fields(eps0=0.0))
+    zero = torch.zeros(M.n_dofs, dtype=torch.float64, device="cuda")
+    for kind in ("picard", "newton"):
+        _, want = M.jacobian(to_dev(U), dtype=dtype, kind=kind)
+        _, J = M0.jacobian(zero, dtype=dtype, kind=kind)
+        Je, R = torch.full_like(J, float("nan")), torch.empty_like(zero)
+        Ensemble([M0]).assemble([zero], [R], [Je], dtype=dtype, kind=kind)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(want).all()) and torch.equal(J, want) and torch.equal(Je, want), kind
+        Ro, Jo = fo.assemble(m, U, picard=True)
+        bar = TOL64 if dtype == "f64" else 1e-5
+        assert np.abs(gpu_jacobian(M0, 0 * U, dtype, kind)[1] - Jo).max() <= bar * np.abs(Jo.data).max()
