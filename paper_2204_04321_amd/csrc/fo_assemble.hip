@@ -190,8 +190,8 @@ __device__ __forceinline__ FlatCopy<N> flat_copy(const MeshView &m, const TaskCo
   return f;
 }
 
-// Copies a finished interior level's window to its CSR rows and clears it for level + 2
-// (store = false: clears it only); all LDS reads are issued before the first store.
+// Copies a finished level's window to its rows and clears it for level + 2 (store = false: clears it
+// only); all LDS reads are issued before the first store.  With a Jacobian, interior levels only.
 template <bool JAC, int N, class JT>
 __device__ __forceinline__ void copy_out_flat(const FlatCopy<N> &f, int lev, int slot, bool store, int vb, int nvt, int L,
                                               double *Jw, double *Rw, int max_slot, int max_tv, int lane,
@@ -224,7 +224,7 @@ __device__ __forceinline__ void copy_out_flat(const FlatCopy<N> &f, int lev, int
 // the first global store, so one LDS latency is exposed per batch, not per chunk.  Each lane moves
 // two consecutive entries: one 16-byte LDS read and one 16-byte clearing write per column cover
 // up to 128 entries (degree <= 10 on three levels).
-template <bool JAC, class JT>
+template <class JT>
 __device__ __forceinline__ void copy_out(const TaskColumns &cols, int lev, int slot, bool store, int vb, int nvt,
                                          int L, double *Jw, double *Rw, int max_slot, int max_tv, int lane,
                                          double *__restrict__ R, JT *__restrict__ J) {
@@ -232,36 +232,34 @@ __device__ __forceinline__ void copy_out(const TaskColumns &cols, int lev, int s
   const int lk = cumlev(lev);
   double *wb = Jw + slot * max_slot;   // 16-byte aligned, as is every column's slot
   for (int i0 = 0; i0 < nvt; i0 += 4) {
-    if constexpr (JAC) {
-      double2 val[4];
-      int nn[4], so[4];
+    double2 val[4];
+    int nn[4], so[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ii = i0 + i < nvt ? i0 + i : nvt - 1;
-        so[i] = __builtin_amdgcn_readlane(cols.soff, ii);
-        nn[i] = i0 + i < nvt ? 4 * nl * __builtin_amdgcn_readlane(cols.deg, ii) : 0;
-        const int e = 2 * lane;
-        val[i] = *reinterpret_cast<const double2 *>(wb + so[i] + (e < nn[i] ? e : 0));
+    for (int i = 0; i < 4; ++i) {
+      const int ii = i0 + i < nvt ? i0 + i : nvt - 1;
+      so[i] = __builtin_amdgcn_readlane(cols.soff, ii);
+      nn[i] = i0 + i < nvt ? 4 * nl * __builtin_amdgcn_readlane(cols.deg, ii) : 0;
+      const int e = 2 * lane;
+      val[i] = *reinterpret_cast<const double2 *>(wb + so[i] + (e < nn[i] ? e : 0));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i0 + i >= nvt) break;
+      const int ii = i0 + i;
+      const int D = __builtin_amdgcn_readlane(cols.deg, ii);
+      const int64_t col = int64_t(unsigned(__builtin_amdgcn_readlane(cols.col_lo, ii))) |
+                          (int64_t(__builtin_amdgcn_readlane(cols.col_hi, ii)) << 32);
+      JT *dst = J + col + int64_t(4) * D * lk;
+      double *src = wb + so[i];
+      const int e = 2 * lane;   // nn is a multiple of 4, so e < nn implies e + 1 < nn
+      if (e < nn[i]) {
+        if (store) store2_nt(dst + e, val[i].x, val[i].y);
+        *reinterpret_cast<double2 *>(src + e) = make_double2(0.0, 0.0);
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (i0 + i >= nvt) break;
-        const int ii = i0 + i;
-        const int D = __builtin_amdgcn_readlane(cols.deg, ii);
-        const int64_t col = int64_t(unsigned(__builtin_amdgcn_readlane(cols.col_lo, ii))) |
-                            (int64_t(__builtin_amdgcn_readlane(cols.col_hi, ii)) << 32);
-        JT *dst = J + col + int64_t(4) * D * lk;
-        double *src = wb + so[i];
-        const int e = 2 * lane;   // nn is a multiple of 4, so e < nn implies e + 1 < nn
-        if (e < nn[i]) {
-          if (store) store2_nt(dst + e, val[i].x, val[i].y);
-          *reinterpret_cast<double2 *>(src + e) = make_double2(0.0, 0.0);
-        }
-        for (int f = e + 2 * WAVE; f < nn[i]; f += 2 * WAVE) {
-          const double2 w = *reinterpret_cast<const double2 *>(src + f);
-          if (store) store2_nt(dst + f, w.x, w.y);
-          *reinterpret_cast<double2 *>(src + f) = make_double2(0.0, 0.0);
-        }
+      for (int f = e + 2 * WAVE; f < nn[i]; f += 2 * WAVE) {
+        const double2 w = *reinterpret_cast<const double2 *>(src + f);
+        if (store) store2_nt(dst + f, w.x, w.y);
+        *reinterpret_cast<double2 *>(src + f) = make_double2(0.0, 0.0);
       }
     }
     if (lane < 8 && i0 + (lane >> 1) < nvt) {
@@ -270,6 +268,22 @@ __device__ __forceinline__ void copy_out(const TaskColumns &cols, int lev, int s
       if (R && store) R[2 * (int64_t(u) * (L + 1) + lev) + (lane & 1)] = *rs;
       *rs = 0.0;
     }
+  }
+}
+
+// A finished level by its kind: with a Jacobian the rows of the first and the last level (two levels each)
+// leave gaps in the columns' slots.  The residual alone has no slots, so any level goes in one piece
+// (one-layer sheet of 125,000 columns: 40 -> 38 us).
+template <bool JAC, int N, class JT>
+__device__ __forceinline__ void copy_level(const FlatCopy<N> &f, const TaskColumns &cols, int lev, int slot, bool store,
+                                           int vb, int nvt, int L, double *Jw, double *Rw, int max_slot, int max_tv,
+                                           int lane, double *__restrict__ R, JT *__restrict__ J) {
+  if constexpr (!JAC) {
+    copy_out_flat<false>(f, lev, slot, store, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+  } else if (lev > 0 && lev < L && f.slot_size > 0) {
+    copy_out_flat<true>(f, lev, slot, store, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+  } else {
+    copy_out(cols, lev, slot, store, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
   }
 }
 
@@ -311,7 +325,9 @@ __device__ __forceinline__ float quad_xor(float v) {
 // With a Jacobian it is bound by FP64 issue and the LDS adds alike (ice sheet of 125,000 columns of
 // 10 layers: vector units 76% busy while two waves share a SIMD, the LDS 66% of the kernel's
 // time); the residual alone, four waves per SIMD, by vector issue.  R+J 705 -> 551-575 us in FP64 and
-// 670 -> 519 us with FP32 values, residual 175-180 -> 152 us, against one lane per item.  The parts:
+// 670 -> 519 us with FP32 values, residual 175-180 -> 151 us, against one lane per item (of one layer
+// R+J 140 -> 126 us, but the residual 34.5 -> 38: both lanes of an item load and work out its
+// constants; from two layers on it is even, from three faster).  The parts:
 // the split itself, with the constants in LDS, -7%; items of one vertex spread over the wave
 // (below) -5%; sigma through scalar loads and the wait before the copy-out -2%; the copy-out of a
 // level in one piece -6%.  Carrying the shared entries in FP64 too spills (+5%).
@@ -354,6 +370,16 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
   int vid[3] = {0, 0, 0}, Dv = 0, soff = 0, rloc = 0;
   uint32_t rk = 0u;
   bool act = false;
+  auto gather = [&](int lev, double2 (&a)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      a[i] = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[i]) * (L + 1) + lev));
+  };
+  const int k0 = kb > 0 ? kb - 1 : 0;
+  double2 lo[3], up[3];                       // u, v of the corners on levels k and k + 1
+  // a layer's upper velocities are kept for the next one's lower level, and those above loaded a
+  // layer ahead; with a Jacobian the general power's constants leave no registers for either
+  constexpr bool AHEAD = N3 && !PASSES;
   auto load_item = [&](int first) {
     act = first + slot < ie;
     const int item = act ? first + slot : ib;
@@ -365,6 +391,10 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
     rk = (rk >> (8 * rot)) | (rk << (8 * (3 - rot)));   // the low three bytes
 #pragma unroll
     for (int i = 0; i < 3; ++i) vid[i] = m.cells[3 * int64_t(t) + (i + rot >= 3 ? i + rot - 3 : i + rot)];
+    if constexpr (AHEAD) {      // with the geometry's loads (one layer of 125,000 columns, R alone: 42 -> 40 us)
+      gather(k0, lo);
+      gather(k0 + 1, up);
+    }
     double4 g[3];
     double s[3], lx[3], ly[3], c[PRISM_CONST];
 #pragma unroll
@@ -403,11 +433,6 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
     }
     wave_sync();
   };
-  auto gather = [&](int lev, double2 (&a)[3]) {
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-      a[i] = *reinterpret_cast<const double2 *>(U + 2 * (int64_t(vid[i]) * (L + 1) + lev));
-  };
   // slopes of u and v along x and y on one level
   struct Slopes { double ux, uy, vx, vy; };
   auto slopes = [&](const double2 (&a)[3]) {
@@ -422,12 +447,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
   };
   wave_sync();
 
-  const int k0 = kb > 0 ? kb - 1 : 0;
-  double2 lo[3], up[3];                       // u, v of the corners on levels k and k + 1
   Slopes f0 = {0, 0, 0, 0};
-  // a layer's upper velocities are kept for the next one's lower level, and those above loaded a
-  // layer ahead; the general power's constants leave no registers for either
-  constexpr bool AHEAD = N3 && !PASSES;
   constexpr bool CARRY = sizeof(JT) == 4;
   AT carry[4][3];                             // lane z = 0: the upper row at the upper level of the layer below
 #pragma unroll
@@ -440,7 +460,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
   if (kb == 0) {
     for (int g = ib; PASSES ? g < ie : g == ib; g += PRISM_ITEMS) {
       load_item(g);
-      gather(0, lo);
+      if constexpr (!AHEAD) gather(0, lo);
       // face normal from the slopes of its z; basis products at the three points (2/3, 1/6, 1/6)
       const double bx = fma(m.sigma[0], c_[THK], c_[BED]), by = fma(m.sigma[0], c_[THK + 1], c_[BED + 1]);
       // the cell's doubled base area from its gradients: 1 / (lx_1 ly_2 - lx_2 ly_1)
@@ -475,9 +495,7 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
   if constexpr (!PASSES) {
     if (kb > 0) load_item(ib);
     if constexpr (AHEAD) {
-      gather(k0, lo);
       f0 = slopes(lo);
-      gather(k0 + 1, up);
       asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));   // waited for here, as below
     }
   }
@@ -635,11 +653,8 @@ __device__ __forceinline__ void prism_task(const MeshView &m, const int4 task, c
     // The copy-out runs at raised wave priority (2), the window adds at 1: the copy-out's LDS reads
     // and streaming stores then issue ahead of the other waves' work instead of queuing behind it.
     __builtin_amdgcn_s_setprio(2);
-    if (k > 0 && (!JAC || flat.slot_size > 0))
-      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    else
-      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    copy_level<JAC>(flat, cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_level<JAC>(flat, cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     wave_sync();
     __builtin_amdgcn_s_setprio(0);
   }
@@ -943,11 +958,8 @@ __device__ __forceinline__ void hex_task(const MeshView &m, const int4 task, con
     if constexpr (!PASSES) asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y), "+v"(up[3].x), "+v"(up[3].y));
     wave_sync();
     __builtin_amdgcn_s_setprio(2);
-    if (k > 0 && (!JAC || flat.slot_size > 0))
-      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    else
-      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    copy_level<JAC>(flat, cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_level<JAC>(flat, cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     wave_sync();
     __builtin_amdgcn_s_setprio(0);
   }
@@ -1223,11 +1235,8 @@ __device__ __forceinline__ void tet_task(const MeshView &m, const int4 task, con
       asm volatile("" : "+v"(up[0].x), "+v"(up[0].y), "+v"(up[1].x), "+v"(up[1].y), "+v"(up[2].x), "+v"(up[2].y));
     wave_sync();
     __builtin_amdgcn_s_setprio(2);
-    if (k > 0 && (!JAC || flat.slot_size > 0))
-      copy_out_flat<JAC>(flat, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    else
-      copy_out<JAC>(cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
-    if (k == L - 1) copy_out<JAC>(cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    copy_level<JAC>(flat, cols, k, cur, k >= kb, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
+    if (k == L - 1) copy_level<JAC>(flat, cols, L, nxt, true, vb, nvt, L, Jw, Rw, max_slot, max_tv, lane, R, J);
     wave_sync();
     __builtin_amdgcn_s_setprio(0);
   }
